@@ -1769,7 +1769,9 @@ int db_checkpoint_load(db_ctx* c, const void* buf, size_t bytes) {
     c->list_valid = h.list_valid;
     c->tiles_valid = h.tiles_valid;
     c->regions_valid = h.regions_valid;
-    c->halo_force = h.halo_force;
+    // the halo follows from the tables: rebuilt here, so that a checkpoint written with
+    // another coding of its entries continues with this one's
+    c->halo_force = true;
     c->halo_sweep = h.halo_sweep;
     c->have_state = true;
     c->have_topology = h.have_topology;

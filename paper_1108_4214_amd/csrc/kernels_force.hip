@@ -66,22 +66,82 @@ __device__ __forceinline__ R r_sqrt(R v);
 template <>
 __device__ __forceinline__ double r_sqrt<double>(double v) { return sqrt(v); }
 template <>
-__device__ __forceinline__ float r_sqrt<float>(float v) { return sqrtf(v); }
-// reciprocal and reciprocal square root: IEEE in double; in float the native
-// single-instruction approximations (about 1 ulp), far inside the float path's
-// error budget
+__device__ __forceinline__ float r_sqrt<float>(float v) { return __builtin_amdgcn_sqrtf(v); }
+// Reciprocal and reciprocal square root.  In float the native single-instruction
+// approximations (about 1 ulp), far inside the float path's error budget.  In
+// double the native approximation (relative error e0 below 2^-23) and one
+// third-order step, 1/v = y (1 + e + e^2) with e = 1 - v y and v^-1/2 =
+// y (1 + e/2 + 3 e^2/8) with e = 1 - v y^2, whose remainder is of order e^3 <
+// 2^-67: correct to about one rounding, in four and six instructions where the
+// IEEE division and square root take about ten each.  v > 0 and normal.
 template <typename R>
 __device__ __forceinline__ R r_rcp(R v);
 template <>
-__device__ __forceinline__ double r_rcp<double>(double v) { return 1.0 / v; }
+__device__ __forceinline__ double r_rcp<double>(double v) {
+    const double y = __builtin_amdgcn_rcp(v);
+    const double e = fma(-v, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
 template <>
 __device__ __forceinline__ float r_rcp<float>(float v) { return __builtin_amdgcn_rcpf(v); }
 template <typename R>
 __device__ __forceinline__ R r_rsqrt(R v);
 template <>
-__device__ __forceinline__ double r_rsqrt<double>(double v) { return 1.0 / sqrt(v); }
+__device__ __forceinline__ double r_rsqrt<double>(double v) {
+    const double y = __builtin_amdgcn_rsq(v);
+    const double e = fma(-(v * y), y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
 template <>
 __device__ __forceinline__ float r_rsqrt<float>(float v) { return __builtin_amdgcn_rsqf(v); }
+__device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// three components of the force type, with fused products (the build contracts
+// nothing by itself)
+template <typename R>
+struct V3 {
+    R x, y, z;
+};
+template <typename R>
+__device__ __forceinline__ R dot(const V3<R>& a, const V3<R>& b) {
+    return mad(a.z, b.z, mad(a.y, b.y, a.x * b.x));
+}
+template <typename R>
+__device__ __forceinline__ V3<R> cross(const V3<R>& a, const V3<R>& b) {
+    return V3<R>{mad(a.y, b.z, -(a.z * b.y)), mad(a.z, b.x, -(a.x * b.z)), mad(a.x, b.y, -(a.y * b.x))};
+}
+template <typename R>
+__device__ __forceinline__ V3<R> sub(const V3<R>& a, const V3<R>& b) {
+    return V3<R>{a.x - b.x, a.y - b.y, a.z - b.z};
+}
+// a - k b
+template <typename R>
+__device__ __forceinline__ V3<R> sub_scaled(const V3<R>& a, R k, const V3<R>& b) {
+    return V3<R>{mad(-k, b.x, a.x), mad(-k, b.y, a.y), mad(-k, b.z, a.z)};
+}
+
+// asin(s) / s for s^2 = t <= 1/2: the polynomial through its values at the Chebyshev
+// nodes of [0, 1/2] (relative error below 3e-9 with nine terms, 4e-18 with twenty)
+__device__ __forceinline__ float asin_ratio(float t) {
+    constexpr float c[9] = {1.000000002f, 0.1666661424f, 0.07502757316f, 0.04409161673f, 0.03581423928f,
+                            -0.007020579152f, 0.1074000213f, -0.1359162712f, 0.1239134949f};
+    float p = c[8];
+#pragma unroll
+    for (int k = 7; k >= 0; --k) p = mad(p, t, c[k]);
+    return p;
+}
+__device__ __forceinline__ double asin_ratio(double t) {
+    constexpr double c[20] = {0.999999999999999998, 0.166666666666669623, 0.074999999999216023, 0.0446428572251978305,
+                               0.0303819398816733953, 0.0223723131724858034, 0.0173493103271581963, 0.0140191720400696588,
+                               0.0109293490649123701, 0.0150917950285833644, -0.0263163245523388273, 0.180957462091106506,
+                               -0.664123630254941186, 2.00160411092915451, -4.53579180282295538, 7.76816537455500807,
+                               -9.66965939855062292, 8.32498352944691134, -4.43881669206693937, 1.12641928788075076};
+    double p = c[19];
+#pragma unroll
+    for (int k = 18; k >= 0; --k) p = mad(p, t, c[k]);
+    return p;
+}
 template <typename R>
 __device__ __forceinline__ R r_atan2(R y, R x);
 template <>
@@ -139,9 +199,9 @@ __device__ __forceinline__ void pair_term(const Params& P, const Box& X, const d
     R sr2 = (R)P.sig2 * ir2;
     R sr6 = sr2 * sr2 * sr2;
     R fr = (R)24.0 * (R)P.eps * ((R)2.0 * sr6 * sr6 - sr6) * ir2;   // -dU/dr / r
-    a.fx -= (double)(fr * rx);
-    a.fy -= (double)(fr * ry);
-    a.fz -= (double)(fr * rz);
+    a.fx = fma(-(double)fr, dx, a.fx);
+    a.fy = fma(-(double)fr, dy, a.fy);
+    a.fz = fma(-(double)fr, dz, a.fz);
     if (MODE == MODE_ENERGY) {
         a.e_pair += 0.5 * (double)((R)4.0 * (R)P.eps * (sr6 * sr6 - sr6) + (R)P.eps);
         a.vir += 0.5 * (double)(fr * r2);
@@ -156,10 +216,17 @@ __device__ __forceinline__ void pair_term(const Params& P, const Box& X, const d
 // cancel exactly.  Without THERMO only the conservative part is formed.
 template <typename R, bool THERMO, bool ENERGY>
 __device__ __forceinline__ void dpd_pair(const Params& P, const Box& X, const double4& xi, const double4& xj,
-                                         R rx, R ry, R rz, R r2, double dvx, double dvy, double dvz, int64_t step,
-                                         double dsig, Acc<R>& a) {
-    const R r = r_sqrt<R>(r2);
-    const R ir = r_rcp<R>(r);
+                                         double dx, double dy, double dz, R r2, double dvx, double dvy, double dvz,
+                                         int64_t step, double dsig, Acc<R>& a) {
+    const R rx = (R)dx, ry = (R)dy, rz = (R)dz;
+    R r, ir;
+    if constexpr (sizeof(R) == 4) {
+        r = sqrtf(r2);
+        ir = r_rcp<R>(r);
+    } else {
+        ir = r_rsqrt<R>(r2);
+        r = r2 * ir;
+    }
     const R w = (R)1.0 - r * (R)P.inv_rc;
     R f = (R)P.dpd_a * w;
     if (ENERGY) {
@@ -174,9 +241,17 @@ __device__ __forceinline__ void dpd_pair(const Params& P, const Box& X, const do
         f += -(R)P.dpd_gamma * w * w * ev + (R)dsig * w * xg;
     }
     const R fi = f * ir;
-    a.fx -= (double)(fi * rx);
-    a.fy -= (double)(fi * ry);
-    a.fz -= (double)(fi * rz);
+    if constexpr (sizeof(R) == 4) {
+        // products rounded to float: their double sums hardly round, so a bead's force
+        // does not depend on the order of its list (lists of other skins, batches)
+        a.fx -= (double)(fi * rx);
+        a.fy -= (double)(fi * ry);
+        a.fz -= (double)(fi * rz);
+    } else {
+        a.fx = fma(-fi, dx, a.fx);
+        a.fy = fma(-fi, dy, a.fy);
+        a.fz = fma(-fi, dz, a.fz);
+    }
 }
 
 // pair forces over the 27 cells (energy evaluation); vi and dsig feed the DPD
@@ -224,11 +299,11 @@ __device__ void pair_forces(const Params& P, const Box& X, const Bank& B, const 
                     if (P.pair_style == PAIR_DPD) {
                         const int n = P.n;
                         if (P.dpd_gamma != 0.0)
-                            dpd_pair<R, true, MODE == MODE_ENERGY>(P, X, xi, xj, rx, ry, rz, r2, vix - B.v[j],
+                            dpd_pair<R, true, MODE == MODE_ENERGY>(P, X, xi, xj, dx, dy, dz, r2, vix - B.v[j],
                                                                    viy - B.v[n + j], viz - B.v[2 * n + j], step,
                                                                    dsig, a);
                         else
-                            dpd_pair<R, false, MODE == MODE_ENERGY>(P, X, xi, xj, rx, ry, rz, r2, 0, 0, 0, 0, 0,
+                            dpd_pair<R, false, MODE == MODE_ENERGY>(P, X, xi, xj, dx, dy, dz, r2, 0, 0, 0, 0, 0,
                                                                     a);
                     } else {
                         pair_term<R, MODE>(P, X, xi, xj, a);
@@ -444,20 +519,23 @@ __global__ __launch_bounds__(DB_BLOCK) void k_patch_nlist(const Params* __restri
 // Entries are taken four at a time: the four indices, then the four positions are
 // requested before any of them is used, so one bead keeps several loads in flight.
 template <typename R>
-__device__ __forceinline__ void pair_one(const Params& P, const Box& X, const double4& xi, const double4& xj, R rc2, Acc<R>& a) {
-    R rx = (R)near_image(xj.x - xi.x, X);
-    R ry = (R)near_image(xj.y - xi.y, X);
-    R rz = (R)near_image(xj.z - xi.z, X);
-    R r2 = (rx * rx + ry * ry) + rz * rz;
+__device__ __forceinline__ void pair_sep(const Params& P, double dx, double dy, double dz, R rc2, Acc<R>& a) {
+    const R rx = (R)dx, ry = (R)dy, rz = (R)dz;
+    const R r2 = mad(rz, rz, mad(ry, ry, rx * rx));
     if (r2 < rc2) {
-        R ir2 = r_rcp<R>(r2);
-        R sr2 = (R)P.sig2 * ir2;
-        R sr6 = sr2 * sr2 * sr2;
-        R fr = (R)24.0 * (R)P.eps * ((R)2.0 * sr6 * sr6 - sr6) * ir2;
-        a.fx -= (double)(fr * rx);
-        a.fy -= (double)(fr * ry);
-        a.fz -= (double)(fr * rz);
+        const R ir2 = r_rcp<R>(r2);
+        const R sr2 = (R)P.sig2 * ir2;
+        const R sr6 = sr2 * sr2 * sr2;
+        // the separation is at hand in double: one conversion and three fused adds
+        const double fr = (double)((R)24.0 * (R)P.eps * mad((R)2.0 * sr6, sr6, -sr6) * ir2);
+        a.fx = fma(-fr, dx, a.fx);
+        a.fy = fma(-fr, dy, a.fy);
+        a.fz = fma(-fr, dz, a.fz);
     }
+}
+template <typename R>
+__device__ __forceinline__ void pair_one(const Params& P, const Box& X, const double4& xi, const double4& xj, R rc2, Acc<R>& a) {
+    pair_sep<R>(P, near_image(xj.x - xi.x, X), near_image(xj.y - xi.y, X), near_image(xj.z - xi.z, X), rc2, a);
 }
 
 // entries of the Verlet list requested together: eight in the FP64 WCA kernel
@@ -477,9 +555,10 @@ __device__ __forceinline__ void list_pair_forces(const Params& P, const Box& X, 
     constexpr int Q = pair_batch<R, PAIR_WCA>();
     const int n = P.n;
     const R rc2 = (R)P.rc2;
+    const int i0 = __builtin_amdgcn_readfirstlane(i);   // read by the lanes past their list: one line for all of them
     int j[Q];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) j[q] = q < m ? jpre[q] : i;
+    for (int q = 0; q < Q; ++q) j[q] = q < m ? jpre[q] : i0;
     for (int k0 = 0; k0 < m; k0 += Q) {
         double4 xj[Q];
 #pragma unroll
@@ -487,7 +566,7 @@ __device__ __forceinline__ void list_pair_forces(const Params& P, const Box& X, 
         // the next batch's entries are requested before this batch is evaluated
         const int k1 = k0 + Q;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) j[q] = k1 + q < m ? NL.nl[(k1 + q) * n + i] : i;
+        for (int q = 0; q < Q; ++q) j[q] = k1 + q < m ? NL.nl[(k1 + q) * n + i] : i0;
 #pragma unroll
         for (int q = 0; q < Q; ++q)
             if (k0 + q < m) pair_one<R>(P, X, xi, xj[q], rc2, a);
@@ -508,11 +587,12 @@ __device__ __forceinline__ void list_pair_dpd(const Params& P, const Box& X, con
     constexpr int Q = pair_batch<R, PAIR_DPD>();
     const int n = P.n;
     const R rc2 = (R)P.rc2;
+    const int i0 = __builtin_amdgcn_readfirstlane(i);   // read by the lanes past their list: one line for all of them
     for (int k0 = 0; k0 < m; k0 += Q) {
         int j[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q)
-            j[q] = (k0 + q < m) ? (k0 == 0 ? jpre[q] : NL.nl[(k0 + q) * n + i]) : i;
+            j[q] = (k0 + q < m) ? (k0 == 0 ? jpre[q] : NL.nl[(k0 + q) * n + i]) : i0;
         double4 xj[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) xj[q] = B.x[j[q]];
@@ -526,9 +606,10 @@ __device__ __forceinline__ void list_pair_dpd(const Params& P, const Box& X, con
         }
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            const R rx = (R)near_image(xj[q].x - xi.x, X);
-            const R ry = (R)near_image(xj[q].y - xi.y, X);
-            const R rz = (R)near_image(xj[q].z - xi.z, X);
+            const double dx = near_image(xj[q].x - xi.x, X);
+            const double dy = near_image(xj[q].y - xi.y, X);
+            const double dz = near_image(xj[q].z - xi.z, X);
+            const R rx = (R)dx, ry = (R)dy, rz = (R)dz;
             const R r2 = (rx * rx + ry * ry) + rz * rz;
             if ((k0 + q < m) & (r2 < rc2)) {
                 if (THERMO) {
@@ -538,168 +619,128 @@ __device__ __forceinline__ void list_pair_dpd(const Params& P, const Box& X, con
                         vjy[q] = B.v[n + jq];
                         vjz[q] = B.v[2 * n + jq];
                     }
-                    dpd_pair<R, true, false>(P, X, xi, xj[q], rx, ry, rz, r2, vix - vjx[q], viy - vjy[q],
+                    dpd_pair<R, true, false>(P, X, xi, xj[q], dx, dy, dz, r2, vix - vjx[q], viy - vjy[q],
                                              viz - vjz[q], step, dsig, a);
                 } else {
-                    dpd_pair<R, false, false>(P, X, xi, xj[q], rx, ry, rz, r2, 0, 0, 0, 0, 0, a);
+                    dpd_pair<R, false, false>(P, X, xi, xj[q], dx, dy, dz, r2, 0, 0, 0, 0, 0, a);
                 }
             }
         }
     }
 }
 
-// harmonic bond U = K (r - r0)^2 with the type bead i stores (all partners requested at once)
+// harmonic bond U = K (r - r0)^2, K and r0 of type t, on the separation d = x_j - x_i;
+// the cutoff decision is taken in double, whatever the force type
 template <typename R, int MODE>
-__device__ __forceinline__ void bond_terms(const Params& P, const Box& X, const Coef<R>& C, const Bank& B, int i, const double4& xi, int nb,
+__device__ __forceinline__ void bond_force(const Params& P, const Coef<R>& C, int t, double dx, double dy, double dz,
                                            Acc<R>& a) {
-    const int n = P.n;
-    int jj[DB_MAXB], tt[DB_MAXB];
-#pragma unroll
-    for (int k = 0; k < DB_MAXB; ++k) {
-        jj[k] = k < nb ? B.bp[k * n + i] : i;
-        tt[k] = k < nb ? (int)B.bt[k * n + i] & (DB_MAXT - 1) : 0;
-    }
-    double4 xs[DB_MAXB];
-#pragma unroll
-    for (int k = 0; k < DB_MAXB; ++k) xs[k] = B.x[jj[k]];
-#pragma unroll
-    for (int k = 0; k < DB_MAXB; ++k) {
-        if (k >= nb) continue;
-        const double4& xj = xs[k];
-        const int t = tt[k];
-        double dx = near_image(xj.x - xi.x, X);
-        double dy = near_image(xj.y - xi.y, X);
-        double dz = near_image(xj.z - xi.z, X);
-        // the cutoff decision in double, whatever the force type
-        const double rd2 = (dx * dx + dy * dy) + dz * dz;
-        if (!(rd2 > 0.0) || !(rd2 < C.bRc2[t])) continue;
-        R rx = (R)dx, ry = (R)dy, rz = (R)dz;
-        R rr2 = (rx * rx + ry * ry) + rz * rz;
-        R ir = r_rsqrt<R>(rr2);
-        R r = rr2 * ir;
-        R K = C.bK[t], r0 = C.bR0[t];
-        R g = (R)2.0 * K * (r - r0) * ir;   // F_i = g * (x_j - x_i)
-        a.fx += (double)(g * rx);
-        a.fy += (double)(g * ry);
-        a.fz += (double)(g * rz);
-        if (MODE == MODE_ENERGY) {
-            a.e_bond += 0.5 * ((double)(K * (r - r0) * (r - r0)) + P.bE0[t]);
-            a.vir -= 0.5 * (double)(g * r * r);
-        }
-    }
-}
-
-// harmonic angle U = K (theta - theta0)^2 on u = x_a - x_b, w = x_c - x_b; the
-// bead takes the force of its role (0: end a, 1: centre b, 2: end c)
-template <typename R, int MODE>
-__device__ __forceinline__ void angle_core(const Coef<R>& C, int role, int t, R ux, R uy, R uz, R wx, R wy, R wz,
-                                           Acc<R>& a) {
-    R ru2 = (ux * ux + uy * uy) + uz * uz;
-    R rw2 = (wx * wx + wy * wy) + wz * wz;
-    if (!(ru2 > (R)0) || !(rw2 > (R)0)) return;
-    R iru = r_rsqrt<R>(ru2), irw = r_rsqrt<R>(rw2);
-    R cux = ux * iru, cuy = uy * iru, cuz = uz * iru;
-    R cwx = wx * irw, cwy = wy * irw, cwz = wz * irw;
-    R cs = (cux * cwx + cuy * cwy) + cuz * cwz;
-    R crx = cuy * cwz - cuz * cwy, cry = cuz * cwx - cux * cwz, crz = cux * cwy - cuy * cwx;
-    R sn = r_sqrt<R>((crx * crx + cry * cry) + crz * crz);
-    R K = C.aK[t];
-    // dU/dtheta / sin(theta), finite at theta = pi when theta0 = pi
-    R del = r_atan2<R>(sn, -cs);   // pi - theta
-    R isn = r_rcp<R>(sn > (R)1e-8 ? sn : (R)1e-8);
-    R ratio = del < (R)1e-6 ? (R)1.0 + del * del * (R)(1.0 / 6.0) : del * isn;
-    R pth = C.aPm[t];
-    R A = (R)2.0 * K * (-ratio + (pth != (R)0 ? pth * isn : (R)0));
-    R Au = -A * iru, Aw = -A * irw;
-    R fax = Au * (cs * cux - cwx), fay = Au * (cs * cuy - cwy), faz = Au * (cs * cuz - cwz);
-    R fcx = Aw * (cs * cwx - cux), fcy = Aw * (cs * cwy - cuy), fcz = Aw * (cs * cwz - cuz);
-    if (role == 0) {
-        a.fx += (double)fax; a.fy += (double)fay; a.fz += (double)faz;
-    } else if (role == 2) {
-        a.fx += (double)fcx; a.fy += (double)fcy; a.fz += (double)fcz;
-    } else {
-        a.fx -= (double)(fax + fcx); a.fy -= (double)(fay + fcy); a.fz -= (double)(faz + fcz);
-    }
+    const double rd2 = (dx * dx + dy * dy) + dz * dz;
+    if (!(rd2 > 0.0) || !(rd2 < C.bRc2[t])) return;
+    const R rr2 = (R)rd2;
+    const R ir = r_rsqrt<R>(rr2);
+    const R r = rr2 * ir;
+    const R K = C.bK[t], dr = r - C.bR0[t];
+    const R g = (R)2.0 * K * dr * ir;   // F_i = g * (x_j - x_i)
+    a.fx = fma((double)g, dx, a.fx);
+    a.fy = fma((double)g, dy, a.fy);
+    a.fz = fma((double)g, dz, a.fz);
     if (MODE == MODE_ENERGY) {
-        R th = r_atan2<R>(sn, cs);
-        R th0 = C.aT0[t];
-        a.e_ang += (double)(K * (th - th0) * (th - th0)) / 3.0;
-        a.vir += (double)((ux * fax + uy * fay + uz * faz) + (wx * fcx + wy * fcy + wz * fcz)) / 3.0;
+        a.e_bond += 0.5 * ((double)(K * dr * dr) + P.bE0[t]);
+        a.vir -= 0.5 * (double)(g * r * r);
     }
 }
 
-// angle entry e = (a, b, c, type) of bead i from the members' positions
+// A bead's share of an angle U = K (theta - theta0)^2, a - b - c with centre b.
+//
+// The step kernel is bound by VALU issue, most of it these terms, so they are laid
+// out for few instructions.  The potential is symmetric in its ends, so a bead is
+// either the centre or "end a".  With s1, s2 the separations of the other members
+// from the bead (centre: the ends; end: the centre, then the far end), both roles
+// come down to one pair of vectors, s1 and w = s2 (centre) or s2 - s1 (end: from the
+// centre to the far end), up to the sign sg of s1, and the bead's force is al s1 +
+// be w with al, be chosen by role: nothing is formed for the other members and
+// nothing is selected per component.
+// theta enters as ratio = (pi - theta) / sin(theta), regular at the straight angle:
+// for bends up to 45 degrees from straight, asin_ratio of sin^2, without square
+// root or arctangent; a wave that holds a wider bend takes those too.
+// Step kernel, before and after these two functions: FP64 20.6 -> 15.5 us (80k-bead
+// duplex box), 175 -> 149 us (400k beads, 1-bead model in DPD solvent); FP32 69.9 ->
+// 66.8 us with 28.4M -> 20.8M VALU instructions per launch (1M-bead duplex box: its
+// gathers now weigh as much, 26M L1 accesses).
 template <typename R, int MODE>
-__device__ __forceinline__ void angle_one(const Params& P, const Box& X, const Coef<R>& C, int i, const int4& e,
-                                          const double4& xa, const double4& xb, const double4& xc, Acc<R>& a) {
-    R ux = (R)near_image(xa.x - xb.x, X), uy = (R)near_image(xa.y - xb.y, X), uz = (R)near_image(xa.z - xb.z, X);
-    R wx = (R)near_image(xc.x - xb.x, X), wy = (R)near_image(xc.y - xb.y, X), wz = (R)near_image(xc.z - xb.z, X);
-    const int role = e.x == i ? 0 : (e.z == i ? 2 : 1);
-    angle_core<R, MODE>(C, role, e.w & (DB_MAXT - 1), ux, uy, uz, wx, wy, wz, a);
-}
-
-template <typename R, int MODE>
-__device__ __forceinline__ void angle_terms(const Params& P, const Box& X, const Coef<R>& C, const Bank& B, int i, int na,
+__device__ __forceinline__ void angle_share(const Coef<R>& C, bool centre, int t, const V3<R>& s1, const V3<R>& w,
                                             Acc<R>& a) {
-    const int n = P.n;
-    for (int k = 0; k < na; ++k) {
-        int4 e = B.ang[k * n + i];
-        angle_one<R, MODE>(P, X, C, i, e, B.x[e.x], B.x[e.y], B.x[e.z], a);
+    const R sg = centre ? (R)1 : (R)-1;
+    const R ru2 = dot(s1, s1), rw2 = dot(w, w);
+    if (!(ru2 > (R)0) || !(rw2 > (R)0)) return;
+    const R iru = r_rsqrt<R>(ru2), irw = r_rsqrt<R>(rw2);
+    const R q = iru * irw;
+    const R cs = sg * (dot(s1, w) * q);   // cos(theta)
+    const V3<R> cr = cross(s1, w);
+    const R sn2 = dot(cr, cr) * (q * q);
+    const R K = C.aK[t], pth = C.aPm[t];   // pth = pi - theta0
+    R ratio, del = (R)0;
+    if (cs < (R)0 && sn2 <= (R)0.5) {
+        ratio = asin_ratio(sn2);
+        if (MODE == MODE_ENERGY) del = ratio * r_sqrt<R>(sn2);
+    } else {
+        const R sn = r_sqrt<R>(sn2);
+        del = r_atan2<R>(sn, -cs);   // pi - theta
+        ratio = del < (R)1e-6 ? mad(del * del, (R)(1.0 / 6.0), (R)1) : del * r_rcp<R>(sn > (R)1e-8 ? sn : (R)1e-8);
     }
+    // dU/dtheta / sin(theta), finite at theta = pi when theta0 = pi
+    R A = -ratio;
+    if (pth != (R)0) A = mad(pth, r_rsqrt<R>(sn2 > (R)1e-16 ? sn2 : (R)1e-16), A);
+    A = (R)2.0 * K * A;
+    const R Au = -A * iru, Aw = -A * irw, p = Au * cs;
+    const R al = (centre ? Aw - p : p) * (sg * iru);
+    const R be = (centre ? mad(-Aw, cs, Au) : -Au) * irw;
+    a.fx += (double)mad(al, s1.x, be * w.x);
+    a.fy += (double)mad(al, s1.y, be * w.y);
+    a.fz += (double)mad(al, s1.z, be * w.z);
+    // the potential does not change under scaling: no virial
+    if (MODE == MODE_ENERGY) a.e_ang += (double)(K * (del - pth) * (del - pth)) / 3.0;
 }
 
-// cosine dihedral U = K [1 - cos(phi - phi0)], phi = atan2(|b2| b1.(b2 x b3), (b1 x b2).(b2 x b3))
-// on the bond vectors b1 = x_b - x_a, b2 = x_c - x_b, b3 = x_d - x_c; role 0..3 = a..d
+template <typename R>
+__device__ __forceinline__ V3<R> sep_of(const Box& X, const double4& xj, const double4& xi) {
+    return V3<R>{(R)near_image(xj.x - xi.x, X), (R)near_image(xj.y - xi.y, X), (R)near_image(xj.z - xi.z, X)};
+}
+
+// A bead's share of a cosine dihedral U = K [1 - cos(phi - phi0)], phi = atan2(|b2|
+// b1.(b2 x b3), (b1 x b2).(b2 x b3)) on the bond vectors b1 = x_b - x_a, b2 = x_c - x_b,
+// b3 = x_d - x_c.  phi is the same read from either end, so a bead is either end a
+// or the inner bead b.  s1: the separation from it of b (for an end) or a (for the
+// inner bead), so b1 = sg s1, and the bead's force is al m + be n, m = s1 x b2 and n =
+// b2 x b3, with al, be chosen by role: F_a = -dU g_a, F_b = -dU (qq g_d - (pp + 1)
+// g_a).
 template <typename R, int MODE>
-__device__ __forceinline__ void dihedral_core(const Coef<R>& C, int role, int t, R b1x, R b1y, R b1z, R b2x, R b2y,
-                                              R b2z, R b3x, R b3y, R b3z, Acc<R>& a) {
-    R mx = b1y * b2z - b1z * b2y, my = b1z * b2x - b1x * b2z, mz = b1x * b2y - b1y * b2x;
-    R nx = b2y * b3z - b2z * b3y, ny = b2z * b3x - b2x * b3z, nz = b2x * b3y - b2y * b3x;
-    R m2 = (mx * mx + my * my) + mz * mz;
-    R n2 = (nx * nx + ny * ny) + nz * nz;
-    R b22 = (b2x * b2x + b2y * b2y) + b2z * b2z;
+__device__ __forceinline__ void dihedral_share(const Coef<R>& C, bool end, int t, const V3<R>& s1, const V3<R>& b2,
+                                               const V3<R>& b3, Acc<R>& a) {
+    const R sg = end ? (R)1 : (R)-1;
+    const V3<R> m = cross(s1, b2), n = cross(b2, b3);
+    const R m2 = dot(m, m), n2 = dot(n, n), b22 = dot(b2, b2);
     if (m2 < (R)1e-24 || n2 < (R)1e-24 || b22 < (R)1e-24) return;   // collinear: no defined plane
-    R nb2 = r_sqrt<R>(b22);
-    R inv = r_rsqrt<R>(m2 * n2);
-    R cphi = ((mx * nx + my * ny) + mz * nz) * inv;
-    R sphi = nb2 * ((b1x * nx + b1y * ny) + b1z * nz) * inv;
-    R K = C.dK[t], c0 = C.dC0[t], s0 = C.dS0[t];
-    R dU = K * (sphi * c0 - cphi * s0);   // dU/dphi
-    R sa = -nb2 * r_rcp<R>(m2), sd = nb2 * r_rcp<R>(n2), ib22 = r_rcp<R>(b22);
-    R gax = sa * mx, gay = sa * my, gaz = sa * mz;
-    R gdx = sd * nx, gdy = sd * ny, gdz = sd * nz;
-    R pp = ((b1x * b2x + b1y * b2y) + b1z * b2z) * ib22;
-    R qq = ((b3x * b2x + b3y * b2y) + b3z * b2z) * ib22;
-    R fx, fy, fz;
-    if (role == 0) {
-        fx = -dU * gax; fy = -dU * gay; fz = -dU * gaz;
-    } else if (role == 3) {
-        fx = -dU * gdx; fy = -dU * gdy; fz = -dU * gdz;
-    } else if (role == 1) {
-        fx = -dU * (qq * gdx - (pp + (R)1) * gax);
-        fy = -dU * (qq * gdy - (pp + (R)1) * gay);
-        fz = -dU * (qq * gdz - (pp + (R)1) * gaz);
-    } else {
-        fx = -dU * (pp * gax - (qq + (R)1) * gdx);
-        fy = -dU * (pp * gay - (qq + (R)1) * gdy);
-        fz = -dU * (pp * gaz - (qq + (R)1) * gdz);
-    }
-    a.fx += (double)fx; a.fy += (double)fy; a.fz += (double)fz;
-    if (MODE == MODE_ENERGY) {
-        a.e_dih += (double)(K * ((R)1 - (cphi * c0 + sphi * s0))) / 4.0;
-        // virial about bead b: (x_a - x_b).F_a + (x_c - x_b).F_c + (x_d - x_b).F_d
-        R fa_x = -dU * gax, fa_y = -dU * gay, fa_z = -dU * gaz;
-        R fd_x = -dU * gdx, fd_y = -dU * gdy, fd_z = -dU * gdz;
-        R fc_x = -dU * (pp * gax - (qq + (R)1) * gdx), fc_y = -dU * (pp * gay - (qq + (R)1) * gdy),
-          fc_z = -dU * (pp * gaz - (qq + (R)1) * gdz);
-        R w = -(b1x * fa_x + b1y * fa_y + b1z * fa_z) + (b2x * fc_x + b2y * fc_y + b2z * fc_z) +
-              ((b2x + b3x) * fd_x + (b2y + b3y) * fd_y + (b2z + b3z) * fd_z);
-        a.vir += (double)w / 4.0;
-    }
+    const R im = r_rsqrt<R>(m2), in = r_rsqrt<R>(n2), ib = r_rsqrt<R>(b22);
+    const R nb2 = b22 * ib, inv = sg * (im * in);
+    const R cphi = dot(m, n) * inv;
+    const R sphi = nb2 * dot(s1, n) * inv;
+    const R K = C.dK[t], c0 = C.dC0[t], s0 = C.dS0[t];
+    const R dU = K * mad(sphi, c0, -(cphi * s0));   // dU/dphi
+    const R ga = dU * nb2 * (im * im) * sg;         // -dU g_a = ga m
+    const R ib2 = ib * ib;
+    const R pp = sg * dot(s1, b2) * ib2, qq = dot(b3, b2) * ib2;
+    const R al = end ? ga : -ga * (pp + (R)1);
+    const R be = end ? (R)0 : -dU * qq * nb2 * (in * in);
+    a.fx += (double)mad(al, m.x, be * n.x);
+    a.fy += (double)mad(al, m.y, be * n.y);
+    a.fz += (double)mad(al, m.z, be * n.z);
+    // the potential does not change under scaling: no virial
+    if (MODE == MODE_ENERGY) a.e_dih += (double)(K * ((R)1 - (cphi * c0 + sphi * s0))) / 4.0;
 }
 
 // The forces on all three members of an angle (a, b, c), u = x_a - x_b, w = x_c - x_b:
-// the arithmetic of angle_core, every role at once (f[role][component])
+// angle_share's terms up to rounding, every role at once (f[role][component])
 template <typename R>
 __device__ __forceinline__ void angle_all(const Coef<R>& C, int t, R ux, R uy, R uz, R wx, R wy, R wz,
                                           R (&f)[3][3]) {
@@ -735,7 +776,7 @@ __device__ __forceinline__ void angle_all(const Coef<R>& C, int t, R ux, R uy, R
 // The forces on the end members (a, d) of a dihedral (a, b, c, d) from its bond
 // vectors, and the projections pp = b1.b2 / |b2|^2, qq = b3.b2 / |b2|^2 that give
 // those on the inner ones: f_b = qq f_d - (pp + 1) f_a, f_c = pp f_a - (qq + 1) f_d.
-// The arithmetic of dihedral_core.
+// dihedral_share's terms up to rounding.
 template <typename R>
 __device__ __forceinline__ void dihedral_ends(const Coef<R>& C, int t, R b1x, R b1y, R b1z, R b2x, R b2y, R b2z,
                                               R b3x, R b3y, R b3z, R (&fa)[3], R (&fd)[3], R& pp, R& qq) {
@@ -765,25 +806,201 @@ __device__ __forceinline__ void dihedral_ends(const Coef<R>& C, int t, R b1x, R 
     fd[2] = -dU * (sd * nz);
 }
 
-template <typename R, int MODE>
+// ---- unfused float forms -------------------------------------------------------
+// The FP32 kernel with DPD pairs keeps these: at the paper's friction a DPD step
+// multiplies small velocity differences, so that another rounding of the forces
+// shows in every velocity after some twenty steps, and mixed runs with DPD keep the
+// rounding, and with it the trajectories, that they have always had.  (There the
+// bonded terms of the few chain beads are a small part of the step.)
+template <typename R, int PAIR>
+constexpr bool unfused() { return sizeof(R) == 4 && PAIR == PAIR_DPD; }
+
+__device__ __forceinline__ void bond_unfused(const Coef<float>& C, int t, double dx, double dy, double dz,
+                                             Acc<float>& a) {
+    const double rd2 = (dx * dx + dy * dy) + dz * dz;
+    if (!(rd2 > 0.0) || !(rd2 < C.bRc2[t])) return;
+    const float rx = (float)dx, ry = (float)dy, rz = (float)dz;
+    const float rr2 = (rx * rx + ry * ry) + rz * rz;
+    const float ir = r_rsqrt<float>(rr2);
+    const float r = rr2 * ir;
+    const float g = 2.0f * C.bK[t] * (r - C.bR0[t]) * ir;
+    a.fx += (double)(g * rx);
+    a.fy += (double)(g * ry);
+    a.fz += (double)(g * rz);
+}
+
+// u, w: the separations of the ends from the centre, the bead's own end first
+__device__ __forceinline__ void angle_unfused(const Coef<float>& C, bool centre, int t, const V3<float>& u,
+                                              const V3<float>& w, Acc<float>& a) {
+    const float ux = u.x, uy = u.y, uz = u.z, wx = w.x, wy = w.y, wz = w.z;
+    const float ru2 = (ux * ux + uy * uy) + uz * uz;
+    const float rw2 = (wx * wx + wy * wy) + wz * wz;
+    if (!(ru2 > 0.0f) || !(rw2 > 0.0f)) return;
+    const float iru = r_rsqrt<float>(ru2), irw = r_rsqrt<float>(rw2);
+    const float cux = ux * iru, cuy = uy * iru, cuz = uz * iru;
+    const float cwx = wx * irw, cwy = wy * irw, cwz = wz * irw;
+    const float cs = (cux * cwx + cuy * cwy) + cuz * cwz;
+    const float crx = cuy * cwz - cuz * cwy, cry = cuz * cwx - cux * cwz, crz = cux * cwy - cuy * cwx;
+    const float sn = sqrtf((crx * crx + cry * cry) + crz * crz);
+    const float del = r_atan2<float>(sn, -cs);   // pi - theta
+    const float isn = r_rcp<float>(sn > 1e-8f ? sn : 1e-8f);
+    const float ratio = del < 1e-6f ? 1.0f + del * del * (float)(1.0 / 6.0) : del * isn;
+    const float pth = C.aPm[t];
+    const float A = 2.0f * C.aK[t] * (-ratio + (pth != 0.0f ? pth * isn : 0.0f));
+    const float Au = -A * iru, Aw = -A * irw;
+    const float fax = Au * (cs * cux - cwx), fay = Au * (cs * cuy - cwy), faz = Au * (cs * cuz - cwz);
+    if (!centre) {
+        a.fx += (double)fax; a.fy += (double)fay; a.fz += (double)faz;
+    } else {
+        const float fcx = Aw * (cs * cwx - cux), fcy = Aw * (cs * cwy - cuy), fcz = Aw * (cs * cwz - cuz);
+        a.fx -= (double)(fax + fcx); a.fy -= (double)(fay + fcy); a.fz -= (double)(faz + fcz);
+    }
+}
+
+// b1 = x_b - x_a, b2 = x_c - x_b, b3 = x_d - x_c; rev: the bead is c or d
+__device__ __forceinline__ void dihedral_unfused(const Coef<float>& C, bool end, bool rev, int t, const V3<float>& b1,
+                                                 const V3<float>& b2, const V3<float>& b3, Acc<float>& a) {
+    const float b1x = b1.x, b1y = b1.y, b1z = b1.z, b2x = b2.x, b2y = b2.y, b2z = b2.z, b3x = b3.x, b3y = b3.y, b3z = b3.z;
+    const float mx = b1y * b2z - b1z * b2y, my = b1z * b2x - b1x * b2z, mz = b1x * b2y - b1y * b2x;
+    const float nx = b2y * b3z - b2z * b3y, ny = b2z * b3x - b2x * b3z, nz = b2x * b3y - b2y * b3x;
+    const float m2 = (mx * mx + my * my) + mz * mz;
+    const float n2 = (nx * nx + ny * ny) + nz * nz;
+    const float b22 = (b2x * b2x + b2y * b2y) + b2z * b2z;
+    if (m2 < 1e-24f || n2 < 1e-24f || b22 < 1e-24f) return;   // collinear: no defined plane
+    const float nb2 = sqrtf(b22);
+    const float inv = r_rsqrt<float>(m2 * n2);
+    const float cphi = ((mx * nx + my * ny) + mz * nz) * inv;
+    const float sphi = nb2 * ((b1x * nx + b1y * ny) + b1z * nz) * inv;
+    const float dU = C.dK[t] * (sphi * C.dC0[t] - cphi * C.dS0[t]);   // dU/dphi
+    const float sa = -nb2 * r_rcp<float>(m2), sd = nb2 * r_rcp<float>(n2), ib22 = r_rcp<float>(b22);
+    const float gax = sa * mx, gay = sa * my, gaz = sa * mz;
+    const float gdx = sd * nx, gdy = sd * ny, gdz = sd * nz;
+    const float pp = ((b1x * b2x + b1y * b2y) + b1z * b2z) * ib22;
+    const float qq = ((b3x * b2x + b3y * b2y) + b3z * b2z) * ib22;
+    float fx, fy, fz;
+    if (end) {
+        fx = -dU * (rev ? gdx : gax); fy = -dU * (rev ? gdy : gay); fz = -dU * (rev ? gdz : gaz);
+    } else if (!rev) {
+        fx = -dU * (qq * gdx - (pp + 1.0f) * gax);
+        fy = -dU * (qq * gdy - (pp + 1.0f) * gay);
+        fz = -dU * (qq * gdz - (pp + 1.0f) * gaz);
+    } else {
+        fx = -dU * (pp * gax - (qq + 1.0f) * gdx);
+        fy = -dU * (pp * gay - (qq + 1.0f) * gdy);
+        fz = -dU * (pp * gaz - (qq + 1.0f) * gdz);
+    }
+    a.fx += (double)fx; a.fy += (double)fy; a.fz += (double)fz;
+}
+
+// one term of the step's force in the form the kernel's type and pair style take
+template <typename R, int PAIR>
+__device__ __forceinline__ void bond_step(const Params& P, const Coef<R>& C, int t, double dx, double dy, double dz,
+                                          Acc<R>& a) {
+    if constexpr (unfused<R, PAIR>()) bond_unfused(C, t, dx, dy, dz, a);
+    else bond_force<R, MODE_STEP>(P, C, t, dx, dy, dz, a);
+}
+// (s1, s2 and s1, s2, s3: the other members' separations from the bead, in the order
+// of the halo's entry codes)
+template <typename R, int PAIR>
+__device__ __forceinline__ void angle_step(const Coef<R>& C, uint32_t code, const V3<R>& s1, const V3<R>& s2,
+                                           Acc<R>& a) {
+    const bool centre = (code & 1u) != 0;
+    const int t = (int)(code >> 8) & (DB_MAXT - 1);
+    if constexpr (unfused<R, PAIR>()) {
+        const V3<R> z{(R)0, (R)0, (R)0};
+        angle_unfused(C, centre, t, centre ? s1 : sub(z, s1), centre ? s2 : sub(s2, s1), a);
+    } else {
+        angle_share<R, MODE_STEP>(C, centre, t, s1, sub_scaled(s2, centre ? (R)0 : (R)1, s1), a);
+    }
+}
+template <typename R, int PAIR>
+__device__ __forceinline__ void dihedral_step(const Coef<R>& C, uint32_t code, const V3<R>& s1, const V3<R>& s2,
+                                              const V3<R>& s3, Acc<R>& a) {
+    const bool end = (code & 1u) != 0;
+    const int t = (int)(code >> 11) & (DB_MAXT - 1);
+    if constexpr (unfused<R, PAIR>()) {
+        const bool rev = (code & 2u) != 0;
+        const V3<R> z{(R)0, (R)0, (R)0}, q0 = end ? z : s1, q1 = end ? s1 : z;
+        const V3<R> pa = rev ? s3 : q0, pb = rev ? s2 : q1, pc = rev ? q1 : s2, pd = rev ? q0 : s3;
+        dihedral_unfused(C, end, rev, t, sub(pb, pa), sub(pc, pb), sub(pd, pc), a);
+    } else {
+        dihedral_share<R, MODE_STEP>(C, end, t, s1, sub_scaled(s2, end ? (R)1 : (R)0, s1), sub(s3, s2), a);
+    }
+}
+
+// the bonds of bead i with the types it stores (all partners requested at once)
+template <typename R, int MODE, int PAIR>
+__device__ __forceinline__ void bond_terms(const Params& P, const Box& X, const Coef<R>& C, const Bank& B, int i, const double4& xi, int nb,
+                                           Acc<R>& a) {
+    const int n = P.n;
+    int jj[DB_MAXB], tt[DB_MAXB];
+#pragma unroll
+    for (int k = 0; k < DB_MAXB; ++k) {
+        jj[k] = k < nb ? B.bp[k * n + i] : i;
+        tt[k] = k < nb ? (int)B.bt[k * n + i] & (DB_MAXT - 1) : 0;
+    }
+    double4 xs[DB_MAXB];
+#pragma unroll
+    for (int k = 0; k < DB_MAXB; ++k) xs[k] = B.x[jj[k]];
+#pragma unroll
+    for (int k = 0; k < DB_MAXB; ++k) {
+        if (k >= nb) continue;
+        const double4& xj = xs[k];
+        const double dx = near_image(xj.x - xi.x, X), dy = near_image(xj.y - xi.y, X), dz = near_image(xj.z - xi.z, X);
+        if constexpr (MODE == MODE_ENERGY) bond_force<R, MODE>(P, C, tt[k], dx, dy, dz, a);
+        else bond_step<R, PAIR>(P, C, tt[k], dx, dy, dz, a);
+    }
+}
+
+// angle and dihedral entries of bead i from the members' positions; separations
+// between other members are formed from their positions, not through the bead
+template <typename R, int MODE, int PAIR>
+__device__ __forceinline__ void angle_one(const Params& P, const Box& X, const Coef<R>& C, int i, const int4& e,
+                                          const double4& xa, const double4& xb, const double4& xc, Acc<R>& a) {
+    const int t = e.w & (DB_MAXT - 1);
+    const bool centre = e.x != i && e.z != i;
+    const double4 &x1 = e.z == i ? xc : xa, &x2 = e.z == i ? xa : xc;   // the bead's own end first
+    if constexpr (MODE == MODE_ENERGY || !unfused<R, PAIR>())
+        angle_share<R, MODE>(C, centre, t, centre ? sep_of<R>(X, x1, xb) : sep_of<R>(X, xb, x1), sep_of<R>(X, x2, xb),
+                             a);
+    else
+        angle_unfused(C, centre, t, sep_of<R>(X, x1, xb), sep_of<R>(X, x2, xb), a);
+}
+
+template <typename R, int MODE, int PAIR>
 __device__ __forceinline__ void dihedral_one(const Params& P, const Box& X, const Coef<R>& C, int i, const int4& e, int t,
                                              const double4& xa, const double4& xb, const double4& xc,
                                              const double4& xd, Acc<R>& a) {
-    R b1x = (R)near_image(xb.x - xa.x, X), b1y = (R)near_image(xb.y - xa.y, X), b1z = (R)near_image(xb.z - xa.z, X);
-    R b2x = (R)near_image(xc.x - xb.x, X), b2y = (R)near_image(xc.y - xb.y, X), b2z = (R)near_image(xc.z - xb.z, X);
-    R b3x = (R)near_image(xd.x - xc.x, X), b3y = (R)near_image(xd.y - xc.y, X), b3z = (R)near_image(xd.z - xc.z, X);
-    const int role = e.x == i ? 0 : (e.w == i ? 3 : (e.y == i ? 1 : 2));
-    dihedral_core<R, MODE>(C, role, t, b1x, b1y, b1z, b2x, b2y, b2z, b3x, b3y, b3z, a);
+    // the path from the bead's own half: a b c d, or d c b a
+    const bool rev = e.w == i || (e.x != i && e.y != i);
+    const bool end = e.x == i || e.w == i;
+    if constexpr (MODE == MODE_ENERGY || !unfused<R, PAIR>()) {
+        const double4 &pa = rev ? xd : xa, &pb = rev ? xc : xb, &pc = rev ? xb : xc, &pd = rev ? xa : xd;
+        dihedral_share<R, MODE>(C, end, t, end ? sep_of<R>(X, pb, pa) : sep_of<R>(X, pa, pb), sep_of<R>(X, pc, pb),
+                                sep_of<R>(X, pd, pc), a);
+    } else {
+        dihedral_unfused(C, end, rev, t, sep_of<R>(X, xb, xa), sep_of<R>(X, xc, xb), sep_of<R>(X, xd, xc), a);
+    }
 }
 
-template <typename R, int MODE>
+template <typename R, int MODE, int PAIR>
+__device__ __forceinline__ void angle_terms(const Params& P, const Box& X, const Coef<R>& C, const Bank& B, int i, int na,
+                                            Acc<R>& a) {
+    const int n = P.n;
+    for (int k = 0; k < na; ++k) {
+        int4 e = B.ang[k * n + i];
+        angle_one<R, MODE, PAIR>(P, X, C, i, e, B.x[e.x], B.x[e.y], B.x[e.z], a);
+    }
+}
+
+template <typename R, int MODE, int PAIR>
 __device__ __forceinline__ void dihedral_terms(const Params& P, const Box& X, const Coef<R>& C, const Bank& B, int i, int nd,
                                                Acc<R>& a) {
     const int n = P.n;
     for (int k = 0; k < nd; ++k) {
         int4 e = B.dih[k * n + i];
         int t = B.dt[k * n + i] & (DB_MAXT - 1);
-        dihedral_one<R, MODE>(P, X, C, i, e, t, B.x[e.x], B.x[e.y], B.x[e.z], B.x[e.w], a);
+        dihedral_one<R, MODE, PAIR>(P, X, C, i, e, t, B.x[e.x], B.x[e.y], B.x[e.z], B.x[e.w], a);
     }
 }
 
@@ -794,8 +1011,11 @@ __device__ __forceinline__ void dihedral_terms(const Params& P, const Box& X, co
 // dihedral entry as the bead's role plus halo indices of the other members.
 // The step kernel then reads each of those positions once, as a separation from
 // bead i, instead of once per entry that names it.
-//   acode: role (2 bits) | other member 1 << 2 | other member 2 << 5 | type << 8
-//   dcode: role (2 bits) | others 1..3 << 2, 5, 8 (3 bits each) | type << 11
+//   acode: centre | s1 << 2 | s2 << 5 | type << 8, with s1, s2 the other members
+//          (centre: a, c; an end: the centre, the far end)
+//   dcode: end | rev << 1 | s1 << 2 | s2 << 5 | s3 << 8 (3 bits each) | type << 11, with
+//          s1, s2, s3 the other members along the path from the bead's own half
+//          (a b c d, or with rev d c b a)
 // only == nullptr: every bead; else only the beads flagged there (those whose own
 // tables the last sweep changed: a bead's halo depends on its own tables alone)
 __global__ __launch_bounds__(DB_BLOCK) void k_halo(const Params* __restrict__ Pp, Bank B, Halo H,
@@ -838,12 +1058,10 @@ __global__ __launch_bounds__(DB_BLOCK) void k_halo(const Params* __restrict__ Pp
         for (int q = 0; q < 4; ++q) {
             if (k0 + q >= na) continue;
             const int4 e = e4[q];
-            const int role = e.x == i ? 0 : (e.z == i ? 2 : 1);
-            const int m1 = role == 0 ? e.y : e.x;
-            const int m2 = role == 2 ? e.y : e.z;
-            const int c1 = code_of(m1);
-            const int c2 = code_of(m2);
-            H.acode[(k0 + q) * n + i] = (uint32_t)(role | c1 << 2 | c2 << 5 | (e.w & (DB_MAXT - 1)) << 8);
+            const bool centre = e.x != i && e.z != i;
+            const int c1 = code_of(centre ? e.x : e.y);
+            const int c2 = code_of(e.z == i ? e.x : e.z);
+            H.acode[(k0 + q) * n + i] = (uint32_t)(centre ? 1 : 0) | (uint32_t)(c1 << 2 | c2 << 5 | (e.w & (DB_MAXT - 1)) << 8);
         }
     }
     const int nd = B.nd[i];
@@ -861,14 +1079,13 @@ __global__ __launch_bounds__(DB_BLOCK) void k_halo(const Params* __restrict__ Pp
             if (k0 + q >= nd) continue;
             const int4 e = e4[q];
             const int t = t4[q];
-            const int role = e.x == i ? 0 : (e.w == i ? 3 : (e.y == i ? 1 : 2));
-            const int o1 = role == 0 ? e.y : e.x;
-            const int o2 = role <= 1 ? e.z : e.y;
-            const int o3 = role <= 2 ? e.w : e.z;
-            const int c1 = code_of(o1);
-            const int c2 = code_of(o2);
-            const int c3 = code_of(o3);
-            H.dcode[(k0 + q) * n + i] = (uint32_t)(role | c1 << 2 | c2 << 5 | c3 << 8 | t << 11);
+            // the path from the bead's own half: a b c d, or d c b a
+            const bool rev = e.w == i || (e.x != i && e.y != i);
+            const bool end = e.x == i || e.w == i;
+            const int c1 = code_of(end ? (rev ? e.z : e.y) : (rev ? e.w : e.x));
+            const int c2 = code_of(rev ? e.y : e.z);
+            const int c3 = code_of(rev ? e.x : e.w);
+            H.dcode[(k0 + q) * n + i] = (uint32_t)((end ? 1 : 0) | (rev ? 2 : 0)) | (uint32_t)(c1 << 2 | c2 << 5 | c3 << 8 | t << 11);
         }
     }
 #pragma unroll
@@ -880,7 +1097,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_halo(const Params* __restrict__ Pp
 // all bonded forces on bead i from its halo (nu <= DB_MAXU entries).  The
 // separations are parked in LDS, one column per thread, so that angle and
 // dihedral entries can index them at run time without holding 24 registers.
-template <typename R>
+template <typename R, int PAIR>
 __device__ __forceinline__ void halo_bonded(const Params& P, const Box& X, const Coef<R>& C, const Bank& B, const Halo& H, int i,
                                             const double4& xi, int nu, Acc<R>& a) {
     const int n = P.n;
@@ -894,6 +1111,7 @@ __device__ __forceinline__ void halo_bonded(const Params& P, const Box& X, const
     // positions at once; the FP32 kernel takes them four at a time.
     constexpr bool wide = sizeof(R) == 8;
     constexpr int G = wide ? DB_MAXU : 4;
+    const int i0 = __builtin_amdgcn_readfirstlane(i);   // read for unused entries: one line for the wave
     int su[DB_MAXU];
 #pragma unroll
     for (int q = 0; q < DB_MAXU; ++q) su[q] = H.u[q * n + i];
@@ -903,16 +1121,15 @@ __device__ __forceinline__ void halo_bonded(const Params& P, const Box& X, const
     const int nb = B.nb[i];
     const int na = B.na[i];
     const int nd = B.nd[i];
-    const uint32_t acode0 = H.acode[i];
-    const uint32_t dcode0 = H.dcode[i];
-    // separations x_k - x_i, G at a time; for the bond partners (the first nb
-    // entries) the cutoff decision is taken here, in double, whatever the force type
-    unsigned inb = 0;
+    uint32_t acode = H.acode[i];
+    uint32_t dcode = H.dcode[i];
+    // separations x_k - x_i, G at a time; the first nb entries are the bond
+    // partners in table order
 #pragma unroll
     for (int k0 = 0; k0 < DB_MAXU; k0 += G) {
         int s[G];
 #pragma unroll
-        for (int q = 0; q < G; ++q) s[q] = k0 + q < nu ? su[k0 + q] : i;
+        for (int q = 0; q < G; ++q) s[q] = k0 + q < nu ? su[k0 + q] : i0;
         double4 xk[G];
 #pragma unroll
         for (int q = 0; q < G; ++q) xk[q] = B.x[s[q]];
@@ -921,62 +1138,24 @@ __device__ __forceinline__ void halo_bonded(const Params& P, const Box& X, const
             const double dx = near_image(xk[q].x - xi.x, X);
             const double dy = near_image(xk[q].y - xi.y, X);
             const double dz = near_image(xk[q].z - xi.z, X);
-            if (k0 + q < DB_MAXB) {
-                const double rd2 = (dx * dx + dy * dy) + dz * dz;
-                const int t = btk[k0 + q] & (DB_MAXT - 1);
-                inb |= (k0 + q < nb && rd2 > 0.0 && rd2 < C.bRc2[t]) ? 1u << (k0 + q) : 0u;
-            }
-            hx[k0 + q] = (R)dx;
-            hy[k0 + q] = (R)dy;
-            hz[k0 + q] = (R)dz;
-            hs[0][k0 + q][tid] = hx[k0 + q];
-            hs[1][k0 + q][tid] = hy[k0 + q];
-            hs[2][k0 + q][tid] = hz[k0 + q];
+            if (k0 + q < DB_MAXB && k0 + q < nb)
+                bond_step<R, PAIR>(P, C, btk[k0 + q] & (DB_MAXT - 1), dx, dy, dz, a);
+            hs[0][k0 + q][tid] = (R)dx;
+            hs[1][k0 + q][tid] = (R)dy;
+            hs[2][k0 + q][tid] = (R)dz;
         }
     }
-    // bonds: the first nb halo entries are the partners in table order
-#pragma unroll
-    for (int k = 0; k < DB_MAXB; ++k) {
-        if (!((inb >> k) & 1u)) continue;
-        const int t = btk[k] & (DB_MAXT - 1);
-        const R rx = hx[k], ry = hy[k], rz = hz[k];
-        R rr2 = (rx * rx + ry * ry) + rz * rz;
-        R ir = r_rsqrt<R>(rr2);
-        R r = rr2 * ir;
-        R g = (R)2.0 * C.bK[t] * (r - C.bR0[t]) * ir;   // F_i = g * (x_j - x_i)
-        a.fx += (double)(g * rx);
-        a.fy += (double)(g * ry);
-        a.fz += (double)(g * rz);
-    }
+    auto at = [&](uint32_t k) { return V3<R>{hs[0][k & 7][tid], hs[1][k & 7][tid], hs[2][k & 7][tid]}; };
+    // each entry's code is requested before the entry ahead of it is evaluated
     for (int k = 0; k < na; ++k) {
-        const uint32_t code = k == 0 ? acode0 : H.acode[k * n + i];
-        const int role = code & 3, k1 = (code >> 2) & 7, k2 = (code >> 5) & 7, t = (code >> 8) & (DB_MAXT - 1);
-        const R s1x = hs[0][k1][tid], s1y = hs[1][k1][tid], s1z = hs[2][k1][tid];
-        const R s2x = hs[0][k2][tid], s2y = hs[1][k2][tid], s2z = hs[2][k2][tid];
-        // member positions relative to bead i (which sits at the origin)
-        const R z = (R)0;
-        const R pax = role == 0 ? z : s1x, pay = role == 0 ? z : s1y, paz = role == 0 ? z : s1z;
-        const R pbx = role == 0 ? s1x : (role == 1 ? z : s2x), pby = role == 0 ? s1y : (role == 1 ? z : s2y),
-                pbz = role == 0 ? s1z : (role == 1 ? z : s2z);
-        const R pcx = role == 2 ? z : s2x, pcy = role == 2 ? z : s2y, pcz = role == 2 ? z : s2z;
-        angle_core<R, MODE_STEP>(C, role, t, pax - pbx, pay - pby, paz - pbz, pcx - pbx, pcy - pby, pcz - pbz, a);
+        const uint32_t code = acode;
+        if (k + 1 < na) acode = H.acode[(k + 1) * n + i];
+        angle_step<R, PAIR>(C, code, at(code >> 2), at(code >> 5), a);
     }
     for (int k = 0; k < nd; ++k) {
-        const uint32_t code = k == 0 ? dcode0 : H.dcode[k * n + i];
-        const int role = code & 3, k1 = (code >> 2) & 7, k2 = (code >> 5) & 7, k3 = (code >> 8) & 7;
-        const int t = (code >> 11) & (DB_MAXT - 1);
-        const R s1x = hs[0][k1][tid], s1y = hs[1][k1][tid], s1z = hs[2][k1][tid];
-        const R s2x = hs[0][k2][tid], s2y = hs[1][k2][tid], s2z = hs[2][k2][tid];
-        const R s3x = hs[0][k3][tid], s3y = hs[1][k3][tid], s3z = hs[2][k3][tid];
-        const R z = (R)0;
-        const R pax = role == 0 ? z : s1x, pay = role == 0 ? z : s1y, paz = role == 0 ? z : s1z;
-        const R pbx = role == 0 ? s1x : (role == 1 ? z : s2x), pby = role == 0 ? s1y : (role == 1 ? z : s2y),
-                pbz = role == 0 ? s1z : (role == 1 ? z : s2z);
-        const R pcx = role <= 1 ? s2x : (role == 2 ? z : s3x), pcy = role <= 1 ? s2y : (role == 2 ? z : s3y),
-                pcz = role <= 1 ? s2z : (role == 2 ? z : s3z);
-        const R pdx = role == 3 ? z : s3x, pdy = role == 3 ? z : s3y, pdz = role == 3 ? z : s3z;
-        dihedral_core<R, MODE_STEP>(C, role, t, pbx - pax, pby - pay, pbz - paz, pcx - pbx, pcy - pby, pcz - pbz,
-                                    pdx - pcx, pdy - pcy, pdz - pcz, a);
+        const uint32_t code = dcode;
+        if (k + 1 < nd) dcode = H.dcode[(k + 1) * n + i];
+        dihedral_step<R, PAIR>(C, code, at(code >> 2), at(code >> 5), at(code >> 8), a);
     }
 }
 
@@ -1005,11 +1184,11 @@ __device__ __forceinline__ void step_amplitudes(const Params& P, const int64_t* 
 // reads the neighbours' input velocities.  Each step reports the workgroup maxima
 // of |v|^2 (WCA) or, with DPD, of the squared displacement of the new position
 // from xref, the position at the last full Verlet-list build.
-// The FP32 WCA step is held to the registers of six waves per SIMD (its LDS
-// allows six), which the compiler otherwise gives up for a few registers (the
-// batched form took 94 and ran at five).
+// The step kernels are held to the registers of six (FP32 WCA), five (FP32 DPD)
+// and three (FP64) waves per SIMD, what their LDS allows or just below, which the
+// compiler otherwise gives up for a few registers.
 template <typename R, int MODE, bool BATCH, int PAIR>
-__global__ __launch_bounds__(DB_BLOCK, (sizeof(R) == 4 && PAIR == PAIR_WCA && MODE == MODE_STEP) ? 6 : 1)
+__global__ __launch_bounds__(DB_BLOCK, MODE != MODE_STEP ? 1 : (sizeof(R) == 8 ? 3 : (PAIR == PAIR_WCA ? 6 : 5)))
 void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __restrict__ xout, double* vout,
             int64_t step, double pref, double dsig, unsigned int* __restrict__ vmax2_slot, double* __restrict__ fout,
             int* __restrict__ err, double4* __restrict__ xsave, double* __restrict__ vsave,
@@ -1044,12 +1223,12 @@ void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __
                 for (int q = 0; q < PQ; ++q) jpre[q] = NL.nl[q * n + i];
             }
             if (nu <= DB_MAXU) {
-                halo_bonded<R>(P, X, C, B, H, i, xi, nu, a);
+                halo_bonded<R, PAIR>(P, X, C, B, H, i, xi, nu, a);
             } else {
                 // more distinct bonded partners than the halo holds: read them per entry
-                bond_terms<R, MODE_STEP>(P, X, C, B, i, xi, B.nb[i], a);
-                angle_terms<R, MODE_STEP>(P, X, C, B, i, B.na[i], a);
-                dihedral_terms<R, MODE_STEP>(P, X, C, B, i, B.nd[i], a);
+                bond_terms<R, MODE_STEP, PAIR>(P, X, C, B, i, xi, B.nb[i], a);
+                angle_terms<R, MODE_STEP, PAIR>(P, X, C, B, i, B.na[i], a);
+                dihedral_terms<R, MODE_STEP, PAIR>(P, X, C, B, i, B.nd[i], a);
             }
             if constexpr (PAIR == PAIR_DPD) {
                 if (MODE == MODE_STEP && P.dpd_gamma != 0.0) {
@@ -1539,17 +1718,7 @@ __device__ __forceinline__ void tile_bonds(const Params& P, const Box& X, const 
         if (k >= tb.nb) continue;
         double dx, dy, dz;
         tp.sep(half16(tb.hu, k), xi, X, dx, dy, dz);
-        const int t = tb.btk[k] & (DB_MAXT - 1);
-        const double rd2 = (dx * dx + dy * dy) + dz * dz;
-        if (!(rd2 > 0.0) || !(rd2 < C.bRc2[t])) continue;
-        const R ex = (R)dx, ey = (R)dy, ez = (R)dz;
-        R rr2 = (ex * ex + ey * ey) + ez * ez;
-        R ir = r_rsqrt<R>(rr2);
-        R r = rr2 * ir;
-        R g = (R)2.0 * C.bK[t] * (r - C.bR0[t]) * ir;
-        a.fx += (double)(g * ex);
-        a.fy += (double)(g * ey);
-        a.fz += (double)(g * ez);
+        bond_force<R, MODE_STEP>(P, C, tb.btk[k] & (DB_MAXT - 1), dx, dy, dz, a);
     }
 }
 
@@ -1575,57 +1744,26 @@ __device__ __forceinline__ void tile_bonded(const Params& P, const Box& X, const
         if (k >= tb.nb) continue;
         double dx, dy, dz;
         tp.sep(STAGED ? half16(tb.hu, k) : member(k), xi, X, dx, dy, dz);
-        const int t = tb.btk[k] & (DB_MAXT - 1);
-        const double rd2 = (dx * dx + dy * dy) + dz * dz;
-        if (!(rd2 > 0.0) || !(rd2 < C.bRc2[t])) continue;
-        const R ex = (R)dx, ey = (R)dy, ez = (R)dz;
-        R rr2 = (ex * ex + ey * ey) + ez * ez;
-        R ir = r_rsqrt<R>(rr2);
-        R r = rr2 * ir;
-        R g = (R)2.0 * C.bK[t] * (r - C.bR0[t]) * ir;
-        a.fx += (double)(g * ex);
-        a.fy += (double)(g * ey);
-        a.fz += (double)(g * ez);
+        bond_force<R, MODE_STEP>(P, C, tb.btk[k] & (DB_MAXT - 1), dx, dy, dz, a);
     }
+    auto at = [&](uint32_t q) {
+        double dx, dy, dz;
+        tp.sep(member((int)(q & 7u)), xi, X, dx, dy, dz);
+        return V3<R>{(R)dx, (R)dy, (R)dz};
+    };
     // the first four entries unrolled (codes in registers, so every member's loads
     // can be issued together), then any further ones
 #pragma unroll
     for (int k = 0; k < DB_MAXA; ++k) {
         if (k >= tb.na) continue;
         const uint32_t code = k < 4 ? tb.ac[k < 4 ? k : 0] : H.acode[k * n + i];
-        const int role = code & 3, k1 = (code >> 2) & 7, k2 = (code >> 5) & 7, t = (code >> 8) & (DB_MAXT - 1);
-        double d1x, d1y, d1z, d2x, d2y, d2z;
-        tp.sep(member(k1), xi, X, d1x, d1y, d1z);
-        tp.sep(member(k2), xi, X, d2x, d2y, d2z);
-        const R s1x = (R)d1x, s1y = (R)d1y, s1z = (R)d1z, s2x = (R)d2x, s2y = (R)d2y, s2z = (R)d2z;
-        const R z = (R)0;
-        const R pax = role == 0 ? z : s1x, pay = role == 0 ? z : s1y, paz = role == 0 ? z : s1z;
-        const R pbx = role == 0 ? s1x : (role == 1 ? z : s2x), pby = role == 0 ? s1y : (role == 1 ? z : s2y),
-                pbz = role == 0 ? s1z : (role == 1 ? z : s2z);
-        const R pcx = role == 2 ? z : s2x, pcy = role == 2 ? z : s2y, pcz = role == 2 ? z : s2z;
-        angle_core<R, MODE_STEP>(C, role, t, pax - pbx, pay - pby, paz - pbz, pcx - pbx, pcy - pby, pcz - pbz, a);
+        angle_step<R, PAIR_WCA>(C, code, at(code >> 2), at(code >> 5), a);
     }
 #pragma unroll
     for (int k = 0; k < DB_MAXD; ++k) {
         if (k >= tb.nd) continue;
         const uint32_t code = k < 4 ? tb.dc[k < 4 ? k : 0] : H.dcode[k * n + i];
-        const int role = code & 3, k1 = (code >> 2) & 7, k2 = (code >> 5) & 7, k3 = (code >> 8) & 7;
-        const int t = (code >> 11) & (DB_MAXT - 1);
-        double d1x, d1y, d1z, d2x, d2y, d2z, d3x, d3y, d3z;
-        tp.sep(member(k1), xi, X, d1x, d1y, d1z);
-        tp.sep(member(k2), xi, X, d2x, d2y, d2z);
-        tp.sep(member(k3), xi, X, d3x, d3y, d3z);
-        const R s1x = (R)d1x, s1y = (R)d1y, s1z = (R)d1z, s2x = (R)d2x, s2y = (R)d2y, s2z = (R)d2z;
-        const R s3x = (R)d3x, s3y = (R)d3y, s3z = (R)d3z;
-        const R z = (R)0;
-        const R pax = role == 0 ? z : s1x, pay = role == 0 ? z : s1y, paz = role == 0 ? z : s1z;
-        const R pbx = role == 0 ? s1x : (role == 1 ? z : s2x), pby = role == 0 ? s1y : (role == 1 ? z : s2y),
-                pbz = role == 0 ? s1z : (role == 1 ? z : s2z);
-        const R pcx = role <= 1 ? s2x : (role == 2 ? z : s3x), pcy = role <= 1 ? s2y : (role == 2 ? z : s3y),
-                pcz = role <= 1 ? s2z : (role == 2 ? z : s3z);
-        const R pdx = role == 3 ? z : s3x, pdy = role == 3 ? z : s3y, pdz = role == 3 ? z : s3z;
-        dihedral_core<R, MODE_STEP>(C, role, t, pbx - pax, pby - pay, pbz - paz, pcx - pbx, pcy - pby, pcz - pbz,
-                                    pdx - pcx, pdy - pcy, pdz - pcz, a);
+        dihedral_step<R, PAIR_WCA>(C, code, at(code >> 2), at(code >> 5), at(code >> 8), a);
     }
 }
 
@@ -1635,17 +1773,7 @@ __device__ __forceinline__ void tile_pair(const Params& P, const Box& X, const T
                                           const double4& xi, R rc2, Acc<R>& a) {
     double dx, dy, dz;
     tp.sep(r, xi, X, dx, dy, dz);
-    const R ex = (R)dx, ey = (R)dy, ez = (R)dz;
-    const R r2 = (ex * ex + ey * ey) + ez * ez;
-    if (r2 < rc2) {
-        R ir2 = r_rcp<R>(r2);
-        R sr2 = (R)P.sig2 * ir2;
-        R sr6 = sr2 * sr2 * sr2;
-        R fr = (R)24.0 * (R)P.eps * ((R)2.0 * sr6 * sr6 - sr6) * ir2;
-        a.fx -= (double)(fr * ex);
-        a.fy -= (double)(fr * ey);
-        a.fz -= (double)(fr * ez);
-    }
+    pair_sep<R>(P, dx, dy, dz, rc2, a);
 }
 
 // Bonded forces of a bead with more distinct bonded partners than the halo holds:
@@ -1661,27 +1789,18 @@ __device__ __forceinline__ void wide_bonded(const Params& P, const Box& X, const
         const int t = (int)B.bt[k * n + i] & (DB_MAXT - 1);
         const double4 xj = B.x[j];
         const double dx = near_image(xj.x - xi.x, X), dy = near_image(xj.y - xi.y, X), dz = near_image(xj.z - xi.z, X);
-        const double rd2 = (dx * dx + dy * dy) + dz * dz;
-        if (!(rd2 > 0.0) || !(rd2 < C.bRc2[t])) continue;
-        R rx = (R)dx, ry = (R)dy, rz = (R)dz;
-        R rr2 = (rx * rx + ry * ry) + rz * rz;
-        R ir = r_rsqrt<R>(rr2);
-        R r = rr2 * ir;
-        R g = (R)2.0 * C.bK[t] * (r - C.bR0[t]) * ir;
-        a.fx += (double)(g * rx);
-        a.fy += (double)(g * ry);
-        a.fz += (double)(g * rz);
+        bond_force<R, MODE_STEP>(P, C, t, dx, dy, dz, a);
     }
     const int na = B.na[i];
     for (int k = 0; k < na; ++k) {
         const int4 e = B.ang[k * n + i];
-        angle_one<R, MODE_STEP>(P, X, C, i, e, B.x[e.x], B.x[e.y], B.x[e.z], a);
+        angle_one<R, MODE_STEP, PAIR_WCA>(P, X, C, i, e, B.x[e.x], B.x[e.y], B.x[e.z], a);
     }
     const int nd = B.nd[i];
     for (int k = 0; k < nd; ++k) {
         const int4 e = B.dih[k * n + i];
         const int t = B.dt[k * n + i] & (DB_MAXT - 1);
-        dihedral_one<R, MODE_STEP>(P, X, C, i, e, t, B.x[e.x], B.x[e.y], B.x[e.z], B.x[e.w], a);
+        dihedral_one<R, MODE_STEP, PAIR_WCA>(P, X, C, i, e, t, B.x[e.x], B.x[e.y], B.x[e.z], B.x[e.w], a);
     }
 }
 
@@ -2031,9 +2150,9 @@ __global__ __launch_bounds__(DB_BLOCK) void k_energy(const Params* __restrict__ 
         if (P.have_pair)
             pair_forces<R, MODE_ENERGY>(P, X, B, cstart, clist, i, xi, nb, p0, p1, p2, p3, vx, vy, vz, step, dsig,
                                         a);
-        bond_terms<R, MODE_ENERGY>(P, X, C, B, i, xi, nb, a);
-        angle_terms<R, MODE_ENERGY>(P, X, C, B, i, B.na[i], a);
-        dihedral_terms<R, MODE_ENERGY>(P, X, C, B, i, B.nd[i], a);
+        bond_terms<R, MODE_ENERGY, PAIR_WCA>(P, X, C, B, i, xi, nb, a);
+        angle_terms<R, MODE_ENERGY, PAIR_WCA>(P, X, C, B, i, B.na[i], a);
+        dihedral_terms<R, MODE_ENERGY, PAIR_WCA>(P, X, C, B, i, B.nd[i], a);
         if (P.has_ext) {
             const size_t g = (size_t)meta_gid(xi);
             a.fx += P.fext[3 * g];

@@ -1,0 +1,72 @@
+"""Angle and dihedral forces over the whole range of bends and torsions, GPU against the oracle.
+
+The step kernel takes (pi - theta) / sin(theta) from a polynomial up to 45 degrees from the straight angle and from
+an arctangent beyond, and reads a dihedral from either end: molecules of three and four beads sit on both sides of the
+switch, at the straight angle itself and at both resting angles a model uses."""
+import dataclasses
+import math
+
+import numpy as np
+import pytest
+
+import synth
+from gpu_common import both, forces_close
+
+pytestmark = pytest.mark.gpu
+
+BENDS = [0.0, 1e-9, 1e-6, 1e-3, 0.3, math.radians(44.9999), math.radians(45.0001), 1.2, 0.5 * math.pi, 2.2,
+         math.radians(170)]
+TORSIONS = [0.0, 1e-3, 0.7, -0.7, 0.5 * math.pi, -2.0, 3.0, math.pi]
+
+
+def _molecules(kind, seed):
+    rng = np.random.default_rng(seed)
+    xs, angles, dihedrals = [], [], []
+    pitch, per = 8.0, 8
+    cases = BENDS if kind == "angle" else TORSIONS
+    m = 0
+    for value in cases:
+        for rep in range(6):
+            if kind == "angle":
+                w = np.array([math.cos(value), math.sin(value), 0.0]) * (0.8 + 0.1 * rep)
+                p = np.array([[-1.0, 0.0, 0.0], [0.0, 0.0, 0.0], w])
+            else:
+                p = np.array([[0.3 + 0.1 * rep, 1.0, 0.0], [0.0, 0.0, 0.0], [0.0, 0.0, 1.1],
+                              [-0.2 + math.cos(value), math.sin(value), 1.3]])
+                p[0] = [math.cos(0.0), math.sin(0.0), 0.2 - 0.1 * rep]
+            centre = np.array([m % per, m // per % per, m // (per * per)]) * pitch + 4.0
+            base = 4 * m if kind == "dihedral" else 3 * m
+            xs.append(p @ synth._rotation(rng).T + centre)
+            # stored from either end
+            ids = list(range(base, base + len(p)))
+            ids = ids if rep % 2 == 0 else ids[::-1]
+            # a right-angle rest is singular at the straight angle: only for bends from 0.3
+            kind2 = rep % 2 if kind == "dihedral" or value >= 0.3 else 0
+            (angles if kind == "angle" else dihedrals).append((1 + kind2, *ids))
+            m += 1
+    x = np.concatenate(xs)
+    n, L = x.shape[0], per * pitch
+    return synth.System(L=L, x=synth.wrap(x, L), v=np.zeros((n, 3)), type=np.ones(n, dtype=np.int32),
+                        reactive=np.zeros(n, dtype=np.uint8), bonds=np.zeros((0, 4), dtype=np.int32),
+                        angles=np.array(angles, dtype=np.int32).reshape(-1, 4),
+                        dihedrals=np.array(dihedrals, dtype=np.int32).reshape(-1, 5))
+
+
+@pytest.mark.parametrize("kind", ["angle", "dihedral"])
+@pytest.mark.parametrize("pair", ["wca", "dpd"])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_bends_and_torsions_match_oracle(precision, pair, kind):
+    """Tolerances: a force is good to a unit roundoff (1.1e-16, 6e-8) times some twenty operations, over the sine of
+    the angle where the resting angle makes that count, least at 170 degrees of bend (1 / 0.17 = 6): 1.4e-14 and
+    7e-6, so 1e-12 (separations of a 64-edge box hold 1e-14) and 1e-5; energies likewise."""
+    s = _molecules(kind, 3)
+    ff = dataclasses.replace(synth.ForceField(eps=0.0, gamma=0.0), pair=pair, dpd_a=0.0, dpd_gamma=0.0, rc=1.0)
+    ff.angles = {1: (10.0, math.pi), 2: (3.0, 0.5 * math.pi)}
+    ff.dihedrals = {1: (5.0, 0.0), 2: (2.0, 1.1)}
+    g, o = both(s, ff, synth.RuleSet(every=0), precision=precision, generate=False)
+    tol = 1e-12 if precision == 0 else 1e-5
+    ok, msg = forces_close(g.forces(), o.forces(), tol)
+    assert ok, msg
+    eg, eo = g.energy(), o.energy()
+    for k in (3, 4):
+        assert abs(eg[k] - eo[k]) <= tol * max(1.0, abs(eo[k])), (k, eg[k], eo[k])
