@@ -1461,7 +1461,6 @@ int db_forces(db_ctx* c, double* f, int on_device) {
     int rc = ready(c);
     if (rc) return rc;
     rebuild(c, false);
-    launch_build_nlist(c);
     double* d = on_device ? f : (double*)gather_scratch(c, 24 * (size_t)c->n);
     launch_forces(c, d);
     if (!on_device && c->n) HIPCHK(c, hipMemcpyAsync(f, d, 24 * (size_t)c->n, hipMemcpyDeviceToHost, c->stream));
@@ -1476,9 +1475,7 @@ int db_energy(db_ctx* c, double out[6]) {
     int rc = ready(c);
     if (rc) return rc;
     rebuild(c, false);
-    double* d = (double*)gather_scratch(c, 64);
-    launch_energy(c, d);
-    HIPCHK(c, hipMemcpyAsync(ext(c).pin->energy, d, 48, hipMemcpyDeviceToHost, c->stream));
+    launch_energy(c, ext(c).pin_dev->energy);   // the sums go straight to the mapped host words
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipGetLastError());
     memcpy(out, ext(c).pin->energy, 48);
@@ -1499,10 +1496,8 @@ int db_energy_noalloc(db_ctx* c, double out[6]) {
                                   "run db_step, db_forces or db_energy once after the last change");
     double* part = (c->device >= 0 && c->device < kMaxDevices) ? noalloc_ptr[c->device] : nullptr;
     if (!part) return fail(c, DB_ESTATE, "no scratch address for device %d", c->device);
-    double* sums = part + 6 * (size_t)DB_NOALLOC_MAX_BLOCKS;
     rebuild(c, false);
-    launch_energy(c, sums, part);
-    HIPCHK(c, hipMemcpyAsync(X.pin->energy, sums, 48, hipMemcpyDeviceToHost, c->stream));
+    launch_energy(c, X.pin_dev->energy, part);
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipGetLastError());
     memcpy(out, X.pin->energy, 48);

@@ -15,7 +15,8 @@
 
 namespace db {
 
-enum { MODE_STEP = 0, MODE_FORCES = 1, MODE_ENERGY = 2 };
+// MODE_FORCE: the force on a bead alone; MODE_ENERGY: with its share of the energies
+enum { MODE_FORCE = 0, MODE_ENERGY = 1 };
 
 template <typename R>
 struct Acc {
@@ -175,39 +176,6 @@ __device__ __forceinline__ bool in_list4(int j, int nb, int p0, int p1, int p2, 
     return (nb > 0 && j == p0) || (nb > 1 && j == p1) || (nb > 2 && j == p2) || (nb > 3 && j == p3);
 }
 
-// j is one bond from any partner of i
-__device__ bool two_bonds_apart(const Bank& B, int n, int j, int nb, int p0, int p1, int p2, int p3) {
-    int ps[4] = {p0, p1, p2, p3};
-    for (int k = 0; k < nb; ++k) {
-        int q = ps[k];
-        int nq = B.nb[q];
-        for (int m = 0; m < nq; ++m)
-            if (B.bp[m * n + q] == j) return true;
-    }
-    return false;
-}
-
-template <typename R, int MODE>
-__device__ __forceinline__ void pair_term(const Params& P, const Box& X, const double4& xi, const double4& xj, Acc<R>& a) {
-    double dx, dy, dz;
-    dx = near_image(xj.x - xi.x, X);
-    dy = near_image(xj.y - xi.y, X);
-    dz = near_image(xj.z - xi.z, X);
-    R rx = (R)dx, ry = (R)dy, rz = (R)dz;
-    R r2 = (rx * rx + ry * ry) + rz * rz;
-    R ir2 = r_rcp<R>(r2);
-    R sr2 = (R)P.sig2 * ir2;
-    R sr6 = sr2 * sr2 * sr2;
-    R fr = (R)24.0 * (R)P.eps * ((R)2.0 * sr6 * sr6 - sr6) * ir2;   // -dU/dr / r
-    a.fx = fma(-(double)fr, dx, a.fx);
-    a.fy = fma(-(double)fr, dy, a.fy);
-    a.fz = fma(-(double)fr, dz, a.fz);
-    if (MODE == MODE_ENERGY) {
-        a.e_pair += 0.5 * (double)((R)4.0 * (R)P.eps * (sr6 * sr6 - sr6) + (R)P.eps);
-        a.vir += 0.5 * (double)(fr * r2);
-    }
-}
-
 // DPD pair (i, j) as seen by bead i (section 3).  With d = x_j - x_i (minimum
 // image), r = |d|, e = -d / r (from j to i) and w = 1 - r / rc, bead i receives
 // (F^C + F^D + F^R) e with F^C = a w, F^D = -gamma w^2 (e . v_ij) and
@@ -251,66 +219,6 @@ __device__ __forceinline__ void dpd_pair(const Params& P, const Box& X, const do
         a.fx = fma(-fi, dx, a.fx);
         a.fy = fma(-fi, dy, a.fy);
         a.fz = fma(-fi, dz, a.fz);
-    }
-}
-
-// pair forces over the 27 cells (energy evaluation); vi and dsig feed the DPD
-// thermostat terms when the DPD friction is not zero
-template <typename R, int MODE>
-__device__ void pair_forces(const Params& P, const Box& X, const Bank& B, const int* __restrict__ cstart,
-                            const int* __restrict__ clist, int i, const double4& xi, int nb, int p0, int p1, int p2,
-                            int p3, double vix, double viy, double viz, int64_t step, double dsig, Acc<R>& a) {
-    const int nc = X.nc;
-    int cx = cell_coord(xi.x, X.cell_scale, nc);
-    int cy = cell_coord(xi.y, X.cell_scale, nc);
-    int cz = cell_coord(xi.z, X.cell_scale, nc);
-    const R rc2 = (R)P.rc2;
-    const bool rowmerge = (X.noff == 3) && cx >= 1 && cx <= nc - 2;
-    cstart += X.cell_off;
-    for (int oz = 0; oz < X.noff; ++oz) {
-        int zz = wrap_cell(cz + box_off(X, oz), nc);
-        for (int oy = 0; oy < X.noff; ++oy) {
-            int yy = wrap_cell(cy + box_off(X, oy), nc);
-            int row = (zz * nc + yy) * nc;
-            // the three cells of one x-row are contiguous in the list unless the row wraps
-            int nseg = rowmerge ? 1 : X.noff;
-            for (int ox = 0; ox < nseg; ++ox) {
-                int s0, s1;
-                if (rowmerge) {
-                    s0 = cstart[row + cx - 1];
-                    s1 = cstart[row + cx + 2];
-                } else {
-                    int c = row + wrap_cell(cx + box_off(X, ox), nc);
-                    s0 = cstart[c];
-                    s1 = cstart[c + 1];
-                }
-                for (int p = s0; p < s1; ++p) {
-                    int j = clist[p];
-                    if (j == i) continue;
-                    double4 xj = B.x[j];
-                    double dx = near_image(xj.x - xi.x, X);
-                    double dy = near_image(xj.y - xi.y, X);
-                    double dz = near_image(xj.z - xi.z, X);
-                    R rx = (R)dx, ry = (R)dy, rz = (R)dz;
-                    R r2 = (rx * rx + ry * ry) + rz * rz;
-                    if (!(r2 < rc2)) continue;
-                    if (P.excl_depth >= 1 && in_list4(j, nb, p0, p1, p2, p3)) continue;
-                    if (P.excl_depth >= 2 && two_bonds_apart(B, P.n, j, nb, p0, p1, p2, p3)) continue;
-                    if (P.pair_style == PAIR_DPD) {
-                        const int n = P.n;
-                        if (P.dpd_gamma != 0.0)
-                            dpd_pair<R, true, MODE == MODE_ENERGY>(P, X, xi, xj, dx, dy, dz, r2, vix - B.v[j],
-                                                                   viy - B.v[n + j], viz - B.v[2 * n + j], step,
-                                                                   dsig, a);
-                        else
-                            dpd_pair<R, false, MODE == MODE_ENERGY>(P, X, xi, xj, dx, dy, dz, r2, 0, 0, 0, 0, 0,
-                                                                    a);
-                    } else {
-                        pair_term<R, MODE>(P, X, xi, xj, a);
-                    }
-                }
-            }
-        }
     }
 }
 
@@ -413,9 +321,10 @@ __global__ __launch_bounds__(DB_BLOCK) void k_build_nlist(const Params* __restri
     // than three cells per edge, is scanned with the test inside.
     int raw = 0;
     if (X.noff == 3) {
-        scan_cells_all(X, cstart, xs, i, xi, X.pf_list2, [&](int w, bool hit) {
+        const float cut2 = X.pf_list2;
+        scan_cells_all(X, cstart, xs, i, xi, [&](int w, float r2) {
             stage[min(raw, NL_STAGE)][tid] = w;   // the word; its slot is taken below
-            raw += hit ? 1 : 0;
+            raw += r2 < cut2 ? 1 : 0;
         });
     } else {
         raw = NL_STAGE + 1;
@@ -518,7 +427,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_patch_nlist(const Params* __restri
 // pair forces from the Verlet list (exclusions were applied when it was built).
 // Entries are taken four at a time: the four indices, then the four positions are
 // requested before any of them is used, so one bead keeps several loads in flight.
-template <typename R>
+template <typename R, int MODE = MODE_FORCE>
 __device__ __forceinline__ void pair_sep(const Params& P, double dx, double dy, double dz, R rc2, Acc<R>& a) {
     const R rx = (R)dx, ry = (R)dy, rz = (R)dz;
     const R r2 = mad(rz, rz, mad(ry, ry, rx * rx));
@@ -527,10 +436,14 @@ __device__ __forceinline__ void pair_sep(const Params& P, double dx, double dy, 
         const R sr2 = (R)P.sig2 * ir2;
         const R sr6 = sr2 * sr2 * sr2;
         // the separation is at hand in double: one conversion and three fused adds
-        const double fr = (double)((R)24.0 * (R)P.eps * mad((R)2.0 * sr6, sr6, -sr6) * ir2);
+        const double fr = (double)((R)24.0 * (R)P.eps * mad((R)2.0 * sr6, sr6, -sr6) * ir2);   // -dU/dr / r
         a.fx = fma(-fr, dx, a.fx);
         a.fy = fma(-fr, dy, a.fy);
         a.fz = fma(-fr, dz, a.fz);
+        if (MODE == MODE_ENERGY) {
+            a.e_pair += 0.5 * (double)((R)4.0 * (R)P.eps * (sr6 * sr6 - sr6) + (R)P.eps);
+            a.vir += 0.5 * (fr * (double)r2);
+        }
     }
 }
 template <typename R>
@@ -812,8 +725,8 @@ __device__ __forceinline__ void dihedral_ends(const Coef<R>& C, int t, R b1x, R 
 // shows in every velocity after some twenty steps, and mixed runs with DPD keep the
 // rounding, and with it the trajectories, that they have always had.  (There the
 // bonded terms of the few chain beads are a small part of the step.)
-template <typename R, int PAIR>
-constexpr bool unfused() { return sizeof(R) == 4 && PAIR == PAIR_DPD; }
+template <typename R, int MODE, int PAIR>
+constexpr bool unfused() { return MODE == MODE_FORCE && sizeof(R) == 4 && PAIR == PAIR_DPD; }
 
 __device__ __forceinline__ void bond_unfused(const Coef<float>& C, int t, double dx, double dy, double dz,
                                              Acc<float>& a) {
@@ -893,38 +806,38 @@ __device__ __forceinline__ void dihedral_unfused(const Coef<float>& C, bool end,
 }
 
 // one term of the step's force in the form the kernel's type and pair style take
-template <typename R, int PAIR>
+template <typename R, int MODE, int PAIR>
 __device__ __forceinline__ void bond_step(const Params& P, const Coef<R>& C, int t, double dx, double dy, double dz,
                                           Acc<R>& a) {
-    if constexpr (unfused<R, PAIR>()) bond_unfused(C, t, dx, dy, dz, a);
-    else bond_force<R, MODE_STEP>(P, C, t, dx, dy, dz, a);
+    if constexpr (unfused<R, MODE, PAIR>()) bond_unfused(C, t, dx, dy, dz, a);
+    else bond_force<R, MODE>(P, C, t, dx, dy, dz, a);
 }
 // (s1, s2 and s1, s2, s3: the other members' separations from the bead, in the order
 // of the halo's entry codes)
-template <typename R, int PAIR>
+template <typename R, int MODE, int PAIR>
 __device__ __forceinline__ void angle_step(const Coef<R>& C, uint32_t code, const V3<R>& s1, const V3<R>& s2,
                                            Acc<R>& a) {
     const bool centre = (code & 1u) != 0;
     const int t = (int)(code >> 8) & (DB_MAXT - 1);
-    if constexpr (unfused<R, PAIR>()) {
+    if constexpr (unfused<R, MODE, PAIR>()) {
         const V3<R> z{(R)0, (R)0, (R)0};
         angle_unfused(C, centre, t, centre ? s1 : sub(z, s1), centre ? s2 : sub(s2, s1), a);
     } else {
-        angle_share<R, MODE_STEP>(C, centre, t, s1, sub_scaled(s2, centre ? (R)0 : (R)1, s1), a);
+        angle_share<R, MODE>(C, centre, t, s1, sub_scaled(s2, centre ? (R)0 : (R)1, s1), a);
     }
 }
-template <typename R, int PAIR>
+template <typename R, int MODE, int PAIR>
 __device__ __forceinline__ void dihedral_step(const Coef<R>& C, uint32_t code, const V3<R>& s1, const V3<R>& s2,
                                               const V3<R>& s3, Acc<R>& a) {
     const bool end = (code & 1u) != 0;
     const int t = (int)(code >> 11) & (DB_MAXT - 1);
-    if constexpr (unfused<R, PAIR>()) {
+    if constexpr (unfused<R, MODE, PAIR>()) {
         const bool rev = (code & 2u) != 0;
         const V3<R> z{(R)0, (R)0, (R)0}, q0 = end ? z : s1, q1 = end ? s1 : z;
         const V3<R> pa = rev ? s3 : q0, pb = rev ? s2 : q1, pc = rev ? q1 : s2, pd = rev ? q0 : s3;
         dihedral_unfused(C, end, rev, t, sub(pb, pa), sub(pc, pb), sub(pd, pc), a);
     } else {
-        dihedral_share<R, MODE_STEP>(C, end, t, s1, sub_scaled(s2, end ? (R)1 : (R)0, s1), sub(s3, s2), a);
+        dihedral_share<R, MODE>(C, end, t, s1, sub_scaled(s2, end ? (R)1 : (R)0, s1), sub(s3, s2), a);
     }
 }
 
@@ -947,8 +860,7 @@ __device__ __forceinline__ void bond_terms(const Params& P, const Box& X, const 
         if (k >= nb) continue;
         const double4& xj = xs[k];
         const double dx = near_image(xj.x - xi.x, X), dy = near_image(xj.y - xi.y, X), dz = near_image(xj.z - xi.z, X);
-        if constexpr (MODE == MODE_ENERGY) bond_force<R, MODE>(P, C, tt[k], dx, dy, dz, a);
-        else bond_step<R, PAIR>(P, C, tt[k], dx, dy, dz, a);
+        bond_step<R, MODE, PAIR>(P, C, tt[k], dx, dy, dz, a);
     }
 }
 
@@ -960,7 +872,7 @@ __device__ __forceinline__ void angle_one(const Params& P, const Box& X, const C
     const int t = e.w & (DB_MAXT - 1);
     const bool centre = e.x != i && e.z != i;
     const double4 &x1 = e.z == i ? xc : xa, &x2 = e.z == i ? xa : xc;   // the bead's own end first
-    if constexpr (MODE == MODE_ENERGY || !unfused<R, PAIR>())
+    if constexpr (!unfused<R, MODE, PAIR>())
         angle_share<R, MODE>(C, centre, t, centre ? sep_of<R>(X, x1, xb) : sep_of<R>(X, xb, x1), sep_of<R>(X, x2, xb),
                              a);
     else
@@ -974,7 +886,7 @@ __device__ __forceinline__ void dihedral_one(const Params& P, const Box& X, cons
     // the path from the bead's own half: a b c d, or d c b a
     const bool rev = e.w == i || (e.x != i && e.y != i);
     const bool end = e.x == i || e.w == i;
-    if constexpr (MODE == MODE_ENERGY || !unfused<R, PAIR>()) {
+    if constexpr (!unfused<R, MODE, PAIR>()) {
         const double4 &pa = rev ? xd : xa, &pb = rev ? xc : xb, &pc = rev ? xb : xc, &pd = rev ? xa : xd;
         dihedral_share<R, MODE>(C, end, t, end ? sep_of<R>(X, pb, pa) : sep_of<R>(X, pa, pb), sep_of<R>(X, pc, pb),
                                 sep_of<R>(X, pd, pc), a);
@@ -1097,13 +1009,11 @@ __global__ __launch_bounds__(DB_BLOCK) void k_halo(const Params* __restrict__ Pp
 // all bonded forces on bead i from its halo (nu <= DB_MAXU entries).  The
 // separations are parked in LDS, one column per thread, so that angle and
 // dihedral entries can index them at run time without holding 24 registers.
-template <typename R, int PAIR>
+template <typename R, int MODE, int PAIR>
 __device__ __forceinline__ void halo_bonded(const Params& P, const Box& X, const Coef<R>& C, const Bank& B, const Halo& H, int i,
-                                            const double4& xi, int nu, Acc<R>& a) {
+                                            const double4& xi, int nu, R (*hs)[DB_MAXU][DB_BLOCK], Acc<R>& a) {
     const int n = P.n;
     const int tid = threadIdx.x;
-    __shared__ R hs[3][DB_MAXU][DB_BLOCK];
-    R hx[DB_MAXU], hy[DB_MAXU], hz[DB_MAXU];
     // Every per-bead word used below is requested before the first of them is
     // waited for, so that they share one memory latency instead of one each.
     // Rows exist for every bead: unused rows are read and then ignored.  The FP64
@@ -1139,7 +1049,7 @@ __device__ __forceinline__ void halo_bonded(const Params& P, const Box& X, const
             const double dy = near_image(xk[q].y - xi.y, X);
             const double dz = near_image(xk[q].z - xi.z, X);
             if (k0 + q < DB_MAXB && k0 + q < nb)
-                bond_step<R, PAIR>(P, C, btk[k0 + q] & (DB_MAXT - 1), dx, dy, dz, a);
+                bond_step<R, MODE, PAIR>(P, C, btk[k0 + q] & (DB_MAXT - 1), dx, dy, dz, a);
             hs[0][k0 + q][tid] = (R)dx;
             hs[1][k0 + q][tid] = (R)dy;
             hs[2][k0 + q][tid] = (R)dz;
@@ -1150,12 +1060,12 @@ __device__ __forceinline__ void halo_bonded(const Params& P, const Box& X, const
     for (int k = 0; k < na; ++k) {
         const uint32_t code = acode;
         if (k + 1 < na) acode = H.acode[(k + 1) * n + i];
-        angle_step<R, PAIR>(C, code, at(code >> 2), at(code >> 5), a);
+        angle_step<R, MODE, PAIR>(C, code, at(code >> 2), at(code >> 5), a);
     }
     for (int k = 0; k < nd; ++k) {
         const uint32_t code = dcode;
         if (k + 1 < nd) dcode = H.dcode[(k + 1) * n + i];
-        dihedral_step<R, PAIR>(C, code, at(code >> 2), at(code >> 5), at(code >> 8), a);
+        dihedral_step<R, MODE, PAIR>(C, code, at(code >> 2), at(code >> 5), at(code >> 8), a);
     }
 }
 
@@ -1187,17 +1097,16 @@ __device__ __forceinline__ void step_amplitudes(const Params& P, const int64_t* 
 // The step kernels are held to the registers of six (FP32 WCA), five (FP32 DPD)
 // and three (FP64) waves per SIMD, what their LDS allows or just below, which the
 // compiler otherwise gives up for a few registers.
-template <typename R, int MODE, bool BATCH, int PAIR>
-__global__ __launch_bounds__(DB_BLOCK, MODE != MODE_STEP ? 1 : (sizeof(R) == 8 ? 3 : (PAIR == PAIR_WCA ? 6 : 5)))
+template <typename R, bool BATCH, int PAIR>
+__global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 8 ? 3 : (PAIR == PAIR_WCA ? 6 : 5))
 void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __restrict__ xout, double* vout,
-            int64_t step, double pref, double dsig, unsigned int* __restrict__ vmax2_slot, double* __restrict__ fout,
-            int* __restrict__ err, double4* __restrict__ xsave, double* __restrict__ vsave,
+            int64_t step, double pref, double dsig, unsigned int* __restrict__ vmax2_slot, int* __restrict__ err, double4* __restrict__ xsave, double* __restrict__ vsave,
             const double4* __restrict__ xref, const int64_t* __restrict__ step_base) {
-    static_assert(MODE == MODE_STEP || MODE == MODE_FORCES, "energies use k_energy");
     const Params& P = *Pp;
     const int n = P.n;
     if (step_base) step_amplitudes(P, step_base, step, pref, dsig);
     __shared__ Coef<R> C;
+    __shared__ R hs[3][DB_MAXU][DB_BLOCK];
     load_coef<R>(P, C);
     __syncthreads();
     int tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -1223,15 +1132,15 @@ void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __
                 for (int q = 0; q < PQ; ++q) jpre[q] = NL.nl[q * n + i];
             }
             if (nu <= DB_MAXU) {
-                halo_bonded<R, PAIR>(P, X, C, B, H, i, xi, nu, a);
+                halo_bonded<R, MODE_FORCE, PAIR>(P, X, C, B, H, i, xi, nu, hs, a);
             } else {
                 // more distinct bonded partners than the halo holds: read them per entry
-                bond_terms<R, MODE_STEP, PAIR>(P, X, C, B, i, xi, B.nb[i], a);
-                angle_terms<R, MODE_STEP, PAIR>(P, X, C, B, i, B.na[i], a);
-                dihedral_terms<R, MODE_STEP, PAIR>(P, X, C, B, i, B.nd[i], a);
+                bond_terms<R, MODE_FORCE, PAIR>(P, X, C, B, i, xi, B.nb[i], a);
+                angle_terms<R, MODE_FORCE, PAIR>(P, X, C, B, i, B.na[i], a);
+                dihedral_terms<R, MODE_FORCE, PAIR>(P, X, C, B, i, B.nd[i], a);
             }
             if constexpr (PAIR == PAIR_DPD) {
-                if (MODE == MODE_STEP && P.dpd_gamma != 0.0) {
+                if (P.dpd_gamma != 0.0) {
                     if (BATCH) dsig = sqrt(2.0 * box_temperature(X, step) * P.dpd_gamma) / sqrt(P.dt);
                     list_pair_dpd<R, true>(P, X, B, NL, i, xi, B.v[i], B.v[n + i], B.v[2 * n + i], step, dsig, m_pair,
                                            jpre, a);
@@ -1246,13 +1155,6 @@ void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __
                 a.fx += P.fext[3 * g];
                 a.fy += P.fext[3 * g + 1];
                 a.fz += P.fext[3 * g + 2];
-            }
-            if (MODE == MODE_FORCES) {
-                int g = meta_gid(xi);
-                fout[3 * (size_t)g] = a.fx;
-                fout[3 * (size_t)g + 1] = a.fy;
-                fout[3 * (size_t)g + 2] = a.fz;
-                return;
             }
             vx = B.v[i];
             vy = B.v[n + i];
@@ -1302,18 +1204,16 @@ void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __
             }
         });
     }
-    if (MODE == MODE_STEP) {
-        // largest speed of the workgroup; one atomic per workgroup, spread over
-        // 64 words so that the workgroups of one step do not serialise on one address
-        __shared__ float wmax[DB_BLOCK / 64];
-        double v2 = wave_max(m2);
-        if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = (float)v2 * 1.0001f;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            float m = wmax[0];
-            for (int w = 1; w < DB_BLOCK / 64; ++w) m = fmaxf(m, wmax[w]);
-            atomicMax(vmax2_slot + (blockIdx.x & (DB_VMAX_SPREAD - 1)), __float_as_uint(m));
-        }
+    // largest speed of the workgroup; one atomic per workgroup, spread over 64 words
+    // so that the workgroups of one step do not serialise on one address
+    __shared__ float wmax[DB_BLOCK / 64];
+    double v2 = wave_max(m2);
+    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = (float)v2 * 1.0001f;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float m = wmax[0];
+        for (int w = 1; w < DB_BLOCK / 64; ++w) m = fmaxf(m, wmax[w]);
+        atomicMax(vmax2_slot + (blockIdx.x & (DB_VMAX_SPREAD - 1)), __float_as_uint(m));
     }
 }
 
@@ -1718,7 +1618,7 @@ __device__ __forceinline__ void tile_bonds(const Params& P, const Box& X, const 
         if (k >= tb.nb) continue;
         double dx, dy, dz;
         tp.sep(half16(tb.hu, k), xi, X, dx, dy, dz);
-        bond_force<R, MODE_STEP>(P, C, tb.btk[k] & (DB_MAXT - 1), dx, dy, dz, a);
+        bond_force<R, MODE_FORCE>(P, C, tb.btk[k] & (DB_MAXT - 1), dx, dy, dz, a);
     }
 }
 
@@ -1744,7 +1644,7 @@ __device__ __forceinline__ void tile_bonded(const Params& P, const Box& X, const
         if (k >= tb.nb) continue;
         double dx, dy, dz;
         tp.sep(STAGED ? half16(tb.hu, k) : member(k), xi, X, dx, dy, dz);
-        bond_force<R, MODE_STEP>(P, C, tb.btk[k] & (DB_MAXT - 1), dx, dy, dz, a);
+        bond_force<R, MODE_FORCE>(P, C, tb.btk[k] & (DB_MAXT - 1), dx, dy, dz, a);
     }
     auto at = [&](uint32_t q) {
         double dx, dy, dz;
@@ -1757,13 +1657,13 @@ __device__ __forceinline__ void tile_bonded(const Params& P, const Box& X, const
     for (int k = 0; k < DB_MAXA; ++k) {
         if (k >= tb.na) continue;
         const uint32_t code = k < 4 ? tb.ac[k < 4 ? k : 0] : H.acode[k * n + i];
-        angle_step<R, PAIR_WCA>(C, code, at(code >> 2), at(code >> 5), a);
+        angle_step<R, MODE_FORCE, PAIR_WCA>(C, code, at(code >> 2), at(code >> 5), a);
     }
 #pragma unroll
     for (int k = 0; k < DB_MAXD; ++k) {
         if (k >= tb.nd) continue;
         const uint32_t code = k < 4 ? tb.dc[k < 4 ? k : 0] : H.dcode[k * n + i];
-        dihedral_step<R, PAIR_WCA>(C, code, at(code >> 2), at(code >> 5), at(code >> 8), a);
+        dihedral_step<R, MODE_FORCE, PAIR_WCA>(C, code, at(code >> 2), at(code >> 5), at(code >> 8), a);
     }
 }
 
@@ -1789,18 +1689,18 @@ __device__ __forceinline__ void wide_bonded(const Params& P, const Box& X, const
         const int t = (int)B.bt[k * n + i] & (DB_MAXT - 1);
         const double4 xj = B.x[j];
         const double dx = near_image(xj.x - xi.x, X), dy = near_image(xj.y - xi.y, X), dz = near_image(xj.z - xi.z, X);
-        bond_force<R, MODE_STEP>(P, C, t, dx, dy, dz, a);
+        bond_force<R, MODE_FORCE>(P, C, t, dx, dy, dz, a);
     }
     const int na = B.na[i];
     for (int k = 0; k < na; ++k) {
         const int4 e = B.ang[k * n + i];
-        angle_one<R, MODE_STEP, PAIR_WCA>(P, X, C, i, e, B.x[e.x], B.x[e.y], B.x[e.z], a);
+        angle_one<R, MODE_FORCE, PAIR_WCA>(P, X, C, i, e, B.x[e.x], B.x[e.y], B.x[e.z], a);
     }
     const int nd = B.nd[i];
     for (int k = 0; k < nd; ++k) {
         const int4 e = B.dih[k * n + i];
         const int t = B.dt[k * n + i] & (DB_MAXT - 1);
-        dihedral_one<R, MODE_STEP, PAIR_WCA>(P, X, C, i, e, t, B.x[e.x], B.x[e.y], B.x[e.z], B.x[e.w], a);
+        dihedral_one<R, MODE_FORCE, PAIR_WCA>(P, X, C, i, e, t, B.x[e.x], B.x[e.y], B.x[e.z], B.x[e.w], a);
     }
 }
 
@@ -2122,83 +2022,205 @@ __global__ __launch_bounds__(DB_BLOCK) void k_step_tile(const Params* __restrict
     }
 }
 
-// energy reduction: a separate, simpler kernel keeps the step kernel lean
-template <typename R, bool BATCH>
-__global__ __launch_bounds__(DB_BLOCK) void k_energy(const Params* __restrict__ Pp, Bank B,
-                                                      const int* __restrict__ cstart, const int* __restrict__ clist,
-                                                      int64_t step, double* __restrict__ epart) {
+// Forces (MODE_FORCE: the conservative ones of db_forces, in bead-id order at fout)
+// or energies (MODE_ENERGY: with the thermostat's part of the force, for the
+// full-step velocities; the workgroup's six sums go to epart) at the current
+// positions, one thread per bead, straight from the cell list.
+//
+// A one-off evaluation has no use for a Verlet list: the 27 cells are scanned with
+// the pair cutoff, the kept candidates stay in the thread's LDS column, and their
+// pairs are evaluated from there in scan order, four positions requested at a time.
+// The bonded terms then go through the halo in the same LDS (one column per thread
+// in each layout, a barrier between).  It is bound by the scan, as the list build
+// is (L1 accesses and run-length divergence).  500k duplex beads, energies in FP64:
+// 110 us and 5 us for the final sum, against 400 us for a serial loop over the
+// candidates' double positions and 247 us for a final sum by six threads; 100k beads
+// of DPD solution in FP32 81 + 5 against 644 + 51 us; 191k duplex beads, forces in
+// FP32: 33 us against 42 for a list build and a force pass.
+template <typename R, int MODE, bool BATCH, int PAIR>
+__global__ __launch_bounds__(DB_BLOCK) void k_eval(const Params* __restrict__ Pp, Bank B, Halo H,
+                                                   const int* __restrict__ cstart, const float4* __restrict__ xs,
+                                                   int64_t step, double* __restrict__ fout,
+                                                   double* __restrict__ epart, int* __restrict__ err) {
     const Params& P = *Pp;
     const int n = P.n;
+    constexpr int EV_STAGE = 32;   // candidates kept per bead (DPD at density 3 has about 13)
     __shared__ Coef<R> C;
+    __shared__ union {
+        int stage[EV_STAGE + 1][DB_BLOCK];   // the last row takes the candidates that are not kept
+        R hs[3][DB_MAXU][DB_BLOCK];
+    } lds;
     load_coef<R>(P, C);
-    __syncthreads();
-    int i = blockIdx.x * DB_BLOCK + threadIdx.x;
+    const int tid = threadIdx.x;
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int i = tile * DB_BLOCK + tid;
+    const bool active = i < n;
+    Acc<R> a;
+    double4 xi = make_double4(0, 0, 0, 0);
+    double vx = 0, vy = 0, vz = 0;
+    if (active) {
+        xi = B.x[i];
+        if (MODE == MODE_ENERGY) {
+            vx = B.v[i];
+            vy = B.v[n + i];
+            vz = B.v[2 * n + i];
+        }
+    }
+    if (active && P.have_pair) {
+        with_box<BATCH>(P, meta_word(xi), [&](const Box& X) __attribute__((always_inline)) {
+            ExclSet E;
+            gather_excl(P, B, n, i, E);
+            const double reach = P.rc + X.pf_slack;
+            const float cut2 = (float)(reach * reach * 1.0001);
+            const R rc2 = (R)P.rc2;
+            double dsig = 0.0;
+            if (MODE == MODE_ENERGY && PAIR == PAIR_DPD && P.dpd_gamma != 0.0)
+                dsig = sqrt(2.0 * box_temperature(X, step) * P.dpd_gamma) / sqrt(P.dt);
+            auto pair = [&](int j, const double4& xj) {
+                const double dx = near_image(xj.x - xi.x, X), dy = near_image(xj.y - xi.y, X),
+                             dz = near_image(xj.z - xi.z, X);
+                if constexpr (PAIR == PAIR_DPD) {
+                    const R rx = (R)dx, ry = (R)dy, rz = (R)dz;
+                    const R r2 = (rx * rx + ry * ry) + rz * rz;
+                    if (!(r2 < rc2)) return;
+                    if (MODE == MODE_ENERGY && P.dpd_gamma != 0.0)
+                        dpd_pair<R, true, true>(P, X, xi, xj, dx, dy, dz, r2, vx - B.v[j], vy - B.v[n + j],
+                                                vz - B.v[2 * n + j], step, dsig, a);
+                    else
+                        dpd_pair<R, false, MODE == MODE_ENERGY>(P, X, xi, xj, dx, dy, dz, r2, 0, 0, 0, 0, 0, a);
+                } else {
+                    pair_sep<R, MODE>(P, dx, dy, dz, rc2, a);
+                }
+            };
+            int raw = EV_STAGE + 1;
+            bool crowded = X.noff != 3;   // more than a Verlet list's capacity of beads may be within its cutoff
+            if (X.noff == 3) {
+                raw = 0;
+                int listed = 0;
+                const float list2 = X.pf_list2;
+                scan_cells_all(X, cstart, xs, i, xi, [&](int w, float r2) {
+                    lds.stage[min(raw, EV_STAGE)][tid] = w;
+                    raw += r2 < cut2 ? 1 : 0;
+                    if (MODE == MODE_FORCE) listed += r2 < list2 ? 1 : 0;
+                });
+                crowded = listed > DB_NLCAP;
+            }
+            if (raw <= EV_STAGE) {
+                int cnt = 0;
+                for (int k = 0; k < raw; ++k) {   // exclusions, compacting in place
+                    const int j = xs_slot(lds.stage[k][tid]);
+                    if (E.has(j)) continue;
+                    lds.stage[cnt][tid] = j;
+                    ++cnt;
+                }
+                for (int k0 = 0; k0 < cnt; k0 += 4) {
+                    int j[4];
+                    double4 xj[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) j[q] = lds.stage[min(k0 + q, cnt - 1)][tid];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) xj[q] = B.x[j[q]];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (k0 + q < cnt) pair(j[q], xj[q]);
+                }
+            } else {   // crowded, or a grid of fewer than three cells per edge
+                scan_cells(X, cstart, xs, i, xi, cut2, [&](int j, int) {
+                    if (!E.has(j)) pair(j, B.x[j]);
+                });
+            }
+            // a bead whose Verlet list would overflow is an error here too
+            if (MODE == MODE_FORCE && crowded) {
+                int c = 0;
+                scan_cells(X, cstart, xs, i, xi, X.pf_list2, [&](int j, int) { c += E.has(j) ? 0 : 1; });
+                if (c > DB_NLCAP) atomicOr(err, ERR_NLIST);
+            }
+        });
+    }
+    __syncthreads();   // the coefficients, and the LDS columns change their layout
     double vals[6] = {0, 0, 0, 0, 0, 0};
-    if (i < n) {
-        Acc<R> a;
-        double4 xi = B.x[i];
-        const Box& X = box_of<BATCH>(P, meta_word(xi));
-        int nb = B.nb[i];
-        int p0 = nb > 0 ? B.bp[i] : -1;
-        int p1 = nb > 1 ? B.bp[n + i] : -1;
-        int p2 = nb > 2 ? B.bp[2 * n + i] : -1;
-        int p3 = nb > 3 ? B.bp[3 * n + i] : -1;
-        double vx = B.v[i], vy = B.v[n + i], vz = B.v[2 * n + i];
-        const double dsig = P.pair_style == PAIR_DPD && P.dpd_gamma != 0.0
-                                ? sqrt(2.0 * box_temperature(X, step) * P.dpd_gamma) / sqrt(P.dt)
-                                : 0.0;
-        if (P.have_pair)
-            pair_forces<R, MODE_ENERGY>(P, X, B, cstart, clist, i, xi, nb, p0, p1, p2, p3, vx, vy, vz, step, dsig,
-                                        a);
-        bond_terms<R, MODE_ENERGY, PAIR_WCA>(P, X, C, B, i, xi, nb, a);
-        angle_terms<R, MODE_ENERGY, PAIR_WCA>(P, X, C, B, i, B.na[i], a);
-        dihedral_terms<R, MODE_ENERGY, PAIR_WCA>(P, X, C, B, i, B.nd[i], a);
-        if (P.has_ext) {
+    if (active) {
+        with_box<BATCH>(P, meta_word(xi), [&](const Box& X) __attribute__((always_inline)) {
+            const int nu = H.nu[i];
+            if (nu <= DB_MAXU) {
+                halo_bonded<R, MODE, PAIR>(P, X, C, B, H, i, xi, nu, lds.hs, a);
+            } else {
+                bond_terms<R, MODE, PAIR>(P, X, C, B, i, xi, B.nb[i], a);
+                angle_terms<R, MODE, PAIR>(P, X, C, B, i, B.na[i], a);
+                dihedral_terms<R, MODE, PAIR>(P, X, C, B, i, B.nd[i], a);
+            }
             const size_t g = (size_t)meta_gid(xi);
-            a.fx += P.fext[3 * g];
-            a.fy += P.fext[3 * g + 1];
-            a.fz += P.fext[3 * g + 2];
-        }
-        double Fx = a.fx, Fy = a.fy, Fz = a.fz;
-        if (P.gamma != 0.0) {
-            double pref = sqrt(24.0 * P.gamma * box_temperature(X, step) / P.dt);
-            uint4 w = rng_draw(X, (uint32_t)(meta_gid(xi) - X.gid_off), 0u, step, RNG_LANGEVIN);
-            const double s32 = 1.0 / 4294967296.0;
-            double ux = ((double)w.x + 0.5) * s32, uy = ((double)w.y + 0.5) * s32, uz = ((double)w.z + 0.5) * s32;
-            Fx = (Fx - P.gamma * vx) + pref * (ux - 0.5);
-            Fy = (Fy - P.gamma * vy) + pref * (uy - 0.5);
-            Fz = (Fz - P.gamma * vz) + pref * (uz - 0.5);
-        }
-        const double hdt = 0.5 * P.dt;
-        double fvx = vx + hdt * Fx, fvy = vy + hdt * Fy, fvz = vz + hdt * Fz;
-        vals[0] = 0.5 * (fvx * fvx + fvy * fvy + fvz * fvz);
-        vals[1] = a.e_pair;
-        vals[2] = a.e_bond;
-        vals[3] = a.e_ang;
-        vals[4] = a.e_dih;
-        vals[5] = a.vir;
+            if (P.has_ext) {
+                a.fx += P.fext[3 * g];
+                a.fy += P.fext[3 * g + 1];
+                a.fz += P.fext[3 * g + 2];
+            }
+            if (MODE == MODE_FORCE) {
+                fout[3 * g] = a.fx;
+                fout[3 * g + 1] = a.fy;
+                fout[3 * g + 2] = a.fz;
+                return;
+            }
+            double Fx = a.fx, Fy = a.fy, Fz = a.fz;
+            if (P.gamma != 0.0) {
+                const double pref = sqrt(24.0 * P.gamma * box_temperature(X, step) / P.dt);
+                const uint4 w = rng_draw(X, (uint32_t)(meta_gid(xi) - X.gid_off), 0u, step, RNG_LANGEVIN);
+                const double s32 = 1.0 / 4294967296.0;
+                const double ux = ((double)w.x + 0.5) * s32, uy = ((double)w.y + 0.5) * s32,
+                             uz = ((double)w.z + 0.5) * s32;
+                Fx = (Fx - P.gamma * vx) + pref * (ux - 0.5);
+                Fy = (Fy - P.gamma * vy) + pref * (uy - 0.5);
+                Fz = (Fz - P.gamma * vz) + pref * (uz - 0.5);
+            }
+            const double hdt = 0.5 * P.dt;
+            const double fvx = vx + hdt * Fx, fvy = vy + hdt * Fy, fvz = vz + hdt * Fz;
+            vals[0] = 0.5 * (fvx * fvx + fvy * fvy + fvz * fvz);
+            vals[1] = a.e_pair;
+            vals[2] = a.e_bond;
+            vals[3] = a.e_ang;
+            vals[4] = a.e_dih;
+            vals[5] = a.vir;
+        });
     }
-    __shared__ double red[6][DB_BLOCK / 64];
-    for (int q = 0; q < 6; ++q) {
-        double v = vals[q];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if ((threadIdx.x & 63) == 0) red[q][threadIdx.x >> 6] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < 6) {
-        double s = 0;
-        for (int w = 0; w < DB_BLOCK / 64; ++w) s += red[threadIdx.x][w];
-        epart[(size_t)blockIdx.x * 6 + threadIdx.x] = s;
+    if constexpr (MODE == MODE_ENERGY) {
+        __shared__ double red[6][DB_BLOCK / 64];
+        for (int q = 0; q < 6; ++q) {
+            double v = vals[q];
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+            if ((tid & 63) == 0) red[q][tid >> 6] = v;
+        }
+        __syncthreads();
+        if (tid < 6) {
+            double s = 0;
+            for (int w = 0; w < DB_BLOCK / 64; ++w) s += red[tid][w];
+            epart[(size_t)tile * 6 + tid] = s;
+        }
     }
 }
 
-// fixed-order sum of the per-workgroup partials
-__global__ void k_energy_final(const double* __restrict__ epart, int nblocks, double* __restrict__ out) {
-    int q = threadIdx.x;
-    if (q >= 6) return;
-    double s = 0;
-    for (int b = 0; b < nblocks; ++b) s += epart[(size_t)b * 6 + q];
-    out[q] = s;
+// The workgroups' sums in a fixed order: every thread adds up every 1024th partial
+// of each of the six (so that all are in flight together: a serial chain over a
+// million beads' partials took 247 us), then a tree over the threads.
+#define DB_FINAL_BLOCK 1024
+__global__ __launch_bounds__(DB_FINAL_BLOCK) void k_energy_final(const double* __restrict__ epart, int nblocks,
+                                                                 double* __restrict__ out) {
+    __shared__ double red[6][DB_FINAL_BLOCK / 64];
+    double s[6] = {0, 0, 0, 0, 0, 0};
+    for (int b = threadIdx.x; b < nblocks; b += DB_FINAL_BLOCK) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) s[q] += epart[(size_t)b * 6 + q];
+    }
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+        for (int o = 32; o > 0; o >>= 1) s[q] += __shfl_xor(s[q], o, 64);
+        if ((threadIdx.x & 63) == 0) red[q][threadIdx.x >> 6] = s[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < 6) {
+        double t = 0;
+        for (int w = 0; w < DB_FINAL_BLOCK / 64; ++w) t += red[threadIdx.x][w];
+        out[threadIdx.x] = t;
+    }
 }
 
 static unsigned grid_for(int n) { return (unsigned)((n + DB_BLOCK - 1) / DB_BLOCK); }
@@ -2295,38 +2317,28 @@ static bool velocity_double_buffer(const db_ctx* c) {
     return c->hp.have_pair && c->hp.pair_style == PAIR_DPD && c->hp.dpd_gamma != 0.0;
 }
 
-template <typename R, int MODE, bool BATCH, int PAIR>
+template <typename R, bool BATCH, int PAIR>
 static void launch_step_kernel(db_ctx* c, const Bank& B, double4* xout, double* vout, int64_t step, double pref,
-                               double dsig, unsigned* vm, double* f, bool save) {
-    hipLaunchKernelGGL((k_step<R, MODE, BATCH, PAIR>), dim3(grid_for(c->n)), dim3(DB_BLOCK), 0, c->stream, c->dp,
-                       B, c->nlist, c->halo, xout, vout, step, pref, dsig, vm, f, c->err_d,
-                       save ? c->xsave : nullptr, save ? c->vsave : nullptr, c->xref,
-                       MODE == MODE_STEP ? (const int64_t*)c->step_base_d : nullptr);
+                               double dsig, unsigned* vm, bool save) {
+    hipLaunchKernelGGL((k_step<R, BATCH, PAIR>), dim3(grid_for(c->n)), dim3(DB_BLOCK), 0, c->stream, c->dp, B,
+                       c->nlist, c->halo, xout, vout, step, pref, dsig, vm, c->err_d, save ? c->xsave : nullptr,
+                       save ? c->vsave : nullptr, c->xref, (const int64_t*)c->step_base_d);
 }
 
-template <int MODE, int PAIR>
+template <int PAIR>
 static void launch_step_pair(db_ctx* c, const Bank& B, double4* xout, double* vout, int64_t step, double pref,
-                             double dsig, unsigned* vm, double* f, bool save) {
+                             double dsig, unsigned* vm, bool save) {
     const bool batch = c->nrep > 0;
     if (c->precision == DB_MIXED) {
-        if (batch) launch_step_kernel<float, MODE, true, PAIR>(c, B, xout, vout, step, pref, dsig, vm, f, save);
-        else launch_step_kernel<float, MODE, false, PAIR>(c, B, xout, vout, step, pref, dsig, vm, f, save);
+        if (batch) launch_step_kernel<float, true, PAIR>(c, B, xout, vout, step, pref, dsig, vm, save);
+        else launch_step_kernel<float, false, PAIR>(c, B, xout, vout, step, pref, dsig, vm, save);
     } else {
-        if (batch)
-            launch_step_kernel<double, MODE, true, PAIR>(c, B, xout, vout, step, pref, dsig, vm, f, save);
-        else
-            launch_step_kernel<double, MODE, false, PAIR>(c, B, xout, vout, step, pref, dsig, vm, f, save);
+        if (batch) launch_step_kernel<double, true, PAIR>(c, B, xout, vout, step, pref, dsig, vm, save);
+        else launch_step_kernel<double, false, PAIR>(c, B, xout, vout, step, pref, dsig, vm, save);
     }
 }
 
-template <int MODE>
-static void launch_step_any(db_ctx* c, const Bank& B, double4* xout, double* vout, int64_t step, double pref,
-                            double dsig, unsigned* vm, double* f, bool save = false) {
-    if (c->hp.have_pair && c->hp.pair_style == PAIR_DPD)
-        launch_step_pair<MODE, PAIR_DPD>(c, B, xout, vout, step, pref, dsig, vm, f, save);
-    else
-        launch_step_pair<MODE, PAIR_WCA>(c, B, xout, vout, step, pref, dsig, vm, f, save);
-}
+static bool dpd_pairs(const db_ctx* c) { return c->hp.have_pair && c->hp.pair_style == PAIR_DPD; }
 
 // c->step_base_d set (the launch is captured into a graph): step is the offset within
 // the block and the kernel reads the block's first step from the device
@@ -2349,7 +2361,9 @@ void launch_step(db_ctx* c, int64_t step, int slot_in_block, bool save) {
                                c->nlist, c->halo, c->tiles, c->xnext, step, pref, vm, c->err_d, xs, vs,
                                (const int64_t*)c->step_base_d);
     } else {
-        launch_step_any<MODE_STEP>(c, B, c->xnext, vbuf ? c->vnext : B.v, step, pref, dsig, vm, nullptr, save);
+        double* vout = vbuf ? c->vnext : B.v;
+        if (dpd_pairs(c)) launch_step_pair<PAIR_DPD>(c, B, c->xnext, vout, step, pref, dsig, vm, save);
+        else launch_step_pair<PAIR_WCA>(c, B, c->xnext, vout, step, pref, dsig, vm, save);
     }
     double4* t = B.x;
     B.x = c->xnext;
@@ -2361,31 +2375,40 @@ void launch_step(db_ctx* c, int64_t step, int slot_in_block, bool save) {
     }
 }
 
-void launch_forces(db_ctx* c, double* f) {
-    if (c->n == 0) return;
-    launch_step_any<MODE_FORCES>(c, c->bank[c->cur], nullptr, nullptr, 0, 0.0, 0.0, nullptr, f);
+// k_eval with the handle's force type, box form and pair style
+template <typename R, int MODE, bool BATCH>
+static void launch_eval_pair(db_ctx* c, double* f, double* part) {
+    const unsigned nb = grid_for(c->n);
+    if (dpd_pairs(c))
+        hipLaunchKernelGGL((k_eval<R, MODE, BATCH, PAIR_DPD>), dim3(nb), dim3(DB_BLOCK), 0, c->stream, c->dp,
+                           c->bank[c->cur], c->halo, c->cells.start, c->cells.xs, c->step, f, part, c->err_d);
+    else
+        hipLaunchKernelGGL((k_eval<R, MODE, BATCH, PAIR_WCA>), dim3(nb), dim3(DB_BLOCK), 0, c->stream, c->dp,
+                           c->bank[c->cur], c->halo, c->cells.start, c->cells.xs, c->step, f, part, c->err_d);
 }
 
-template <typename R, bool BATCH>
-static void launch_energy_kernel(db_ctx* c, unsigned nb, double* part) {
-    hipLaunchKernelGGL((k_energy<R, BATCH>), dim3(nb), dim3(DB_BLOCK), 0, c->stream, c->dp, c->bank[c->cur],
-                       c->cells.start, c->cells.list, c->step, part);
+template <int MODE>
+static void launch_eval(db_ctx* c, double* f, double* part) {
+    launch_halo(c);
+    const bool batch = c->nrep > 0;
+    if (c->precision == DB_MIXED) {
+        if (batch) launch_eval_pair<float, MODE, true>(c, f, part);
+        else launch_eval_pair<float, MODE, false>(c, f, part);
+    } else {
+        if (batch) launch_eval_pair<double, MODE, true>(c, f, part);
+        else launch_eval_pair<double, MODE, false>(c, f, part);
+    }
+}
+
+void launch_forces(db_ctx* c, double* f) {
+    if (c->n > 0) launch_eval<MODE_FORCE>(c, f, nullptr);
 }
 
 void launch_energy(db_ctx* c, double* out6, double* partials) {
-    unsigned nb = grid_for(c->n);
     double* part = partials ? partials : c->red;
-    if (c->n > 0) {
-        const bool batch = c->nrep > 0;
-        if (c->precision == DB_MIXED) {
-            if (batch) launch_energy_kernel<float, true>(c, nb, part);
-            else launch_energy_kernel<float, false>(c, nb, part);
-        } else {
-            if (batch) launch_energy_kernel<double, true>(c, nb, part);
-            else launch_energy_kernel<double, false>(c, nb, part);
-        }
-    }
-    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(64), 0, c->stream, part, (int)(c->n > 0 ? nb : 0), out6);
+    if (c->n > 0) launch_eval<MODE_ENERGY>(c, nullptr, part);
+    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(DB_FINAL_BLOCK), 0, c->stream, part,
+                       (int)(c->n > 0 ? grid_for(c->n) : 0), out6);
 }
 
 }  // namespace db

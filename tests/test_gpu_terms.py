@@ -1,4 +1,4 @@
-"""Angle and dihedral forces over the whole range of bends and torsions, GPU against the oracle.
+"""Terms of the force and energy evaluations at the edges of their ranges, GPU against the oracle.
 
 The step kernel takes (pi - theta) / sin(theta) from a polynomial up to 45 degrees from the straight angle and from
 an arctangent beyond, and reads a dihedral from either end: molecules of three and four beads sit on both sides of the
@@ -70,3 +70,35 @@ def test_bends_and_torsions_match_oracle(precision, pair, kind):
     eg, eo = g.energy(), o.energy()
     for k in (3, 4):
         assert abs(eg[k] - eo[k]) <= tol * max(1.0, abs(eo[k])), (k, eg[k], eo[k])
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n,L", [(1, 2.2), (60, 2.2), (257, 2.9), (300, 3.3), (1000, 4.1)])
+def test_evaluation_from_cells_matches_oracle(n, L, precision):
+    """One, two, three and four cells per edge (a list cutoff of 1.02), from a lone bead to a density of 14 where
+    most beads have more candidates than the staged rows hold.  The DPD pairs are soft, so every term is good to
+    some twenty roundings of numbers of order 25, summed over at most about 100 pairs."""
+    s = synth.random_gas(n, L, seed=n)
+    ff = synth.ff_dpd(gamma_dpd=20.0)
+    g, o = both(s, ff, synth.RuleSet(every=0), precision=precision, generate=False)
+    tol = 1e-12 if precision == 0 else 1e-5
+    if n > 1:
+        ok, msg = forces_close(g.forces(), o.forces(), tol)
+        assert ok, msg
+    eg, eo = g.energy(), o.energy()
+    assert np.all(np.abs(eg - eo) <= 10 * tol * np.maximum(1.0, np.abs(eo))), (eg, eo)
+
+
+def test_forces_report_a_crowded_bead():
+    """A clump whose central beads have more neighbours within the list cutoff than a list holds is an error of the
+    force evaluation, though it reads no list."""
+    import paper_1108_4214_amd as pk
+    rng = np.random.default_rng(41)
+    d = rng.normal(size=(300, 3))
+    d *= 1.2 * rng.uniform(size=(300, 1)) ** (1.0 / 3.0) / np.linalg.norm(d, axis=1)[:, None]
+    s = synth.System(L=20.0, x=10.0 + d, v=np.zeros_like(d), type=np.ones(300, dtype=np.int32),
+                     reactive=np.zeros(300, dtype=np.uint8), bonds=np.zeros((0, 4), dtype=np.int32))
+    g = pk.System(s.n, s.L, 3).configure(s, synth.ForceField(eps=0.0), synth.RuleSet(every=0))
+    with pytest.raises(pk.DynBondError) as e:
+        g.forces()
+    assert e.value.code == pk.DB_ECAPACITY
