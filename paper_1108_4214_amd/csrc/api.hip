@@ -91,12 +91,12 @@ struct HostSys {
 
 struct db_host_ext {
     HostSys h;
-    bool host_valid = true;   // host copies reflect the current state
+    bool host_valid = true;   // host copies reflect the current positions and velocities
+    bool topo_valid = true;   // host lists reflect the current topology
     bool dev_valid = false;   // device holds the current state
     int dev_error = 0;        // latched device error code
     Pinned* pin = nullptr;
     Pinned* pin_dev = nullptr;   // device view of pin
-    int* tmp_n1 = nullptr;    // n + 1 ints
 };
 
 static db_host_ext& ext(db_ctx* c) { return *c->hx; }
@@ -224,9 +224,8 @@ static size_t layout(db_ctx* c, bool assign) {
     put(c->ledger_d, 8 * 16);
     put(c->dp, sizeof(Params));
     put(c->rep_d, sizeof(Box) * (size_t)std::max(1, c->nrep));
-    int* t1 = nullptr;
-    put(t1, 4 * (n + 1));
-    if (assign) ext(c).tmp_n1 = t1;
+    int* unused = nullptr;   // keeps the arena's size, which checkpoints record
+    put(unused, 4 * (n + 1));
     return L.total;
 }
 
@@ -492,11 +491,6 @@ static int upload_system(db_ctx* c) {
     return DB_OK;
 }
 
-namespace db {
-void launch_owned_offsets(db_ctx* c, int kind, int* buf);
-void launch_write_owned(db_ctx* c, int kind, const int* off, int32_t* tup, int32_t* typ);
-}  // namespace db
-
 __global__ void k_gather_state(int n, Bank B, double* __restrict__ xo, double* __restrict__ vo) {
     int s = blockIdx.x * DB_BLOCK + threadIdx.x;
     if (s >= n) return;
@@ -514,92 +508,73 @@ __global__ void k_gather_state(int n, Bank B, double* __restrict__ xo, double* _
     }
 }
 
-// scratch for gathers: the per-bead storage of the inactive bank (free between reorders)
-static char* gather_scratch(db_ctx* c, size_t bytes) {
-    Bank& O = c->bank[1 - c->cur];
-    size_t avail = (size_t)((char*)O.nd - (char*)O.ang);
-    (void)avail;
-    (void)bytes;
-    return (char*)O.ang;
-}
-static size_t gather_scratch_bytes(db_ctx* c) {
-    Bank& O = c->bank[1 - c->cur];
-    return (size_t)((char*)O.nd - (char*)O.ang);
-}
+// scratch for gathers: tables of the inactive bank (free between reorders), 192 bytes
+// per bead at ang and 256 at dih
+static char* gather_scratch(db_ctx* c) { return (char*)c->bank[1 - c->cur].ang; }
 
-static int read_owned(db_ctx* c, int kind, std::vector<int32_t>& tup, std::vector<int32_t>& typ, int64_t* count) {
-    const int n = c->n;
-    const int width = kind == 0 ? 2 : (kind == 1 ? 3 : 4);
-    const int twidth = kind == 0 ? 2 : 1;
+// device -> host lists of the topology in bead ids, canonical and sorted
+static int download_topology(db_ctx* c) {
+    db_host_ext& X = ext(c);
+    if (X.topo_valid || !X.dev_valid) return DB_OK;
+    HostSys& h = X.h;
+    const size_t n = (size_t)c->n;
     if (n == 0) {
-        *count = 0;
-        tup.clear();
-        typ.clear();
+        h.bonds.clear();
+        h.ang.clear();
+        h.dih.clear();
+        X.topo_valid = true;
         return DB_OK;
     }
-    int* off = ext(c).tmp_n1;
-    launch_owned_offsets(c, kind, off);
-    HIPCHK(c, hipMemcpyAsync(&ext(c).pin->total[0], off + n, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    // a bead's 4 bonds, 12 angles and 16 dihedrals are shared by 2, 3 and 4 beads: at
+    // most 2 n rows of 16 bytes, 4 n of 16 and 4 n of 20 fit the scratch's 192 n bytes
+    static_assert(16 * DB_MAXB / 2 + 16 * DB_MAXA / 3 + 20 * DB_MAXD / 4 <= 16 * DB_MAXA, "the lists fit the scratch");
+    int* off = (int*)c->bank[1 - c->cur].dih;
+    launch_owned_offsets(c, off, X.pin_dev->total);
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    int64_t m = ext(c).pin->total[0];
-    *count = m;
-    size_t need = (size_t)m * 4 * (width + twidth);
-    if (need > gather_scratch_bytes(c)) return fail(c, DB_ECAPACITY, "topology list larger than the gather scratch");
-    int32_t* dtup = (int32_t*)gather_scratch(c, need);
-    int32_t* dtyp = dtup + (size_t)m * width;
-    launch_write_owned(c, kind, off, dtup, dtyp);
-    tup.resize((size_t)m * width);
-    typ.resize((size_t)m * twidth);
-    if (m) {
-        HIPCHK(c, hipMemcpyAsync(tup.data(), dtup, 4 * (size_t)m * width, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipMemcpyAsync(typ.data(), dtyp, 4 * (size_t)m * twidth, hipMemcpyDeviceToHost, c->stream));
-    }
+    const size_t nb = (size_t)X.pin->total[0], na = (size_t)X.pin->total[1], nd = (size_t)X.pin->total[2];
+    if (16 * (nb + na) + 20 * nd > 16 * DB_MAXA * n)
+        return fail(c, DB_ECAPACITY, "topology list larger than the gather scratch");
+    int* bonds = (int*)gather_scratch(c);
+    int* ang = bonds + 4 * nb;
+    int* dih = ang + 4 * na;
+    launch_write_owned(c, off, bonds, ang, dih);
+    h.bonds.resize(4 * nb);
+    h.ang.resize(4 * na);
+    h.dih.resize(5 * nd);
+    if (nb) HIPCHK(c, hipMemcpyAsync(h.bonds.data(), bonds, 16 * nb, hipMemcpyDeviceToHost, c->stream));
+    if (na) HIPCHK(c, hipMemcpyAsync(h.ang.data(), ang, 16 * na, hipMemcpyDeviceToHost, c->stream));
+    if (nd) HIPCHK(c, hipMemcpyAsync(h.dih.data(), dih, 20 * nd, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipGetLastError());
+    X.topo_valid = true;
     return DB_OK;
 }
 
-// device -> host copies in bead-id order, canonical and sorted topology
+// device -> host copies in bead-id order
 static int download_system(db_ctx* c) {
     db_host_ext& X = ext(c);
+    int rc = download_topology(c);
+    if (rc) return rc;
     if (X.host_valid || !X.dev_valid) return DB_OK;
     const int n = c->n;
     HostSys& h = X.h;
     if (n > 0) {
-        double* d = (double*)gather_scratch(c, 48 * (size_t)n);
+        double* d = (double*)gather_scratch(c);
         hipLaunchKernelGGL(k_gather_state, dim3((n + DB_BLOCK - 1) / DB_BLOCK), dim3(DB_BLOCK), 0, c->stream, n,
                            c->bank[c->cur], d, d + 3 * (size_t)n);
         HIPCHK(c, hipMemcpyAsync(h.x.data(), d, 24 * (size_t)n, hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipMemcpyAsync(h.v.data(), d + 3 * (size_t)n, 24 * (size_t)n, hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
-    }
-    std::vector<int32_t> tup, typ;
-    int64_t m;
-    int rc = read_owned(c, 0, tup, typ, &m);
-    if (rc) return rc;
-    h.bonds.resize(4 * (size_t)m);
-    for (int64_t k = 0; k < m; ++k) {
-        h.bonds[4 * k] = tup[2 * k];
-        h.bonds[4 * k + 1] = tup[2 * k + 1];
-        h.bonds[4 * k + 2] = typ[2 * k];
-        h.bonds[4 * k + 3] = typ[2 * k + 1];
-    }
-    rc = read_owned(c, 1, tup, typ, &m);
-    if (rc) return rc;
-    h.ang.resize(4 * (size_t)m);
-    for (int64_t k = 0; k < m; ++k) {
-        h.ang[4 * k] = typ[k];
-        for (int q = 0; q < 3; ++q) h.ang[4 * k + 1 + q] = tup[3 * k + q];
-    }
-    rc = read_owned(c, 2, tup, typ, &m);
-    if (rc) return rc;
-    h.dih.resize(5 * (size_t)m);
-    for (int64_t k = 0; k < m; ++k) {
-        h.dih[5 * k] = typ[k];
-        for (int q = 0; q < 4; ++q) h.dih[5 * k + 1 + q] = tup[4 * k + q];
+        HIPCHK(c, hipGetLastError());
     }
     X.host_valid = true;
     return DB_OK;
+}
+
+// the host copies no longer follow the device
+static void host_stale(db_ctx* c) {
+    ext(c).host_valid = false;
+    ext(c).topo_valid = false;
 }
 
 // make the device state current (upload once after host-side edits)
@@ -621,7 +596,7 @@ static int ready(db_ctx* c) {
 // host-side edits start from a current host copy
 static int editable(db_ctx* c) {
     db_host_ext& X = ext(c);
-    if (X.dev_valid && !X.host_valid && !X.dev_error) {
+    if (X.dev_valid && !X.dev_error) {
         int rc = download_system(c);
         if (rc) return rc;
     }
@@ -650,28 +625,35 @@ static void rebuild(db_ctx* c, bool permute, bool save = false, bool cells_ready
 }
 
 // rows of src: tuple then types (typ_first = 0) or types then tuple (typ_first = 1);
-// written sorted by tuple, then type
+// written sorted by tuple, then type.  Lists that came from the device are sorted
+// already; a list as the caller set it may not be.
 template <int W, int TW>
 static void sorted_copy(const std::vector<int32_t>& src, int32_t* tup, int32_t* typ, int typ_first) {
-    // src rows: [typ_first ? type, tuple : tuple, types]
-    const size_t rows = src.size() / (W + TW);
+    constexpr int S = W + TW;
+    const size_t rows = src.size() / S;
+    const int t0 = typ_first ? TW : 0, y0 = typ_first ? 0 : W;
+    auto less = [&](const int32_t* a, const int32_t* b) {
+        for (int q = 0; q < W; ++q)
+            if (a[t0 + q] != b[t0 + q]) return a[t0 + q] < b[t0 + q];
+        for (int q = 0; q < TW; ++q)
+            if (a[y0 + q] != b[y0 + q]) return a[y0 + q] < b[y0 + q];
+        return false;
+    };
+    const int32_t* p = src.data();
+    auto put = [&](size_t k, const int32_t* r) {
+        for (int q = 0; q < W; ++q) tup[k * W + q] = r[t0 + q];
+        for (int q = 0; q < TW; ++q) typ[k * TW + q] = r[y0 + q];
+    };
+    bool sorted = true;
+    for (size_t k = 1; k < rows && sorted; ++k) sorted = !less(p + k * S, p + (k - 1) * S);
+    if (sorted) {
+        for (size_t k = 0; k < rows; ++k) put(k, p + k * S);
+        return;
+    }
     std::vector<size_t> idx(rows);
     std::iota(idx.begin(), idx.end(), 0);
-    auto key = [&](size_t r, int q) { return src[r * (W + TW) + (typ_first ? TW : 0) + q]; };
-    std::sort(idx.begin(), idx.end(), [&](size_t a, size_t b) {
-        for (int q = 0; q < W; ++q)
-            if (key(a, q) != key(b, q)) return key(a, q) < key(b, q);
-        for (int q = 0; q < TW; ++q) {
-            int ta = src[a * (W + TW) + (typ_first ? q : W + q)], tb = src[b * (W + TW) + (typ_first ? q : W + q)];
-            if (ta != tb) return ta < tb;
-        }
-        return false;
-    });
-    for (size_t k = 0; k < rows; ++k) {
-        size_t r = idx[k];
-        for (int q = 0; q < W; ++q) tup[k * W + q] = key(r, q);
-        for (int q = 0; q < TW; ++q) typ[k * TW + q] = src[r * (W + TW) + (typ_first ? q : W + q)];
-    }
+    std::sort(idx.begin(), idx.end(), [&](size_t a, size_t b) { return less(p + a * S, p + b * S); });
+    for (size_t k = 0; k < rows; ++k) put(k, p + idx[k] * S);
 }
 
 // ------------------------------------------------------------------------------------
@@ -908,7 +890,7 @@ int db_generate_angles_dihedrals(db_ctx* c) {
     HIPCHK(c, hipMemcpyAsync(&ext(c).pin->err, c->err_d, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipGetLastError());
-    ext(c).host_valid = false;
+    host_stale(c);
     return check_device_error(c);
 }
 
@@ -1371,7 +1353,7 @@ int db_step(db_ctx* c, int64_t nsteps) {
             if (rc) return rc;
         }
         if (sweep_due) record_sweep_stats(c);
-        X.host_valid = false;
+        host_stale(c);
         rc = check_device_error(c);
         if (rc) return rc;
         // bound: how far any bead may be from where the list was built, at the
@@ -1452,7 +1434,7 @@ int db_sweep_now(db_ctx* c) {
     HIPCHK(c, hipGetLastError());
     record_sweep_stats(c);
     c->swept_step = c->step;
-    ext(c).host_valid = false;
+    host_stale(c);
     return check_device_error(c);
 }
 
@@ -1461,7 +1443,7 @@ int db_forces(db_ctx* c, double* f, int on_device) {
     int rc = ready(c);
     if (rc) return rc;
     rebuild(c, false);
-    double* d = on_device ? f : (double*)gather_scratch(c, 24 * (size_t)c->n);
+    double* d = on_device ? f : (double*)gather_scratch(c);
     launch_forces(c, d);
     if (!on_device && c->n) HIPCHK(c, hipMemcpyAsync(f, d, 24 * (size_t)c->n, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipMemcpyAsync(&ext(c).pin->err, c->err_d, sizeof(int), hipMemcpyDeviceToHost, c->stream));
@@ -1520,7 +1502,7 @@ int db_get_state(db_ctx* c, double* x, double* v, int on_device) {
         return DB_OK;
     }
     if (n == 0) return DB_OK;
-    double* d = (double*)gather_scratch(c, 48 * n);
+    double* d = (double*)gather_scratch(c);
     hipLaunchKernelGGL(k_gather_state, dim3((unsigned)((n + DB_BLOCK - 1) / DB_BLOCK)), dim3(DB_BLOCK), 0, c->stream,
                        (int)n, c->bank[c->cur], d, d + 3 * n);
     hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
@@ -1534,20 +1516,17 @@ int db_get_state(db_ctx* c, double* x, double* v, int on_device) {
 int db_topology_counts(db_ctx* c, int64_t* nb, int64_t* na, int64_t* nd) {
     if (!c) return DB_EINVAL;
     db_host_ext& X = ext(c);
-    if (X.host_valid) {
-        if (nb) *nb = (int64_t)(X.h.bonds.size() / 4);
-        if (na) *na = (int64_t)(X.h.ang.size() / 4);
-        if (nd) *nd = (int64_t)(X.h.dih.size() / 5);
-        return DB_OK;
-    }
-    int rc = download_system(c);
+    int rc = download_topology(c);
     if (rc) return rc;
-    return db_topology_counts(c, nb, na, nd);
+    if (nb) *nb = (int64_t)(X.h.bonds.size() / 4);
+    if (na) *na = (int64_t)(X.h.ang.size() / 4);
+    if (nd) *nd = (int64_t)(X.h.dih.size() / 5);
+    return DB_OK;
 }
 
 int db_get_bonds(db_ctx* c, int32_t* ij, int32_t* tij, int32_t* tji) {
     if (!c) return DB_EINVAL;
-    int rc = download_system(c);
+    int rc = download_topology(c);
     if (rc) return rc;
     const std::vector<int32_t>& b = ext(c).h.bonds;
     const size_t m = b.size() / 4;
@@ -1562,7 +1541,7 @@ int db_get_bonds(db_ctx* c, int32_t* ij, int32_t* tij, int32_t* tji) {
 
 int db_get_angles(db_ctx* c, int32_t* abc, int32_t* type) {
     if (!c) return DB_EINVAL;
-    int rc = download_system(c);
+    int rc = download_topology(c);
     if (rc) return rc;
     sorted_copy<3, 1>(ext(c).h.ang, abc, type, 1);
     return DB_OK;
@@ -1570,7 +1549,7 @@ int db_get_angles(db_ctx* c, int32_t* abc, int32_t* type) {
 
 int db_get_dihedrals(db_ctx* c, int32_t* abcd, int32_t* type) {
     if (!c) return DB_EINVAL;
-    int rc = download_system(c);
+    int rc = download_topology(c);
     if (rc) return rc;
     sorted_copy<4, 1>(ext(c).h.dih, abcd, type, 1);
     return DB_OK;
@@ -1777,7 +1756,7 @@ int db_checkpoint_load(db_ctx* c, const void* buf, size_t bytes) {
     c->du_last = h.du_last;
     c->du_cum = h.du_cum;
     X.dev_valid = true;
-    X.host_valid = false;
+    host_stale(c);
     X.dev_error = 0;
     X.pin->err = 0;
     return DB_OK;
@@ -1967,7 +1946,7 @@ int db_batch_create(db_ctx** out, db_ctx* const* reps, int32_t nrep, void* strea
         if (q->hp.has_ext) return DB_EINVAL;   // external forces are tied to one system's bead ids
         db_host_ext& X = ext(q);
         if (X.dev_error) return DB_ESTATE;
-        if (X.dev_valid && !X.host_valid) {
+        if (X.dev_valid) {
             int rc = download_system(q);
             if (rc) return rc;
         }
@@ -2045,7 +2024,7 @@ int db_batch_get_state(db_ctx* c, int32_t r, double* x, double* v, int on_device
         return DB_OK;
     }
     if (nr == 0) return DB_OK;
-    double* d = (double*)gather_scratch(c, 48 * n);
+    double* d = (double*)gather_scratch(c);
     hipLaunchKernelGGL(k_gather_state, dim3((unsigned)((n + DB_BLOCK - 1) / DB_BLOCK)), dim3(DB_BLOCK), 0, c->stream,
                        (int)n, c->bank[c->cur], d, d + 3 * n);
     hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;

@@ -346,7 +346,9 @@ void launch_energy(db_ctx* c, double* out6_device, double* partials = nullptr);
 // kernels_sweep.hip
 void launch_sweep(db_ctx* c, int64_t step);
 void launch_generate_all(db_ctx* c);
-void launch_count_topology(db_ctx* c, int64_t* nb_na_nd_device);
-void launch_gather_topology(db_ctx* c, int kind, int32_t* out_tuples, int32_t* out_types, int64_t count);
+// sorted topology lists: offsets of every bead's entries (buf: 3 (n + 1) ints) and
+// the totals of bonds, angles and dihedrals (mapped host words), then the rows
+void launch_owned_offsets(db_ctx* c, int* buf, int* totals);
+void launch_write_owned(db_ctx* c, const int* off, int* bonds, int* angles, int* dihedrals);
 
 }  // namespace db

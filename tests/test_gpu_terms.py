@@ -102,3 +102,31 @@ def test_forces_report_a_crowded_bead():
     with pytest.raises(pk.DynBondError) as e:
         g.forces()
     assert e.value.code == pk.DB_ECAPACITY
+
+
+@pytest.mark.parametrize("n", [4, 255, 256, 1025])
+def test_topology_lists_come_back_sorted(n):
+    """Lists read from the device are those set, canonical and sorted: beads with many entries, equal paths under
+    several types, a ragged last workgroup."""
+    import paper_1108_4214_amd as pk
+    rng = np.random.default_rng(n)
+    k = np.arange(n - 3)
+    s = synth.System(L=20.0, x=rng.uniform(0, 20.0, size=(n, 3)), v=np.zeros((n, 3)), type=np.ones(n, dtype=np.int32),
+                     reactive=np.zeros(n, dtype=np.uint8), bonds=np.zeros((0, 4), dtype=np.int32))
+    perm = rng.permutation(n)
+    bonds = np.column_stack([perm[k], perm[k + 1], 1 + k % 5, 1 + k % 7])
+    angles = np.concatenate([np.column_stack([1 + (k + r) % 3, perm[k], perm[k + 1], perm[k + 2]]) for r in (0, 1)])
+    dihedrals = np.concatenate([np.column_stack([1 + (k + r) % 4, perm[k], perm[k + 1], perm[k + 2], perm[k + 3]])
+                                for r in (0, 2)])
+    for rows in (bonds, angles, dihedrals):
+        rng.shuffle(rows)
+    s = dataclasses.replace(s, bonds=bonds.astype(np.int32), angles=angles.astype(np.int32),
+                            dihedrals=dihedrals.astype(np.int32))
+    g = pk.System(s.n, s.L, 3).configure(s, synth.ForceField(eps=0.0, gamma=0.0), synth.RuleSet(every=0))
+    g.step(9)
+    b = np.where((bonds[:, 0] > bonds[:, 1])[:, None], bonds[:, [1, 0, 3, 2]], bonds)
+    a = np.where((angles[:, 1] > angles[:, 3])[:, None], angles[:, [0, 3, 2, 1]], angles)
+    d = np.where((dihedrals[:, 1] > dihedrals[:, 4])[:, None], dihedrals[:, [0, 4, 3, 2, 1]], dihedrals)
+    assert np.array_equal(g.bonds(), b[np.lexsort(b.T[::-1])])
+    assert np.array_equal(g.angles(), a[np.lexsort((a[:, 0], a[:, 3], a[:, 2], a[:, 1]))])
+    assert np.array_equal(g.dihedrals(), d[np.lexsort((d[:, 0], d[:, 4], d[:, 3], d[:, 2], d[:, 1]))])
