@@ -68,7 +68,7 @@ typedef struct {
     int64_t sweeps;          /* sweeps performed */
     int64_t steps;           /* current step counter */
     int64_t rebuilds;        /* cell-list rebuilds */
-    int64_t rollbacks;       /* blocks re-run because beads moved further than the skin */
+    int64_t rollbacks;       /* blocks that ended early because beads had moved further than the skin allows */
     /* topology-energy ledger (appendix step 9 statistics, extended): change of the
      * potential energy (pair + bond + angle + dihedral, FP64) across the last sweep
      * at fixed positions, and its sum over all sweeps; 0 while not tracked

@@ -6,15 +6,16 @@
 // list (and, every `permute_every` blocks, a reordering of all per-bead state
 // into cell order), runs the sweep if the block's first step is a sweep step,
 // and then runs up to `rebuild_interval` fused step kernels without rebuilding.
-// Each step kernel records the largest speed; after the block the host bounds
-// the largest displacement by the sum of dt * max speed.  If that bound exceeds
-// half the skin (list cutoff minus pair cutoff) some pair could have been
-// missed, so the block's positions and velocities are restored and the block is
-// re-run with a fresh list at every step.  The interval adapts to the speeds
-// seen.  With DPD the pair friction decorrelates velocities within a few steps,
-// so the motion is diffusive and the speed bound far too cautious: there the
-// step kernels record the largest displacement from the block's first position
-// itself, which is the exact test, and the interval follows its growth.
+// Each step kernel records the largest speed, and the sum of dt * max speed bounds
+// the largest displacement.  Past half the skin (list cutoff minus pair cutoff) some
+// pair could be missed: a step kernel whose input is beyond that bound stores
+// nothing, so the block ends there by itself, the host sees where from the block's
+// report, and the next block starts from that step with a fresh list.  The interval
+// adapts to the speeds seen, so that this is rare.  With DPD the pair friction
+// decorrelates velocities within a few steps, so the motion is diffusive and the
+// speed bound far too cautious: there the step kernels record the largest
+// displacement from the list's positions itself, which is the exact test, and the
+// interval follows its growth.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -43,7 +44,7 @@ static std::mutex noalloc_mutex;
 
 namespace {
 
-const int kMaxBlock = 64;
+const int kMaxBlock = DB_MAX_BLOCK;
 const double kSkinDefault = 0.55;
 // DPD at density 3 with the pair friction of the paper moves some bead far enough
 // to need a new list after about every step whatever the skin, so the thinnest
@@ -171,8 +172,12 @@ static size_t layout(db_ctx* c, bool assign) {
     put(c->vnext, 24 * n);
     put(c->xref, 32 * n);
     put(c->fext, 24 * n);
-    put(c->xsave, 32 * n);
-    put(c->vsave, 24 * n);
+    // two slots of at least 256 bytes each (their sizes are part of the layout that
+    // checkpoints record) hold the bounds of a block
+    static_assert(8 * DB_MAX_BLOCK <= 512, "the bounds fit the two smallest slots");
+    put(c->gate_bound, 32 * n);
+    double* rest = nullptr;
+    put(rest, 24 * n);
     SweepBuf& S = c->sw;
     put(S.nomC, 4 * n);
     put(S.ruleC, n);
@@ -218,7 +223,8 @@ static size_t layout(db_ctx* c, bool assign) {
     put(c->tiles.itemD, 8 * tcap * DB_CAPD);
     put(c->tiles.nitems, 4 * tcap);
     put(c->err_d, 64);
-    put(c->step_dev, 64);
+    static_assert(sizeof(BlockBase) <= 64, "slot of the replayed block");
+    put(c->base_dev, 64);
     put(c->vmax2, 4 * (size_t)kMaxBlock * DB_VMAX_SPREAD);
     put(c->red, 8 * 6 * ((n + DB_BLOCK - 1) / DB_BLOCK + 1));
     put(c->ledger_d, 8 * 16);
@@ -618,9 +624,9 @@ static int check_device_error(db_ctx* c) {
 }
 
 // cells_ready: the cell list was already built for the current positions
-static void rebuild(db_ctx* c, bool permute, bool save = false, bool cells_ready = false) {
+static void rebuild(db_ctx* c, bool permute, bool cells_ready = false) {
     if (!cells_ready) launch_build_cells(c);
-    if (permute) launch_permute(c, save);
+    if (permute) launch_permute(c);
     c->rebuilds++;
 }
 
@@ -674,8 +680,8 @@ int db_create(db_ctx** out, int32_t n, double L, uint64_t seed, int precision, v
     c->precision = precision;
     c->stream = (hipStream_t)stream;
     c->device = -1;
-    c->step_dev = nullptr;
-    c->step_base_d = nullptr;
+    c->base_dev = nullptr;
+    c->base_captured = nullptr;
     c->use_graph = false;
     c->graphs = new std::vector<GraphEntry>();
     c->cap_stream = nullptr;
@@ -1162,7 +1168,7 @@ static int run_sweep(db_ctx* c, int64_t step) {
     return DB_OK;
 }
 
-static int launch_timed_step(db_ctx* c, int64_t step, int slot, bool save) {
+static int launch_timed_step(db_ctx* c, int64_t step, int q, double d0, double limit) {
     if (c->profile && (c->profile_count++ % c->profile_every) == 0) {
         if ((size_t)c->ev_used + 2 > c->ev_pool.size()) {
             for (int k = 0; k < 2 * kMaxBlock; ++k) {
@@ -1172,11 +1178,11 @@ static int launch_timed_step(db_ctx* c, int64_t step, int slot, bool save) {
             }
         }
         HIPCHK(c, hipEventRecord(c->ev_pool[c->ev_used], c->stream));
-        launch_step(c, step, slot, save);
+        launch_step(c, step, q, d0, limit);
         HIPCHK(c, hipEventRecord(c->ev_pool[c->ev_used + 1], c->stream));
         c->ev_used += 2;
     } else {
-        launch_step(c, step, slot, save);
+        launch_step(c, step, q, d0, limit);
     }
     return DB_OK;
 }
@@ -1192,19 +1198,19 @@ static int harvest_events(db_ctx* c) {
     return DB_OK;
 }
 
-__global__ void k_set_step(int64_t* __restrict__ p, int64_t v) {
+__global__ void k_set_base(BlockBase* __restrict__ p, BlockBase v) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
 }
 
 // The len step launches of a block from a captured graph: captured once per
-// (length, rollback copy, buffers, kernel) and replayed with the block's first step
+// (length, buffers, kernel) and replayed with the block's first step and bounds
 // written to the device beforehand.  Only kernel nodes are captured.
-static int run_steps_graph(db_ctx* c, int64_t k0, int len, bool save) {
+static int run_steps_graph(db_ctx* c, int64_t k0, int len, double d0, double limit) {
     Bank& B = c->bank[c->cur];
     const bool tiled = tiles_enabled(c) && c->tiles_valid && c->regions_valid;
     GraphEntry* hit = nullptr;
     for (GraphEntry& e : *c->graphs)
-        if (e.len == len && e.save == save && e.tiled == tiled && e.cur == c->cur && e.x == B.x &&
+        if (e.len == len && e.tiled == tiled && e.cur == c->cur && e.x == B.x &&
             e.xnext == c->xnext && e.v == B.v && e.vnext == c->vnext) {
             hit = &e;
             break;
@@ -1219,7 +1225,6 @@ static int run_steps_graph(db_ctx* c, int64_t k0, int len, bool save) {
         }
         GraphEntry e{};
         e.len = len;
-        e.save = save;
         e.tiled = tiled;
         e.cur = c->cur;
         e.x = B.x;
@@ -1235,13 +1240,13 @@ static int run_steps_graph(db_ctx* c, int64_t k0, int len, bool save) {
         double* v0 = B.v;
         double* vn0 = c->vnext;
         c->stream = cap;
-        c->step_base_d = c->step_dev;
+        c->base_captured = c->base_dev;
         hipError_t st = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
         if (st == hipSuccess) {
-            for (int q = 0; q < len; ++q) launch_step(c, q, q, save && q == 0);
+            for (int q = 0; q < len; ++q) launch_step(c, q, q, 0.0, 0.0);
             st = hipStreamEndCapture(cap, &e.graph);
         }
-        c->step_base_d = nullptr;
+        c->base_captured = nullptr;
         c->stream = run;
         e.x_after = B.x;
         e.xnext_after = c->xnext;
@@ -1256,7 +1261,7 @@ static int run_steps_graph(db_ctx* c, int64_t k0, int len, bool save) {
         c->graphs->push_back(e);
         hit = &c->graphs->back();
     }
-    hipLaunchKernelGGL(k_set_step, dim3(1), dim3(1), 0, c->stream, c->step_dev, k0);
+    hipLaunchKernelGGL(k_set_base, dim3(1), dim3(1), 0, c->stream, c->base_dev, BlockBase{k0, d0, limit});
     HIPCHK(c, hipGraphLaunch(hit->exec, c->stream));
     B.x = (double4*)hit->x_after;
     c->xnext = (double4*)hit->xnext_after;
@@ -1309,18 +1314,15 @@ int db_step(db_ctx* c, int64_t nsteps) {
         const bool reuse = reuse_ok && sweep_due && c->list_valid && c->list_disp + 1.25 * grow <= skin &&
                            patch_cut <= reuse_cut_max;
         const double d0 = reuse ? c->list_disp : 0.0;   // bound at the block's input
-        bool permute = false;
-        const bool guard = std::isfinite(skin) && len > 1;
         if (reuse) {
-            rebuild(c, false, false, cells_ready);   // current cells for the sweep and the patched lists
+            rebuild(c, false, cells_ready);   // current cells for the sweep and the patched lists
             rc = run_sweep(c, k0);
             if (rc) return rc;
             c->swept_step = k0;
             launch_patch_nlist(c, patch_cut);
             c->patches++;
         } else {
-            permute = (c->rebuild_count++ % c->permute_every) == 0;
-            rebuild(c, permute, guard, cells_ready);
+            rebuild(c, (c->rebuild_count++ % c->permute_every) == 0, cells_ready);
             if (sweep_due) {
                 rc = run_sweep(c, k0);
                 if (rc) return rc;
@@ -1328,14 +1330,12 @@ int db_step(db_ctx* c, int64_t nsteps) {
             }
             launch_build_nlist(c);   // after the sweep: exclusions follow the new bonds
         }
-        // the block's input state is kept for a re-run: by the reorder, or else by
-        // the first step kernel of the block
         if (c->use_graph && !c->profile) {
-            rc = run_steps_graph(c, k0, (int)len, guard && !permute);
+            rc = run_steps_graph(c, k0, (int)len, d0, skin);
             if (rc) return rc;
         } else {
             for (int64_t q = 0; q < len; ++q) {
-                rc = launch_timed_step(c, k0 + q, (int)q, guard && !permute && q == 0);
+                rc = launch_timed_step(c, k0 + q, (int)q, d0, skin);
                 if (rc) return rc;
             }
         }
@@ -1343,7 +1343,7 @@ int db_step(db_ctx* c, int64_t nsteps) {
                            sweep_due ? 1 : 0, X.pin_dev);
         HIPCHK(c, hipEventRecord(c->ev_report, s));
         // the next block's cell list (it needs only this block's positions) is built
-        // while the host waits for the report; a re-run of this block discards it
+        // while the host waits for the report; a block cut short discards it
         cells_ready = nsteps > len;
         if (cells_ready) launch_build_cells(c);
         HIPCHK(c, hipEventSynchronize(c->ev_report));
@@ -1356,41 +1356,24 @@ int db_step(db_ctx* c, int64_t nsteps) {
         host_stale(c);
         rc = check_device_error(c);
         if (rc) return rc;
-        // bound: how far any bead may be from where the list was built, at the
-        // input of the block's last step; dlast: the same at the block's output
-        double bound = d0, vmax = 0.0, dlast = d0;
-        for (int64_t q = 0; q < len; ++q) {
-            double v = std::sqrt((double)pin->vmax2[q]);
-            if (track) {   // measured from the full build's positions
-                if (q + 1 < len) bound = std::max(bound, v);
-                dlast = v;
-            } else {
-                vmax = std::max(vmax, v);
-                if (q + 1 < len) bound += dt * v;
-                dlast += dt * v;
-            }
+        // dlast: the bound on how far any bead is from where the list was built, after
+        // the steps so far, by the gate's own arithmetic; the block ended at the first
+        // step whose input was beyond the limit
+        double vmax = 0.0, dlast = d0;
+        int64_t done = 0;
+        for (; done < len; ++done) {
+            if (done > 0 && !(dlast <= skin)) break;
+            const double v = std::sqrt((double)pin->vmax2[done]);
+            vmax = std::max(vmax, v);
+            dlast = track ? std::max(dlast, v) : dlast + dt * v;
         }
-        if (guard && bound > skin) {
-            // some bead may have left the reach of the cell list: redo with a fresh list every step
+        const bool cut = done < len;
+        if (cut) {
             c->rollbacks++;
-            Bank& Bc = c->bank[c->cur];
-            cells_ready = false;
-            HIPCHK(c, hipMemcpyAsync(Bc.x, c->xsave, 32 * (size_t)c->n, hipMemcpyDeviceToDevice, s));
-            HIPCHK(c, hipMemcpyAsync(Bc.v, c->vsave, 24 * (size_t)c->n, hipMemcpyDeviceToDevice, s));
-            for (int64_t q = 0; q < len; ++q) {
-                rebuild(c, false);
-                launch_build_nlist(c);
-                launch_step(c, k0 + q, 0);
-            }
-            // the re-run steps wrote their maxima into the first word row: clear it
-            launch_fill_int((int*)c->vmax2, 0, DB_VMAX_SPREAD, s);
-            HIPCHK(c, hipMemcpyAsync(&pin->err, c->err_d, sizeof(int), hipMemcpyDeviceToHost, s));
-            HIPCHK(c, hipStreamSynchronize(s));
-            rc = check_device_error(c);
-            if (rc) return rc;
-            c->rebuild_interval = std::max<int>(1, (int)(len / 2));
-            c->list_valid = false;
-        } else if (reuse) {
+            cells_ready = false;   // built from the buffers as if every step had run
+            if ((len - done) & 1) swap_step_buffers(c);
+        }
+        if (reuse && !cut) {
             // the interval follows full builds only
             c->list_disp = dlast;
             c->disp_rate = std::max(0.0, dlast - d0) / (double)len;
@@ -1398,22 +1381,28 @@ int db_step(db_ctx* c, int64_t nsteps) {
             // extrapolate the largest displacement linearly in time from the block's
             // end (exact for ballistic motion, cautious for diffusive motion, so the
             // interval keeps growing while the test passes)
-            int want = dlast > 0 ? (int)std::floor(0.8 * skin * (double)len / dlast) + 1 : kMaxBlock;
+            int want = dlast > 0 ? (int)std::floor(0.8 * skin * (double)done / dlast) + 1 : kMaxBlock;
             c->rebuild_interval = std::max(1, std::min(kMaxBlock, want));
         } else if (std::isfinite(skin) && vmax > 0) {
-            int want = (int)std::floor(0.8 * skin / (dt * vmax));
+            // as many steps as the bound admits at the speeds just seen: the last
+            // step's input is want - 1 steps from the list.  A step too many is one
+            // launch that stores nothing; a step too few may split the steps between
+            // two sweeps into two blocks, each with its own list
+            int want = (int)std::floor(1.0 + skin / (1.02 * dt * vmax));
             c->rebuild_interval = std::max(1, std::min(kMaxBlock, want));
         } else if (!std::isfinite(skin)) {
             c->rebuild_interval = kMaxBlock;
         }
-        if (!reuse && !(guard && bound > skin)) {
+        if (cut) {
+            c->list_valid = false;
+        } else if (!reuse) {
             c->list_valid = true;
             c->list_disp = dlast;
             c->disp_rate = dlast / (double)len;
         }
         c->vmax_est = vmax;
-        c->step += len;
-        nsteps -= len;
+        c->step += done;
+        nsteps -= done;
     }
     return DB_OK;
 }

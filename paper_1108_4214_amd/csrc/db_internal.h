@@ -19,6 +19,7 @@
 #define DB_MAXU 8            // bonded halo entries per bead (codes hold 3-bit indices)
 #define DB_HALO_OVF 255      // halo marker: more than DB_MAXU distinct bonded partners
 #define DB_VMAX_SPREAD 64    // words per step over which the speed maxima are spread
+#define DB_MAX_BLOCK 64      // steps of a block
 #define DB_RCAP 768          // region entries a tile of the step kernel stages in LDS
 #define DB_CAPA 448          // angle work items of a tile
 #define DB_CAPD 224          // dihedral work items of a tile
@@ -196,12 +197,32 @@ struct Tiles {
     uint32_t* nitems; // [ntile] angle items | dihedral items << 16; 0xFFFFFFFF: no items (per-bead terms)
 };
 
+// The validity gate of a block's step launches.  A step may use the block's Verlet
+// list while the bound on any bead's displacement since the list's full build, at
+// the step's input, is within half the skin.  The launches of a block are issued
+// ahead of the speeds that decide this, so each step kernel forms the bound itself,
+// from the bound of the step before and that step's maxima, and past the limit it
+// stores nothing: a block ends by itself at its last valid step, nothing has to be
+// restored and no input state is kept.
+struct Gate {
+    unsigned int* vmax2;   // the block's maxima, DB_VMAX_SPREAD words per step
+    double* bound;         // [DB_MAX_BLOCK] the bound at each step's input
+    int q;                 // the step's place in the block
+    double d0, limit;      // the bound at the block's input, and its limit
+};
+
+// what a replayed graph reads from the device instead of its captured arguments
+struct BlockBase {
+    int64_t step;          // the block's first step
+    double d0, limit;      // as in Gate
+};
+
 // The step launches of one block captured as a HIP graph.  The key is everything
 // the captured arguments depend on; the launches swap the position (and velocity)
 // buffers, whose state after the block is kept for replays.
 struct GraphEntry {
     int len;
-    bool save, tiled;
+    bool tiled;
     int cur;
     const void *x, *xnext, *v, *vnext;             // buffers before the block
     const void *x_after, *xnext_after, *v_after, *vnext_after;
@@ -250,8 +271,7 @@ struct db_ctx {
     double4* xref;       // positions at the last full Verlet-list build (slot order)
     double* vnext;       // double buffer of velocities (DPD: the step reads neighbour velocities)
     double* fext;        // [3n] external force by global bead id
-    double4* xsave;      // state at block start (rollback)
-    double* vsave;
+    double* gate_bound;  // [DB_MAX_BLOCK] displacement bounds of the current block (Gate)
     db::SweepBuf sw;
     db::Cells cells;
     db::NList nlist;
@@ -286,8 +306,8 @@ struct db_ctx {
     bool ledger;         // track the topology-energy ledger
     double du_last, du_cum;
     int64_t* cnt64;      // small device counters
-    int64_t* step_dev;   // the first step of the block being replayed from a graph
-    int64_t* step_base_d;   // step_dev while step launches are captured, else nullptr
+    db::BlockBase* base_dev;      // the block being replayed from a graph
+    db::BlockBase* base_captured; // base_dev while step launches are captured, else nullptr
     bool use_graph;      // blocks' step launches are replayed from captured HIP graphs
     std::vector<db::GraphEntry>* graphs;   // captured blocks, keyed by length and buffers
     hipStream_t cap_stream;   // capture stream when the handle's stream is the null stream
@@ -297,7 +317,7 @@ struct db_ctx {
     // topology on the host side until uploaded
     bool have_state, have_topology;
     int64_t step, swept_step;
-    int64_t rebuilds, rollbacks, sweeps;
+    int64_t rebuilds, rollbacks, sweeps;   // rollbacks: blocks ended before their last step by the gate
     int64_t stat_last[8], stat_cum[8];
     int rebuild_interval;     // steps between rebuilds inside a block
     int permute_every;        // permute the state every k-th rebuild
@@ -322,8 +342,7 @@ namespace db {
 // kernels_cells.hip
 void launch_fill_int(int* p, int value, size_t count, hipStream_t s);
 void launch_build_cells(db_ctx* c);                  // bin + scan + scatter + in-cell sort
-void launch_permute(db_ctx* c, bool save);           // reorder all per-bead state by the cell list
-                                                     // (save: also copy x, v to the rollback buffers)
+void launch_permute(db_ctx* c);                      // reorder all per-bead state by the cell list
 bool tiles_enabled(const db_ctx* c);                 // the step kernel runs on brick tiles
 void launch_exclusive_scan(int* data, int count, int* total_out, int* blocksum, hipStream_t s);
 // out[0..count) = exclusive prefix sums of in (in != out), out[count] = the total
@@ -337,8 +356,11 @@ void launch_regions(db_ctx* c);                      // tile regions and 16-bit 
 // Verlet lists of the beads whose exclusions the last sweep changed, with cutoff
 // cut (the list cutoff plus twice the displacement since the full build)
 void launch_patch_nlist(db_ctx* c, double cut);
-// save: keep the input x, v (the block's input state, for a re-run)
-void launch_step(db_ctx* c, int64_t step, int slot_in_block, bool save = false);
+// the step at place q of a block whose displacement bound starts at d0 and may reach
+// limit; exchanges the position (and velocity) buffers, also where the gate is shut
+void launch_step(db_ctx* c, int64_t step, int q, double d0, double limit);
+// exchanges the buffers back after an odd number of launches that stored nothing
+void swap_step_buffers(db_ctx* c);
 void launch_forces(db_ctx* c, double* f_gid_order);
 // partials: 6 doubles per workgroup of the energy kernel (nullptr: the arena's own)
 void launch_energy(db_ctx* c, double* out6_device, double* partials = nullptr);

@@ -407,7 +407,6 @@ __global__ __launch_bounds__(DB_BLOCK) void k_tile_starts(int n, int nc, int bB,
 
 __global__ __launch_bounds__(DB_BLOCK) void k_permute(int n, Bank src, Bank dst, int* __restrict__ list,
                                                        const int* __restrict__ newslot, int* __restrict__ slot_of_gid,
-                                                       double4* __restrict__ xsave, double* __restrict__ vsave,
                                                        float4* __restrict__ xs) {
     int s = blockIdx.x * DB_BLOCK + threadIdx.x;   // position in cell order
     if (s >= n) return;
@@ -419,12 +418,6 @@ __global__ __launch_bounds__(DB_BLOCK) void k_permute(int n, Bank src, Bank dst,
     dst.v[d] = vx;
     dst.v[n + d] = vy;
     dst.v[2 * n + d] = vz;
-    if (xsave) {   // copy kept for re-running the block
-        xsave[d] = x;
-        vsave[d] = vx;
-        vsave[n + d] = vy;
-        vsave[2 * n + d] = vz;
-    }
     slot_of_gid[meta_gid(x)] = d;
     int nb = src.nb[o];
     dst.nb[d] = (uint8_t)nb;
@@ -449,7 +442,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_permute(int n, Bank src, Bank dst,
     xs[s].w = xs_word(d, meta_word(x));
 }
 
-void launch_permute(db_ctx* c, bool save) {
+void launch_permute(db_ctx* c) {
     const int n = c->n;
     if (n == 0) return;
     hipStream_t s = c->stream;
@@ -484,8 +477,7 @@ void launch_permute(db_ctx* c, bool save) {
         hipLaunchKernelGGL(k_newslot, dim3(nb), dim3(DB_BLOCK), 0, s, n, c->cells.list, newslot);
     }
     hipLaunchKernelGGL(k_permute, dim3(nb), dim3(DB_BLOCK), 0, s, n, c->bank[c->cur], c->bank[1 - c->cur],
-                       c->cells.list, newslot, c->slot_of_gid, save ? c->xsave : (double4*)nullptr,
-                       save ? c->vsave : (double*)nullptr, c->cells.xs);
+                       c->cells.list, newslot, c->slot_of_gid, c->cells.xs);
     c->cur = 1 - c->cur;
     c->halo_force = true;
     c->tiles_valid = tiled;

@@ -1076,15 +1076,40 @@ __device__ __forceinline__ double wave_max(double v) {
 }
 
 // Replayed from a HIP graph, a step kernel's arguments are those of its capture:
-// the block's first step is then read from the device word step_base (step is the
-// offset within the block) and the single system's thermostat amplitudes are
-// formed here from the temperature schedule, with the host's arithmetic.
-__device__ __forceinline__ void step_amplitudes(const Params& P, const int64_t* step_base, int64_t& step,
-                                                double& pref, double& dsig) {
-    step += *step_base;
+// the block's first step and its displacement bounds are then read from the device
+// (step is the offset within the block) and the single system's thermostat
+// amplitudes are formed here from the temperature schedule, with the host's
+// arithmetic.
+__device__ __forceinline__ void step_amplitudes(const Params& P, const BlockBase* base, int64_t& step, double& pref,
+                                                double& dsig, Gate& G) {
+    step += base->step;
+    G.d0 = base->d0;
+    G.limit = base->limit;
     const double T = box_temperature(P.box, step);
     pref = P.gamma != 0.0 ? sqrt(24.0 * P.gamma * T / P.dt) : 0.0;
     dsig = (P.pair_style == PAIR_DPD && P.dpd_gamma != 0.0) ? sqrt(2.0 * T * P.dpd_gamma) / sqrt(P.dt) : 0.0;
+}
+
+// Whether the block's list holds for this step: the bound on any bead's displacement
+// at its input, which the host forms alike from the block's report.  The bound
+// grows by dt times the largest speed of each step, or (TRACK: DPD) is the largest
+// displacement measured after the steps so far.  Every wave forms it (the step
+// before has ended, so its words are final); the first one records it for the next
+// step.
+template <bool TRACK>
+__device__ __forceinline__ bool gate_open(const Params& P, const Gate& G) {
+    double b = G.d0;
+    if (G.q > 0) {
+        float m = __uint_as_float(G.vmax2[(size_t)(G.q - 1) * DB_VMAX_SPREAD + (threadIdx.x & 63)]);
+        static_assert(DB_VMAX_SPREAD == 64, "one word per lane");
+        const double before = G.bound[G.q - 1];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+        const double v = sqrt((double)m);
+        b = TRACK ? fmax(before, v) : before + P.dt * v;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) G.bound[G.q] = b;
+    return b <= G.limit;
 }
 
 // pref: sqrt(24 gamma T / dt) of a single system (from the host), dsig: the DPD
@@ -1100,11 +1125,12 @@ __device__ __forceinline__ void step_amplitudes(const Params& P, const int64_t* 
 template <typename R, bool BATCH, int PAIR>
 __global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 8 ? 3 : (PAIR == PAIR_WCA ? 6 : 5))
 void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __restrict__ xout, double* vout,
-            int64_t step, double pref, double dsig, unsigned int* __restrict__ vmax2_slot, int* __restrict__ err, double4* __restrict__ xsave, double* __restrict__ vsave,
-            const double4* __restrict__ xref, const int64_t* __restrict__ step_base) {
+            int64_t step, double pref, double dsig, Gate G, int* __restrict__ err, const double4* __restrict__ xref,
+            const BlockBase* __restrict__ base) {
     const Params& P = *Pp;
     const int n = P.n;
-    if (step_base) step_amplitudes(P, step_base, step, pref, dsig);
+    if (base) step_amplitudes(P, base, step, pref, dsig, G);
+    const bool open = gate_open<PAIR == PAIR_DPD>(P, G);
     __shared__ Coef<R> C;
     __shared__ R hs[3][DB_MAXU][DB_BLOCK];
     load_coef<R>(P, C);
@@ -1159,12 +1185,6 @@ void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __
             vx = B.v[i];
             vy = B.v[n + i];
             vz = B.v[2 * n + i];
-            if (xsave) {   // first step of a block: keep its input state for a re-run
-                xsave[i] = xi;
-                vsave[i] = vx;
-                vsave[n + i] = vy;
-                vsave[2 * n + i] = vz;
-            }
             double Fx = a.fx, Fy = a.fy, Fz = a.fz;
             if (P.gamma != 0.0) {
                 if (BATCH) pref = sqrt(24.0 * P.gamma * box_temperature(X, step) / P.dt);
@@ -1187,6 +1207,7 @@ void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __
                 xo.y = wrap1(nyp, X.L);
                 xo.z = wrap1(nzp, X.L);
                 xo.w = xi.w;
+                if (!open) return;   // past the list's validity: nothing of this step is kept
                 bool bad = !(xo.x >= 0.0 && xo.x < X.L && xo.y >= 0.0 && xo.y < X.L && xo.z >= 0.0 && xo.z < X.L);
                 if (bad) atomicOr(err, ERR_NONFINITE);
                 if (PAIR == PAIR_DPD) {
@@ -1206,6 +1227,7 @@ void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __
     }
     // largest speed of the workgroup; one atomic per workgroup, spread over 64 words
     // so that the workgroups of one step do not serialise on one address
+    if (!open) return;
     __shared__ float wmax[DB_BLOCK / 64];
     double v2 = wave_max(m2);
     if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = (float)v2 * 1.0001f;
@@ -1213,7 +1235,7 @@ void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __
     if (threadIdx.x == 0) {
         float m = wmax[0];
         for (int w = 1; w < DB_BLOCK / 64; ++w) m = fmaxf(m, wmax[w]);
-        atomicMax(vmax2_slot + (blockIdx.x & (DB_VMAX_SPREAD - 1)), __float_as_uint(m));
+        atomicMax(G.vmax2 + (size_t)G.q * DB_VMAX_SPREAD + (blockIdx.x & (DB_VMAX_SPREAD - 1)), __float_as_uint(m));
     }
 }
 
@@ -1791,8 +1813,7 @@ template <typename R>
 __device__ __forceinline__ double tile_bead_finish(const Params& P, const Box& X, Bank& B, int i, const double4& xi,
                                                    double vx, double vy, double vz, const Acc<R>& a,
                                                    double4* __restrict__ xout, int64_t step, double pref,
-                                                   int* __restrict__ err, double4* __restrict__ xsave,
-                                                   double* __restrict__ vsave) {
+                                                   int* __restrict__ err) {
     const int n = P.n;
     double Fx = a.fx, Fy = a.fy, Fz = a.fz;
     if (P.has_ext) {
@@ -1800,12 +1821,6 @@ __device__ __forceinline__ double tile_bead_finish(const Params& P, const Box& X
         Fx += P.fext[3 * g];
         Fy += P.fext[3 * g + 1];
         Fz += P.fext[3 * g + 2];
-    }
-    if (xsave) {   // first step of a block: keep its input state for a re-run
-        xsave[i] = xi;
-        vsave[i] = vx;
-        vsave[n + i] = vy;
-        vsave[2 * n + i] = vz;
     }
     if (P.gamma != 0.0) {
         uint4 w = rng_draw(X, (uint32_t)(meta_gid(xi) - X.gid_off), 0u, step, RNG_LANGEVIN);
@@ -1850,16 +1865,15 @@ __device__ __forceinline__ double tile_bead_finish(const Params& P, const Box& X
 template <typename R>
 __global__ __launch_bounds__(DB_BLOCK) void k_step_tile(const Params* __restrict__ Pp, Bank B, NList NL, Halo H,
                                                         Tiles T, double4* __restrict__ xout, int64_t step,
-                                                        double pref, unsigned int* __restrict__ vmax2_slot,
-                                                        int* __restrict__ err, double4* __restrict__ xsave,
-                                                        double* __restrict__ vsave,
-                                                        const int64_t* __restrict__ step_base) {
+                                                        double pref, Gate G, int* __restrict__ err,
+                                                        const BlockBase* __restrict__ base) {
     const Params& P = *Pp;
     const int n = P.n;
-    if (step_base) {
+    if (base) {
         double dsig = 0.0;
-        step_amplitudes(P, step_base, step, pref, dsig);
+        step_amplitudes(P, base, step, pref, dsig, G);
     }
+    if (!gate_open<false>(P, G)) return;   // the same for every thread of the launch
     const Box& X = P.box;
     __shared__ Coef<R> C;
     __shared__ double rx[DB_RCAP], ry[DB_RCAP], rz[DB_RCAP];
@@ -2008,7 +2022,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_step_tile(const Params* __restrict
         __syncthreads();
         if (active) tile_collect<R>(lu.f, tb, nAi, nDi, a);
     }
-    const double m2 = active ? tile_bead_finish<R>(P, X, B, i, xi, vx, vy, vz, a, xout, step, pref, err, xsave, vsave)
+    const double m2 = active ? tile_bead_finish<R>(P, X, B, i, xi, vx, vy, vz, a, xout, step, pref, err)
                              : 0.0;
     // largest speed of the tile: one atomic per workgroup, spread over 64 words
     __shared__ float wmax[DB_BLOCK / 64];
@@ -2018,7 +2032,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_step_tile(const Params* __restrict
     if (tid == 0) {
         float mm = wmax[0];
         for (int w = 1; w < DB_BLOCK / 64; ++w) mm = fmaxf(mm, wmax[w]);
-        atomicMax(vmax2_slot + (blockIdx.x & (DB_VMAX_SPREAD - 1)), __float_as_uint(mm));
+        atomicMax(G.vmax2 + (size_t)G.q * DB_VMAX_SPREAD + (blockIdx.x & (DB_VMAX_SPREAD - 1)), __float_as_uint(mm));
     }
 }
 
@@ -2319,60 +2333,58 @@ static bool velocity_double_buffer(const db_ctx* c) {
 
 template <typename R, bool BATCH, int PAIR>
 static void launch_step_kernel(db_ctx* c, const Bank& B, double4* xout, double* vout, int64_t step, double pref,
-                               double dsig, unsigned* vm, bool save) {
+                               double dsig, const Gate& G) {
     hipLaunchKernelGGL((k_step<R, BATCH, PAIR>), dim3(grid_for(c->n)), dim3(DB_BLOCK), 0, c->stream, c->dp, B,
-                       c->nlist, c->halo, xout, vout, step, pref, dsig, vm, c->err_d, save ? c->xsave : nullptr,
-                       save ? c->vsave : nullptr, c->xref, (const int64_t*)c->step_base_d);
+                       c->nlist, c->halo, xout, vout, step, pref, dsig, G, c->err_d, c->xref,
+                       (const BlockBase*)c->base_captured);
 }
 
 template <int PAIR>
 static void launch_step_pair(db_ctx* c, const Bank& B, double4* xout, double* vout, int64_t step, double pref,
-                             double dsig, unsigned* vm, bool save) {
+                             double dsig, const Gate& G) {
     const bool batch = c->nrep > 0;
     if (c->precision == DB_MIXED) {
-        if (batch) launch_step_kernel<float, true, PAIR>(c, B, xout, vout, step, pref, dsig, vm, save);
-        else launch_step_kernel<float, false, PAIR>(c, B, xout, vout, step, pref, dsig, vm, save);
+        if (batch) launch_step_kernel<float, true, PAIR>(c, B, xout, vout, step, pref, dsig, G);
+        else launch_step_kernel<float, false, PAIR>(c, B, xout, vout, step, pref, dsig, G);
     } else {
-        if (batch) launch_step_kernel<double, true, PAIR>(c, B, xout, vout, step, pref, dsig, vm, save);
-        else launch_step_kernel<double, false, PAIR>(c, B, xout, vout, step, pref, dsig, vm, save);
+        if (batch) launch_step_kernel<double, true, PAIR>(c, B, xout, vout, step, pref, dsig, G);
+        else launch_step_kernel<double, false, PAIR>(c, B, xout, vout, step, pref, dsig, G);
     }
 }
 
 static bool dpd_pairs(const db_ctx* c) { return c->hp.have_pair && c->hp.pair_style == PAIR_DPD; }
 
-// c->step_base_d set (the launch is captured into a graph): step is the offset within
-// the block and the kernel reads the block's first step from the device
-void launch_step(db_ctx* c, int64_t step, int slot_in_block, bool save) {
-    if (c->n == 0) return;
-    const double pref = c->step_base_d ? 0.0 : langevin_prefactor(c->hp, step);
-    const double dsig = c->step_base_d ? 0.0 : dpd_sigma(c->hp, step);
+// exchanges the buffers a step reads and writes
+void swap_step_buffers(db_ctx* c) {
     Bank& B = c->bank[c->cur];
-    unsigned* vm = (unsigned*)(c->vmax2 + (size_t)slot_in_block * DB_VMAX_SPREAD);
-    const bool vbuf = velocity_double_buffer(c);
+    std::swap(B.x, c->xnext);
+    if (velocity_double_buffer(c)) std::swap(B.v, c->vnext);
+}
+
+// c->base_captured set (the launch is captured into a graph): step is the offset
+// within the block, and the kernel reads the block's first step and bounds from the
+// device
+void launch_step(db_ctx* c, int64_t step, int q, double d0, double limit) {
+    if (c->n == 0) return;
+    const double pref = c->base_captured ? 0.0 : langevin_prefactor(c->hp, step);
+    const double dsig = c->base_captured ? 0.0 : dpd_sigma(c->hp, step);
+    Bank& B = c->bank[c->cur];
+    const Gate G{(unsigned*)c->vmax2, c->gate_bound, q, d0, limit};
     if (tiles_enabled(c) && c->tiles_valid && c->regions_valid) {
-        double4* xs = save ? c->xsave : nullptr;
-        double* vs = save ? c->vsave : nullptr;
         if (c->precision == DB_MIXED)
             hipLaunchKernelGGL(k_step_tile<float>, dim3(c->ntile), dim3(DB_BLOCK), 0, c->stream, c->dp, B, c->nlist,
-                               c->halo, c->tiles, c->xnext, step, pref, vm, c->err_d, xs, vs,
-                               (const int64_t*)c->step_base_d);
+                               c->halo, c->tiles, c->xnext, step, pref, G, c->err_d,
+                               (const BlockBase*)c->base_captured);
         else
             hipLaunchKernelGGL(k_step_tile<double>, dim3(c->ntile), dim3(DB_BLOCK), 0, c->stream, c->dp, B,
-                               c->nlist, c->halo, c->tiles, c->xnext, step, pref, vm, c->err_d, xs, vs,
-                               (const int64_t*)c->step_base_d);
+                               c->nlist, c->halo, c->tiles, c->xnext, step, pref, G, c->err_d,
+                               (const BlockBase*)c->base_captured);
     } else {
-        double* vout = vbuf ? c->vnext : B.v;
-        if (dpd_pairs(c)) launch_step_pair<PAIR_DPD>(c, B, c->xnext, vout, step, pref, dsig, vm, save);
-        else launch_step_pair<PAIR_WCA>(c, B, c->xnext, vout, step, pref, dsig, vm, save);
+        double* vout = velocity_double_buffer(c) ? c->vnext : B.v;
+        if (dpd_pairs(c)) launch_step_pair<PAIR_DPD>(c, B, c->xnext, vout, step, pref, dsig, G);
+        else launch_step_pair<PAIR_WCA>(c, B, c->xnext, vout, step, pref, dsig, G);
     }
-    double4* t = B.x;
-    B.x = c->xnext;
-    c->xnext = t;
-    if (vbuf) {
-        double* u = B.v;
-        B.v = c->vnext;
-        c->vnext = u;
-    }
+    swap_step_buffers(c);
 }
 
 // k_eval with the handle's force type, box form and pair style

@@ -130,3 +130,25 @@ def test_topology_lists_come_back_sorted(n):
     assert np.array_equal(g.bonds(), b[np.lexsort(b.T[::-1])])
     assert np.array_equal(g.angles(), a[np.lexsort((a[:, 0], a[:, 3], a[:, 2], a[:, 1]))])
     assert np.array_equal(g.dihedrals(), d[np.lexsort((d[:, 0], d[:, 4], d[:, 3], d[:, 2], d[:, 1]))])
+
+
+@pytest.mark.parametrize("skin", [0.03, 0.08, 0.17])
+@pytest.mark.parametrize("tiles,graph", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_blocks_cut_short_follow_the_oracle(tiles, graph, skin):
+    """Speeds that outrun a thin skin end blocks after one, two, three ... of their steps (either buffer holding the
+    state then), with launches and graphs, both kernel shapes; positions as in the other trajectory tests."""
+    import paper_1108_4214_amd as pk
+    from gpu_common import same_topology
+    s = synth.single_strands(24, 6, L=11.0, seed_w=3, seed_d=4, T=2.0)
+    g, o = both(s, synth.ff_t2(T0=2.0, T1=2.0), synth.rules_t2(p=0.7, every=7, r_kill=1.35), seed=9)
+    pk.db_tune(g.ctx, skin, 2)
+    pk.db_tile_shape(g.ctx, tiles)
+    pk.db_graph(g.ctx, graph)
+    for _ in range(3):
+        g.step(8)
+        o.step(8)
+    assert g.stats()["rollbacks"] > 0 and g.stats()["steps"] == 24
+    d = g.state()[0] - o.state()[0]
+    d -= s.L * np.round(d / s.L)
+    assert np.abs(d).max() < 1e-9
+    assert same_topology(g, o)
