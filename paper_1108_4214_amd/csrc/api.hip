@@ -172,12 +172,9 @@ static size_t layout(db_ctx* c, bool assign) {
     put(c->vnext, 24 * n);
     put(c->xref, 32 * n);
     put(c->fext, 24 * n);
-    // two slots of at least 256 bytes each (their sizes are part of the layout that
-    // checkpoints record) hold the bounds of a block
-    static_assert(8 * DB_MAX_BLOCK <= 512, "the bounds fit the two smallest slots");
-    put(c->gate_bound, 32 * n);
-    double* rest = nullptr;
-    put(rest, 24 * n);
+    // (the sizes of these two are part of the layout that checkpoints record)
+    put(c->cells.xq, 32 * n);
+    put(c->gate_bound, 24 * n);
     SweepBuf& S = c->sw;
     put(S.nomC, 4 * n);
     put(S.ruleC, n);
@@ -272,6 +269,7 @@ static int ensure_memory(db_ctx* c) {
         HIPCHK(c, hipHostGetDevicePointer(&dptr, p, 0));
         ext(c).pin_dev = (Pinned*)dptr;
     }
+    static_assert(8 * (3 + DB_XS_PAD) <= 32 * 3 && 8 * (2 + DB_XS_PAD) <= 256, "the quantised copy fits its slot");
     // zero the counters that kernels assume start at zero
     launch_fill_int(c->cells.cnt, 0, (size_t)ncell_cap(c), c->stream);
     launch_fill_int(c->err_d, 0, 16, c->stream);

@@ -139,82 +139,202 @@ __device__ __forceinline__ void scan_cells(const Box& X, const int* __restrict__
     }
 }
 
-// The candidates of scan_cells (grids of three or more cells per edge only), each
-// passed as f(w, r2) with w the entry's word (xs_slot(w) is its slot) and r2 the
-// float squared distance, +inf for the bead itself and for entries past the run's
-// end, in scan_cells' order.  f runs for every candidate, so a visitor without
-// branches (one that writes every candidate and advances its count by r2 < its
-// squared cutoff) keeps the lanes of a wave together; the x-range of a
-// row and its wrapped part are separate loops, so the common range needs no
-// per-candidate choice of image.  The bead's own entry is told apart by its whole
-// word (the slot bits differ for every other bead), and r2 is formed with fused
-// multiply-adds, whose rounding is within the relative margin of the cutoffs.
-template <class F>
-__device__ __forceinline__ void scan_cells_all(const Box& X, const int* __restrict__ cstart,
-                                               const float4* __restrict__ xs, int i, const double4& xi, F&& f) {
+// ---- the quantised scan ----------------------------------------------------------
+// The same cells through the quantised copy, for the kernels that scan for every
+// bead.  Scattered loads cost the vector memory path a pass per few lanes whatever
+// their width, and the float scan was bound by them (16 bytes, one candidate, per
+// lane and load) and by its instructions: every lane of a wavefront waits for the
+// longest run of a row, 147 candidate places for 64 candidates.  Here
+//  - a load brings two candidates of 8 bytes, and their distance takes integer
+//    subtractions and dot products with the periodic image for nothing;
+//  - a row's end cells, and whole corner rows, are left out where the bead is
+//    farther from them than the reach (24 % of the candidates);
+//  - the three rows of a layer are consumed back to back, so that a wavefront waits
+//    for the longest layer of its beads, not for the longest row three times.
+// Distances are good to 1.8 units (each component to 1.01), so the cutoff is
+// widened by two units: a list holds up to 9 % more entries than it needs in the
+// largest boxes that take this scan, 0.7 % in the 1M-bead duplex box.
+// List build: 95 -> 72 us (1M duplex beads), 80 -> 65 (400k, 1-bead model in DPD
+// solvent), 47 -> 43.5 (300k DPD solution: its runs differ most), 27 -> 15.5 at 80k and
+// 18 -> 7.6 at 3k beads with four threads per bead; energies of 500k beads in FP64 110
+// -> 75 us.  Now bound by instructions (55 us of issue at 1M) and L1 accesses alike.
+typedef short db_short2 __attribute__((ext_vector_type(2)));
+
+// The squared cutoff of the quantised scan, the reach widened by two units; 0 where
+// the scan does not serve: grids of fewer than three cells per edge, and boxes where
+// two units are more than 3 % of the reach (edges beyond about 1,000 reaches), which
+// would keep too many entries.
+__device__ __forceinline__ uint32_t quantised_cut(const Box& X, double reach) {
+    const double r = reach * (65536.0 / X.L);
+    return X.noff == 3 && 2.0 <= 0.03 * r ? (uint32_t)fmin((r + 2.0) * (r + 2.0) + 1.0, 4294967040.0) : 0u;
+}
+
+// f(p, rem, r2) with p the place in list order of the first of four consecutive
+// entries, rem how many of them belong to the run (those after it are to be ignored:
+// they may be entries of another run), and r2[4] their squared distances in squared
+// units (the bead itself among them).  reach: no entry farther than that from the
+// bead need be visited.
+// Four threads may share a bead (PARTS; a system that does not fill the GPU with one
+// thread per bead takes as long as one thread's chain of loads): each takes an edge
+// row, a corner row and a quarter of the middle row's entries.  One thread takes the
+// rows a layer at a time.
+template <int PARTS, class F>
+__device__ __forceinline__ void scan_cells_quantised(const Box& X, const int* __restrict__ cstart,
+                                                     const uint2* __restrict__ xq, const double4& xi, double reach,
+                                                     int part, F&& f) {
+    static_assert(PARTS == 1 || PARTS == 4, "shares are defined for these");
+    constexpr int BATCHES = PARTS == 1 ? 3 : 1;
+    // row k of a batch as oy + 1 | (oz + 1) << 2; 5 is the middle row
+    auto row_code = [&](int batch, int k) -> int {
+        if (PARTS == 1) return k | batch << 2;
+        if (k == 0) return part == 0 ? 4 : (part == 1 ? 1 : (part == 2 ? 6 : 9));
+        if (k == 1) return part == 0 ? 0 : (part == 1 ? 2 : (part == 2 ? 8 : 10));
+        return 5;
+    };
     const int nc = X.nc;
     const int cx = cell_coord(xi.x, X.cell_scale, nc);
     const int cy = cell_coord(xi.y, X.cell_scale, nc);
     const int cz = cell_coord(xi.z, X.cell_scale, nc);
-    const float Lf = (float)X.L;
-    const float px = (float)xi.x, py = (float)xi.y, pz = (float)xi.z;
-    const int wi = __float_as_int(xs_word(i, meta_word(xi)));
+    const uint2 own = quantise(X, (float)xi.x, (float)xi.y, (float)xi.z);
+    const db_short2 pxy = __builtin_bit_cast(db_short2, own.x);
+    const db_short2 pz0 = __builtin_bit_cast(db_short2, own.y);
     cstart += X.cell_off;
-    auto shift = [&](int c) { return c < 0 ? -Lf : (c >= nc ? Lf : 0.0f); };
-    int a0, a1, b0 = 0, b1 = 0;
-    float qx1 = px;
-    if (cx >= 1 && cx <= nc - 2) {
-        a0 = cx - 1;
-        a1 = cx + 2;
-    } else if (cx == 0) {
-        a0 = 0;
-        a1 = 2;
-        b0 = nc - 1;
-        b1 = nc;
-        qx1 = px + Lf;
-    } else {
-        a0 = nc - 2;
-        a1 = nc;
-        b0 = 0;
-        b1 = 1;
-        qx1 = px - Lf;
-    }
-    const bool wrapx = b1 > b0;
-    auto row_of = [&](int r) { return (wrap_cell(cz + r / 3 - 1, nc) * nc + wrap_cell(cy + r % 3 - 1, nc)) * nc; };
-    // one run [s, e) of consecutive entries seen from (qx, qy, qz); a group of
-    // loads may run past e (into the next cells' entries, or into the padding after
-    // the last entry), and those candidates are masked
-    auto run = [&](int s, int e, float qx, float qy, float qz) {
-        for (int p = s; p < e; p += DB_SCAN_W) {
-            float4 c[DB_SCAN_W];
-            const float4* src = xs + p;
+    // place inside the cell and squared reach, in cell edges (the reach with room for
+    // the rounding of both)
+    const float fx = (float)(xi.x * X.cell_scale - cx), fy = (float)(xi.y * X.cell_scale - cy),
+                fz = (float)(xi.z * X.cell_scale - cz);
+    const float rr = (float)(reach * X.cell_scale) * 1.0001f + 1e-5f;
+    const float r2c = rr * rr;
+    const float lx2 = fx * fx, hx2 = (1.0f - fx) * (1.0f - fx);
+    // the four starts around a row's cells begin at base; where the row wraps, the
+    // cell across the boundary is a run of its own
+    const bool lo = cx == 0, hi = cx == nc - 1;
+    const int base = lo ? 0 : min(cx - 1, nc - 3);
+    const int over = lo ? nc - 1 : 0;
+    const bool any_wrap = __builtin_amdgcn_ballot_w64(lo | hi) != 0;
+    struct Four {
+        uint4 a, b;
+    };
+    auto fetch = [&](int p) {
+        Four c;
+        __builtin_memcpy(&c, (const char*)xq + (uint32_t)p * (uint32_t)sizeof(uint2), sizeof c);
+        return c;
+    };
+    static_assert((uint64_t)DB_MAX_BEADS * sizeof(uint2) < (1ull << 32), "places as 32-bit byte offsets");
+    auto group = [&](const Four& c, int p, int rem) {
+        const uint32_t xy[4] = {c.a.x, c.a.z, c.b.x, c.b.z}, z[4] = {c.a.y, c.a.w, c.b.y, c.b.w};
+        uint32_t r2[4];
 #pragma unroll
-            for (int q = 0; q < DB_SCAN_W; ++q) c[q] = src[q];
-            const int rem = e - p;
+        for (int q = 0; q < 4; ++q) {
+            const db_short2 d = __builtin_bit_cast(db_short2, xy[q]) - pxy;
+            const db_short2 dz = __builtin_bit_cast(db_short2, z[q]) - pz0;
+            r2[q] = (uint32_t)__builtin_amdgcn_sdot2(dz, dz, __builtin_amdgcn_sdot2(d, d, 0, false), false);
+        }
+        f(p, rem, r2);
+    };
+    // the runs [s, e) one after another; the next four entries are requested before
+    // the present four are looked at (two sets of registers take turns)
+    auto consume = [&](auto& s, auto& e) {
+        constexpr int M = sizeof(s) / sizeof(s[0]);
+        // empty runs go last
 #pragma unroll
-            for (int q = 0; q < DB_SCAN_W; ++q) {
-                const int w = __float_as_int(c[q].w);
-                const float dx = c[q].x - qx, dy = c[q].y - qy, dz = c[q].z - qz;
-                const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
-                f(w, ((q < rem) & (w != wi)) ? r2 : __builtin_inff());
+        for (int k = M - 2; k >= 0; --k) {
+            if (s[k] >= e[k]) {
+#pragma unroll
+                for (int m = k; m + 1 < M; ++m) {
+                    s[m] = s[m + 1];
+                    e[m] = e[m + 1];
+                }
+                e[M - 1] = s[M - 1];
             }
         }
-    };
-    int row = row_of(0);
-    int s0 = cstart[row + a0], s1 = cstart[row + a1];
-    int t0 = wrapx ? cstart[row + b0] : 0, t1 = wrapx ? cstart[row + b1] : 0;
-    for (int r = 0; r < 9; ++r) {
-        const float qz = pz - shift(cz + r / 3 - 1), qy = py - shift(cy + r % 3 - 1);
-        const int c0 = s0, c1 = s1, d0 = t0, d1 = t1;
-        if (r + 1 < 9) {   // the next row's bounds are requested before this row is scanned
-            row = row_of(r + 1);
-            s0 = cstart[row + a0];
-            s1 = cstart[row + a1];
-            t0 = wrapx ? cstart[row + b0] : 0;
-            t1 = wrapx ? cstart[row + b1] : 0;
+        int p = s[0], end = e[0];
+        if (!(p < end)) return;
+        auto advance = [&](int& now, int& rem) {
+            now = p;
+            rem = end - p;
+            p += 4;
+            if (p >= end) {
+                p = s[1];
+                end = e[1];
+#pragma unroll
+                for (int m = 1; m + 1 < M; ++m) {
+                    s[m] = s[m + 1];
+                    e[m] = e[m + 1];
+                }
+                e[M - 1] = s[M - 1];
+            }
+        };
+        Four c = fetch(p);
+        for (;;) {
+            int now, rem;
+            advance(now, rem);
+            const Four d = fetch(p);   // past the last run too: a place in the list all the same
+            group(c, now, rem);
+            if (!(p < end)) break;
+            advance(now, rem);
+            c = fetch(p);
+            group(d, now, rem);
+            if (!(p < end)) break;
         }
-        run(c0, c1, px, qy, qz);
-        run(d0, d1, qx1, qy, qz);
+    };
+    auto row_of = [&](int code) {
+        return (wrap_cell(cz + (code >> 2) - 1, nc) * nc + wrap_cell(cy + (code & 3) - 1, nc)) * nc;
+    };
+    // squared reach left along x in a row (negative: the row is out of reach)
+    auto left_of = [&](int code) {
+        const int oy = code & 3, oz = code >> 2;
+        const float dy = oy == 0 ? fy : (oy == 2 ? 1.0f - fy : 0.0f), dz = oz == 0 ? fz : (oz == 2 ? 1.0f - fz : 0.0f);
+        return r2c - dz * dz - dy * dy;
+    };
+    int st[3][4];
+    auto fetch_starts = [&](int batch) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) __builtin_memcpy(st[k], cstart + row_of(row_code(batch, k)) + base, sizeof st[k]);
+    };
+    fetch_starts(0);
+#pragma unroll 1
+    for (int batch = 0; batch < BATCHES; ++batch) {
+        int s[3], e[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int code = row_code(batch, k);
+            const float h2 = left_of(code);
+            const bool left = lx2 <= h2, right = hx2 <= h2, any = h2 >= 0.0f;
+            // starts of the left, own and right cell and the end; a cell across the
+            // boundary is empty here
+            const int t0 = hi ? st[k][1] : st[k][0];
+            const int t1 = lo ? st[k][0] : (hi ? st[k][2] : st[k][1]);
+            const int t2 = lo ? st[k][1] : (hi ? st[k][3] : st[k][2]);
+            const int t3 = lo ? st[k][2] : st[k][3];
+            s[k] = left ? t0 : t1;
+            e[k] = any ? (right ? t3 : t2) : s[k];
+            if (PARTS > 1 && k == 2) {   // the thread's share of the middle row
+                const int chunk = ((e[k] - s[k] + 4 * PARTS - 1) / (4 * PARTS)) * 4;
+                s[k] += part * chunk;
+                e[k] = min(e[k], s[k] + chunk);
+            }
+        }
+        if (batch + 1 < BATCHES) fetch_starts(batch + 1);   // requested before this batch is scanned
+        if (!any_wrap) {
+            consume(s, e);
+        } else {   // some lane's rows wrap: with the cells across the boundary
+            int s6[6], e6[6];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const int code = row_code(batch, k);
+                const float h2 = left_of(code);
+                bool across = (lo & (lx2 <= h2)) | (hi & (hx2 <= h2));
+                if (PARTS > 1 && k == 2) across &= part == 0;
+                int sv[2];
+                __builtin_memcpy(sv, cstart + row_of(code) + over, sizeof sv);
+                s6[2 * k] = s[k];
+                e6[2 * k] = e[k];
+                s6[2 * k + 1] = sv[0];
+                e6[2 * k + 1] = across ? sv[1] : sv[0];
+            }
+            consume(s6, e6);
+        }
     }
 }
 

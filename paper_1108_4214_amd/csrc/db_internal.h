@@ -206,7 +206,7 @@ struct Tiles {
 // restored and no input state is kept.
 struct Gate {
     unsigned int* vmax2;   // the block's maxima, DB_VMAX_SPREAD words per step
-    double* bound;         // [DB_MAX_BLOCK] the bound at each step's input
+    double* bound;         // [2] the bound at the input of step q, at q & 1
     int q;                 // the step's place in the block
     double d0, limit;      // the bound at the block's input, and its limit
 };
@@ -235,6 +235,7 @@ struct Cells {
     int* start;       // [ncell + 1]
     int* list;        // [n] slots, cell by cell, ascending within a cell
     float4* xs;       // [n + DB_XS_PAD] in list order: float x, y, z and (bits) slot | type << 26 | reactive << 31
+    uint2* xq;        // [n + DB_XS_PAD] in list order: x | y << 16, z, in units of edge / 65536 (rounded down)
     int* cellid;      // [n]
     int* rank;        // [n] place of the bead among the beads of its cell
     int* unsorted;    // [n] the list before the ordering inside each cell
@@ -271,7 +272,7 @@ struct db_ctx {
     double4* xref;       // positions at the last full Verlet-list build (slot order)
     double* vnext;       // double buffer of velocities (DPD: the step reads neighbour velocities)
     double* fext;        // [3n] external force by global bead id
-    double* gate_bound;  // [DB_MAX_BLOCK] displacement bounds of the current block (Gate)
+    double* gate_bound;  // [2] displacement bounds of the current block (Gate)
     db::SweepBuf sw;
     db::Cells cells;
     db::NList nlist;

@@ -271,12 +271,15 @@ __global__ __launch_bounds__(DB_BLOCK) void k_scatter(int n, const int* __restri
 // Ascending slot order inside each cell makes the list independent of the
 // arrival order of the atomics above.  One thread per entry of the unsorted
 // list: the entry's place in its cell is the number of the cell's entries with a
-// smaller slot.  The float copy of the positions is written in list order, so a
-// scan over neighbouring cells reads contiguous runs.
-__global__ __launch_bounds__(DB_BLOCK) void k_cellsort(int n, const int* __restrict__ start,
+// smaller slot.  The float and the quantised copy of the positions are written in
+// list order, so a scan over neighbouring cells reads contiguous runs.
+template <bool BATCH>
+__global__ __launch_bounds__(DB_BLOCK) void k_cellsort(const Params* __restrict__ Pp, const int* __restrict__ start,
                                                         const int* __restrict__ cellid,
                                                         const int* __restrict__ unsorted, int* __restrict__ list,
-                                                        const double4* __restrict__ x, float4* __restrict__ xs) {
+                                                        const double4* __restrict__ x, float4* __restrict__ xs,
+                                                        uint2* __restrict__ xq) {
+    const int n = Pp->n;
     const int t = blockIdx.x * DB_BLOCK + threadIdx.x;
     if (t >= n) return;
     const int j = unsorted[t];
@@ -285,8 +288,10 @@ __global__ __launch_bounds__(DB_BLOCK) void k_cellsort(int n, const int* __restr
     const int s0 = start[c], s1 = start[c + 1];
     int r = 0;
     for (int k = s0; k < s1; ++k) r += unsorted[k] < j ? 1 : 0;
+    const float fx = (float)xj.x, fy = (float)xj.y, fz = (float)xj.z;
     list[s0 + r] = j;
-    xs[s0 + r] = make_float4((float)xj.x, (float)xj.y, (float)xj.z, xs_word(j, meta_word(xj)));
+    xs[s0 + r] = make_float4(fx, fy, fz, xs_word(j, meta_word(xj)));
+    xq[s0 + r] = quantise(box_of<BATCH>(*Pp, meta_word(xj)), fx, fy, fz);
 }
 
 void launch_build_cells(db_ctx* c) {
@@ -308,8 +313,12 @@ void launch_build_cells(db_ctx* c) {
     if (n > 0) {
         hipLaunchKernelGGL(k_scatter, dim3(nb), dim3(DB_BLOCK), 0, s, n, c->cells.cellid, c->cells.rank,
                            c->cells.start, c->cells.cnt, c->cells.unsorted, c->sw.stats);
-        hipLaunchKernelGGL(k_cellsort, dim3(nb), dim3(DB_BLOCK), 0, s, n, c->cells.start, c->cells.cellid,
-                           c->cells.unsorted, c->cells.list, B.x, c->cells.xs);
+        if (c->nrep > 0)
+            hipLaunchKernelGGL(k_cellsort<true>, dim3(nb), dim3(DB_BLOCK), 0, s, c->dp, c->cells.start,
+                               c->cells.cellid, c->cells.unsorted, c->cells.list, B.x, c->cells.xs, c->cells.xq);
+        else
+            hipLaunchKernelGGL(k_cellsort<false>, dim3(nb), dim3(DB_BLOCK), 0, s, c->dp, c->cells.start,
+                               c->cells.cellid, c->cells.unsorted, c->cells.list, B.x, c->cells.xs, c->cells.xq);
     }
 }
 

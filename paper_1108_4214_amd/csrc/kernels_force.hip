@@ -258,7 +258,7 @@ __device__ __forceinline__ void gather_excl(const Params& P, const Bank& B, int 
     const int pp[DB_MAXB] = {E.p0, E.p1, E.p2, E.p3};
 #pragma unroll
     for (int k = 0; k < DB_MAXB * DB_MAXB; ++k) E.two[k] = -1;
-    if (E.d2) {
+    if (E.d2 && E.nb > 0) {   // a wavefront of solvent reads no partners' tables
         int nq[DB_MAXB];
 #pragma unroll
         for (int k = 0; k < DB_MAXB; ++k) {
@@ -275,81 +275,142 @@ __device__ __forceinline__ void gather_excl(const Params& P, const Bank& B, int 
     }
 }
 
+// LDS rows for the candidates a thread keeps: 28 hold every list of the DPD fluid at
+// density 3 (14 beads within its list cutoff), 18 a quarter of one and more
+template <int PARTS>
+constexpr int scan_rows() { return PARTS == 1 ? 28 : 18; }
+
+// The candidates of bead i within reach, kept in the thread's LDS column (rows 0 to
+// ROWS - 5; the last four take the places that are not kept) as places in list
+// order: every candidate is written into the row of the next kept one, which a kept
+// one advances, so the scan has no branch per candidate.  counted is advanced by
+// the candidates with a squared distance below count_cut.  Returns their number; more
+// than ROWS - 4: not all were kept.
+template <int ROWS, int PARTS = 1>
+__device__ __forceinline__ int stage_quantised(const Box& X, const int* __restrict__ cstart,
+                                               const uint2* __restrict__ xq, const double4& xi, double reach,
+                                               uint32_t cutq, int (*stage)[DB_BLOCK], int part = 0,
+                                               uint32_t count_cut = 0, int* counted = nullptr) {
+    // the row of the next kept candidate, as a byte offset; past the rows for kept
+    // ones the four after them are written over and over
+    constexpr uint32_t ROW = sizeof(int) * DB_BLOCK, LIMIT = (ROWS - 4) * ROW;
+    char* const column = (char*)&stage[0][threadIdx.x];
+    uint32_t at = 0;
+    bool over = false;
+    scan_cells_quantised<PARTS>(X, cstart, xq, xi, reach, part, [&](int p, int rem, const uint32_t (&r2)[4]) {
+        over |= at > LIMIT;
+        at = min(at, LIMIT);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            *(int*)(column + at) = p + q;
+            const bool in_run = q == 0 || q < rem;   // a group holds one entry of its run at least
+            at += (in_run & (r2[q] < cutq)) ? ROW : 0u;
+            if (counted) *counted += (in_run & (r2[q] < count_cut)) ? 1 : 0;
+        }
+    });
+    return over ? ROWS : (int)(at / ROW);
+}
+
+// the staged places turned into slots, in place and in order, without the bead itself
+// and its exclusions; returns their number
+template <class Excl>
+__device__ __forceinline__ int settle_staged(const int* __restrict__ clist, int i, int raw, int (*stage)[DB_BLOCK],
+                                             const Excl& E) {
+    const int tid = threadIdx.x;
+    int cnt = 0;
+    for (int k0 = 0; k0 < raw; k0 += 4) {
+        int j[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) j[q] = clist[stage[min(k0 + q, raw - 1)][tid]];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if ((k0 + q < raw) & (j[q] != i) && !E.has(j[q])) {
+                stage[cnt][tid] = j[q];   // cnt <= k0 + q: a place already read
+                ++cnt;
+            }
+        }
+    }
+    return cnt;
+}
+
 // Verlet list of bead i: every bead within the list cutoff (pair cutoff plus a
 // skin) that is not excluded, from the 27 cells of the current cell list.  The
 // float prefilter's cutoff is widened by the box's bound on float rounding
 // (Box::pf_slack), so the list is a superset of the pairs within the cutoff in
 // double.  The full build of every bead; with DPD the bead's position is kept in
 // xref, from which the step kernels measure displacements.
-template <bool BATCH>
-__global__ __launch_bounds__(DB_BLOCK) void k_build_nlist(const Params* __restrict__ Pp, Bank B,
-                                                          const int* __restrict__ cstart,
-                                                          const float4* __restrict__ xs, NList NL,
-                                                          int* __restrict__ err, double4* __restrict__ xref) {
+// PARTS threads share a bead; each keeps its candidates in its own LDS column
+// (scan_rows<PARTS>() rows, plus four that take the writes of the candidates that are
+// not kept) and the list holds them thread by thread.  Five waves per SIMD, what the
+// rows of one thread per bead allow, and the registers then suffice (held to six with
+// fewer rows the scan spills and is slower).
+template <bool BATCH, int PARTS>
+__global__ __launch_bounds__(DB_BLOCK, 5)
+void k_build_nlist(const Params* __restrict__ Pp, Bank B, const int* __restrict__ cstart,
+                   const int* __restrict__ clist, const float4* __restrict__ xs, const uint2* __restrict__ xq,
+                   NList NL, int* __restrict__ err, double4* __restrict__ xref) {
     const Params& P = *Pp;
     const int n = P.n;
-    // list rows staged in LDS, plus one row that takes the writes of the
-    // candidates that are not kept
-    constexpr int NL_STAGE = 24;
-    __shared__ int stage[NL_STAGE + 1][DB_BLOCK];
-    const int i = xcd_tile(blockIdx.x, gridDim.x) * DB_BLOCK + threadIdx.x;
-    if (i >= n) return;
-    const double4 xi = B.x[i];
-    if (xref) xref[i] = xi;
-    ExclSet E;
-    gather_excl(P, B, n, i, E);
-    // The first NL_STAGE entries go to the thread's own LDS column and are written
-    // out afterwards one row at a time, so that a store covers consecutive beads of
-    // one row; entries beyond go straight to memory.  (Written as they are found,
-    // the lanes of a wave store into rows that differ by their counts, and each
-    // store scatters over as many rows.)
+    constexpr int NL_STAGE = scan_rows<PARTS>();
+    __shared__ int stage[NL_STAGE + 4][DB_BLOCK];
     const int tid = threadIdx.x;
-    auto put = [&](int k, int j) {
-        if (k < NL_STAGE) stage[k][tid] = j;
-        else if (k < DB_NLCAP) NL.nl[k * n + i] = j;
-    };
+    const int part = PARTS > 1 ? tid % PARTS : 0;
+    const int i = xcd_tile(blockIdx.x, gridDim.x) * (DB_BLOCK / PARTS) + tid / PARTS;
+    if (i >= n) return;   // the threads of a bead leave together
+    const double4 xi = B.x[i];
+    if (xref && part == 0) xref[i] = xi;
+    // The entries go to the thread's own LDS column and are written out afterwards one
+    // row at a time, so that a store covers consecutive beads of one row.  (Written
+    // as they are found, the lanes of a wave store into rows that differ by their
+    // counts, and each store scatters over as many rows.)
     int cnt = 0;
     const Box& X = box_of<BATCH>(P, meta_word(xi));
     // Every candidate within the cutoff is kept first, in the LDS rows, and the
-    // exclusions are applied afterwards, compacting in place in scan order.  The
-    // scan writes every candidate into the row of the next kept entry (a candidate
-    // not kept is overwritten by the next one kept; past the LDS rows the extra row
-    // takes them all) and advances the count by the test, with no branch per
-    // candidate; tested inside the scan, the exclusion test and the store ran for
-    // every candidate some lane of the wave kept, which is nearly every candidate.
-    // A bead with more kept candidates than the LDS rows hold, or a grid of fewer
-    // than three cells per edge, is scanned with the test inside.
-    int raw = 0;
-    if (X.noff == 3) {
-        const float cut2 = X.pf_list2;
-        scan_cells_all(X, cstart, xs, i, xi, [&](int w, float r2) {
-            stage[min(raw, NL_STAGE)][tid] = w;   // the word; its slot is taken below
-            raw += r2 < cut2 ? 1 : 0;
-        });
-    } else {
-        raw = NL_STAGE + 1;
-    }
-    if (raw <= NL_STAGE) {
-        for (int k = 0; k < raw; ++k) {
-            const int j = xs_slot(stage[k][tid]);
-            if (E.has(j)) continue;
-            stage[cnt][tid] = j;
-            ++cnt;
+    // exclusions are applied afterwards, compacting in place in scan order; tested
+    // inside the scan, the exclusion test and the store ran for every candidate some
+    // lane of the wave kept, which is nearly every candidate.  A bead with more kept
+    // candidates than the LDS rows hold, or a box the quantised scan does not serve,
+    // is scanned on the float copy with the test inside, by one thread.
+    int raw = NL_STAGE + 1;
+    const double reach = sqrt(P.rnl2) + X.pf_slack;
+    const uint32_t cutq = quantised_cut(X, reach);
+    if (cutq) raw = stage_quantised<NL_STAGE + 4, PARTS>(X, cstart, xq, xi, reach, cutq, stage, part);
+    ExclSet E;   // gathered after the scan: its registers would cost the scan a wave per SIMD
+    gather_excl(P, B, n, i, E);
+    int most = raw;
+#pragma unroll
+    for (int o = 1; o < PARTS; o <<= 1) most = max(most, __shfl_xor(most, o, 64));
+    if (most <= NL_STAGE) {
+        cnt = settle_staged(clist, i, raw, stage, E);
+        // the thread's place in the list: after its bead's earlier threads
+        int end = cnt;
+#pragma unroll
+        for (int o = 1; o < PARTS; o <<= 1) {
+            const int t = __shfl_up(end, o, PARTS);
+            if (part >= o) end += t;
         }
-    } else {
+        const int off = end - cnt;
+        for (int k = 0; k < cnt; ++k) NL.nl[(off + k) * n + i] = stage[k][tid];
+        static_assert(PARTS * NL_STAGE <= DB_NLCAP, "staged lists fit");
+        cnt = PARTS > 1 ? __shfl(end, PARTS - 1, PARTS) : end;
+    } else if (part == 0) {
+        auto put = [&](int k, int j) {
+            if (k < NL_STAGE) stage[k][tid] = j;
+            else if (k < DB_NLCAP) NL.nl[k * n + i] = j;
+        };
         scan_cells(X, cstart, xs, i, xi, X.pf_list2, [&](int j, int) {
             if (E.has(j)) return;
             put(cnt, j);
             ++cnt;
         });
+        const int ns = min(cnt, NL_STAGE);
+        for (int k = 0; k < ns; ++k) NL.nl[k * n + i] = stage[k][tid];
+        if (cnt > DB_NLCAP) {
+            atomicOr(err, ERR_NLIST);
+            cnt = DB_NLCAP;
+        }
     }
-    const int ns = min(cnt, NL_STAGE);
-    for (int k = 0; k < ns; ++k) NL.nl[k * n + i] = stage[k][tid];
-    if (cnt > DB_NLCAP) {
-        atomicOr(err, ERR_NLIST);
-        cnt = DB_NLCAP;
-    }
-    NL.cnt[i] = (uint8_t)cnt;
+    if (part == 0) NL.cnt[i] = (uint8_t)cnt;
 }
 
 // The list of one bead whose exclusions a sweep changed, redone with cutoff cut
@@ -1102,13 +1163,13 @@ __device__ __forceinline__ bool gate_open(const Params& P, const Gate& G) {
     if (G.q > 0) {
         float m = __uint_as_float(G.vmax2[(size_t)(G.q - 1) * DB_VMAX_SPREAD + (threadIdx.x & 63)]);
         static_assert(DB_VMAX_SPREAD == 64, "one word per lane");
-        const double before = G.bound[G.q - 1];
+        const double before = G.bound[(G.q - 1) & 1];
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
         const double v = sqrt((double)m);
         b = TRACK ? fmax(before, v) : before + P.dt * v;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) G.bound[G.q] = b;
+    if (blockIdx.x == 0 && threadIdx.x == 0) G.bound[G.q & 1] = b;
     return b <= G.limit;
 }
 
@@ -2043,32 +2104,39 @@ __global__ __launch_bounds__(DB_BLOCK) void k_step_tile(const Params* __restrict
 //
 // A one-off evaluation has no use for a Verlet list: the 27 cells are scanned with
 // the pair cutoff, the kept candidates stay in the thread's LDS column, and their
-// pairs are evaluated from there in scan order, four positions requested at a time.
-// The bonded terms then go through the halo in the same LDS (one column per thread
-// in each layout, a barrier between).  It is bound by the scan, as the list build
-// is (L1 accesses and run-length divergence).  500k duplex beads, energies in FP64:
-// 110 us and 5 us for the final sum, against 400 us for a serial loop over the
-// candidates' double positions and 247 us for a final sum by six threads; 100k beads
-// of DPD solution in FP32 81 + 5 against 644 + 51 us; 191k duplex beads, forces in
-// FP32: 33 us against 42 for a list build and a force pass.
+// pairs are evaluated from there in scan order, four positions (and, with friction,
+// velocities) requested at a time.  The bonded terms then go through the halo in the
+// same LDS (one column per thread in each layout, a barrier between).  It is bound by
+// the scan, as the list build is (instructions and L1 accesses).  500k duplex beads,
+// energies in FP64: 75 us and 5 us for the final sum, against 400 us for a serial loop
+// over the candidates' double positions and 247 us for a final sum by six threads;
+// 100k beads of DPD solution in FP32 104 + 5 (46 once reordered: it waits for
+// neighbours' positions and velocities from the other dies' memory) against 644 + 51;
+// 191k duplex beads, forces in FP32: 28 us against 42 for a list build and a force pass.
 template <typename R, int MODE, bool BATCH, int PAIR>
 __global__ __launch_bounds__(DB_BLOCK) void k_eval(const Params* __restrict__ Pp, Bank B, Halo H,
-                                                   const int* __restrict__ cstart, const float4* __restrict__ xs,
-                                                   int64_t step, double* __restrict__ fout,
+                                                   const int* __restrict__ cstart, const int* __restrict__ clist,
+                                                   const float4* __restrict__ xs, const uint2* __restrict__ xq,
+                                                   int64_t step,
+                                                   double* __restrict__ fout,
                                                    double* __restrict__ epart, int* __restrict__ err) {
     const Params& P = *Pp;
     const int n = P.n;
-    constexpr int EV_STAGE = 32;   // candidates kept per bead (DPD at density 3 has about 13)
+    constexpr int EV_STAGE = scan_rows<1>();
     __shared__ Coef<R> C;
     __shared__ union {
-        int stage[EV_STAGE + 1][DB_BLOCK];   // the last row takes the candidates that are not kept
+        int stage[EV_STAGE + 4][DB_BLOCK];
         R hs[3][DB_MAXU][DB_BLOCK];
     } lds;
     load_coef<R>(P, C);
     const int tid = threadIdx.x;
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
-    const int i = tile * DB_BLOCK + tid;
-    const bool active = i < n;
+    const int place = tile * DB_BLOCK + tid;
+    const bool active = place < n;
+    // DPD takes the beads in list order: before the first reordering neighbouring slots
+    // of solvent are anywhere in the box (300k beads 300 -> 217 us, 86 and 88 once
+    // reordered; molecules come in order, and their tables then read better by slot)
+    const int i = PAIR == PAIR_DPD && active ? clist[place] : place;
     Acc<R> a;
     double4 xi = make_double4(0, 0, 0, 0);
     double vx = 0, vy = 0, vz = 0;
@@ -2082,24 +2150,26 @@ __global__ __launch_bounds__(DB_BLOCK) void k_eval(const Params* __restrict__ Pp
     }
     if (active && P.have_pair) {
         with_box<BATCH>(P, meta_word(xi), [&](const Box& X) __attribute__((always_inline)) {
-            ExclSet E;
-            gather_excl(P, B, n, i, E);
             const double reach = P.rc + X.pf_slack;
             const float cut2 = (float)(reach * reach * 1.0001);
             const R rc2 = (R)P.rc2;
+            const bool friction = MODE == MODE_ENERGY && PAIR == PAIR_DPD && P.dpd_gamma != 0.0;
             double dsig = 0.0;
-            if (MODE == MODE_ENERGY && PAIR == PAIR_DPD && P.dpd_gamma != 0.0)
+            if (friction)
                 dsig = sqrt(2.0 * box_temperature(X, step) * P.dpd_gamma) / sqrt(P.dt);
-            auto pair = [&](int j, const double4& xj) {
+            auto vel_of = [&](int j) {
+                return friction ? V3<double>{B.v[j], B.v[n + j], B.v[2 * n + j]} : V3<double>{0.0, 0.0, 0.0};
+            };
+            auto pair = [&](const double4& xj, const V3<double>& vj) {
                 const double dx = near_image(xj.x - xi.x, X), dy = near_image(xj.y - xi.y, X),
                              dz = near_image(xj.z - xi.z, X);
                 if constexpr (PAIR == PAIR_DPD) {
                     const R rx = (R)dx, ry = (R)dy, rz = (R)dz;
                     const R r2 = (rx * rx + ry * ry) + rz * rz;
                     if (!(r2 < rc2)) return;
-                    if (MODE == MODE_ENERGY && P.dpd_gamma != 0.0)
-                        dpd_pair<R, true, true>(P, X, xi, xj, dx, dy, dz, r2, vx - B.v[j], vy - B.v[n + j],
-                                                vz - B.v[2 * n + j], step, dsig, a);
+                    if (friction)
+                        dpd_pair<R, true, true>(P, X, xi, xj, dx, dy, dz, r2, vx - vj.x, vy - vj.y, vz - vj.z, step,
+                                                dsig, a);
                     else
                         dpd_pair<R, false, MODE == MODE_ENERGY>(P, X, xi, xj, dx, dy, dz, r2, 0, 0, 0, 0, 0, a);
                 } else {
@@ -2107,40 +2177,39 @@ __global__ __launch_bounds__(DB_BLOCK) void k_eval(const Params* __restrict__ Pp
                 }
             };
             int raw = EV_STAGE + 1;
-            bool crowded = X.noff != 3;   // more than a Verlet list's capacity of beads may be within its cutoff
-            if (X.noff == 3) {
-                raw = 0;
+            bool crowded = true;   // more than a Verlet list's capacity of beads may be within its cutoff
+            const uint32_t cutq = quantised_cut(X, reach);
+            if (cutq) {
+                const double list_reach = sqrt(P.rnl2) + X.pf_slack;
                 int listed = 0;
-                const float list2 = X.pf_list2;
-                scan_cells_all(X, cstart, xs, i, xi, [&](int w, float r2) {
-                    lds.stage[min(raw, EV_STAGE)][tid] = w;
-                    raw += r2 < cut2 ? 1 : 0;
-                    if (MODE == MODE_FORCE) listed += r2 < list2 ? 1 : 0;
-                });
+                if (MODE == MODE_FORCE)
+                    raw = stage_quantised<EV_STAGE + 4, 1>(X, cstart, xq, xi, list_reach, cutq, lds.stage, 0,
+                                                           quantised_cut(X, list_reach), &listed);
+                else
+                    raw = stage_quantised<EV_STAGE + 4, 1>(X, cstart, xq, xi, reach, cutq, lds.stage, 0);
                 crowded = listed > DB_NLCAP;
             }
+            ExclSet E;   // after the scan, for its registers
+            gather_excl(P, B, n, i, E);
             if (raw <= EV_STAGE) {
-                int cnt = 0;
-                for (int k = 0; k < raw; ++k) {   // exclusions, compacting in place
-                    const int j = xs_slot(lds.stage[k][tid]);
-                    if (E.has(j)) continue;
-                    lds.stage[cnt][tid] = j;
-                    ++cnt;
-                }
+                const int cnt = settle_staged(clist, i, raw, lds.stage, E);
                 for (int k0 = 0; k0 < cnt; k0 += 4) {
                     int j[4];
                     double4 xj[4];
+                    V3<double> vj[4];
 #pragma unroll
                     for (int q = 0; q < 4; ++q) j[q] = lds.stage[min(k0 + q, cnt - 1)][tid];
 #pragma unroll
                     for (int q = 0; q < 4; ++q) xj[q] = B.x[j[q]];
 #pragma unroll
+                    for (int q = 0; q < 4; ++q) vj[q] = vel_of(j[q]);
+#pragma unroll
                     for (int q = 0; q < 4; ++q)
-                        if (k0 + q < cnt) pair(j[q], xj[q]);
+                        if (k0 + q < cnt) pair(xj[q], vj[q]);
                 }
-            } else {   // crowded, or a grid of fewer than three cells per edge
+            } else {   // crowded, or a box the quantised scan does not serve
                 scan_cells(X, cstart, xs, i, xi, cut2, [&](int j, int) {
-                    if (!E.has(j)) pair(j, B.x[j]);
+                    if (!E.has(j)) pair(B.x[j], vel_of(j));
                 });
             }
             // a bead whose Verlet list would overflow is an error here too
@@ -2258,16 +2327,29 @@ void launch_regions(db_ctx* c) {
     c->regions_valid = true;
 }
 
+// Threads per bead of the list build.  A system of fewer than 2^17 beads takes four:
+// one thread per bead leaves each CU a few wavefronts there, and the pass then lasts
+// one thread's chain of loads whatever the size (one against four threads: 8.4 and
+// 5.6 us at 40 beads, 14.2 and 7.6 at 3k, 23.3 and 15.4 at 80k; 30 and 31 at 330k, 72
+// and 99 at 1M).
+static unsigned grid_for_parts(const db_ctx* c, int parts) {
+    return (unsigned)(((int64_t)c->n * parts + DB_BLOCK - 1) / DB_BLOCK);
+}
+
+template <bool BATCH, int PARTS>
+static void launch_nlist(db_ctx* c, double4* xref) {
+    hipLaunchKernelGGL((k_build_nlist<BATCH, PARTS>), dim3(grid_for_parts(c, PARTS)), dim3(DB_BLOCK), 0, c->stream,
+                       c->dp, c->bank[c->cur], c->cells.start, c->cells.list, c->cells.xs, c->cells.xq, c->nlist,
+                       c->err_d, xref);
+}
+
 void launch_build_nlist(db_ctx* c) {
     if (c->n == 0) return;
     launch_halo(c);
     double4* xref = c->hp.have_pair && c->hp.pair_style == PAIR_DPD ? c->xref : nullptr;
-    if (c->nrep > 0)
-        hipLaunchKernelGGL((k_build_nlist<true>), dim3(grid_for(c->n)), dim3(DB_BLOCK), 0, c->stream, c->dp,
-                           c->bank[c->cur], c->cells.start, c->cells.xs, c->nlist, c->err_d, xref);
-    else
-        hipLaunchKernelGGL((k_build_nlist<false>), dim3(grid_for(c->n)), dim3(DB_BLOCK), 0, c->stream, c->dp,
-                           c->bank[c->cur], c->cells.start, c->cells.xs, c->nlist, c->err_d, xref);
+    const bool four = c->n < (1 << 17);
+    if (c->nrep > 0) four ? launch_nlist<true, 4>(c, xref) : launch_nlist<true, 1>(c, xref);
+    else four ? launch_nlist<false, 4>(c, xref) : launch_nlist<false, 1>(c, xref);
     launch_regions(c);
 }
 
@@ -2390,26 +2472,22 @@ void launch_step(db_ctx* c, int64_t step, int q, double d0, double limit) {
 // k_eval with the handle's force type, box form and pair style
 template <typename R, int MODE, bool BATCH>
 static void launch_eval_pair(db_ctx* c, double* f, double* part) {
-    const unsigned nb = grid_for(c->n);
-    if (dpd_pairs(c))
-        hipLaunchKernelGGL((k_eval<R, MODE, BATCH, PAIR_DPD>), dim3(nb), dim3(DB_BLOCK), 0, c->stream, c->dp,
-                           c->bank[c->cur], c->halo, c->cells.start, c->cells.xs, c->step, f, part, c->err_d);
-    else
-        hipLaunchKernelGGL((k_eval<R, MODE, BATCH, PAIR_WCA>), dim3(nb), dim3(DB_BLOCK), 0, c->stream, c->dp,
-                           c->bank[c->cur], c->halo, c->cells.start, c->cells.xs, c->step, f, part, c->err_d);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid_for(c->n)), dim3(DB_BLOCK), 0, c->stream, c->dp, c->bank[c->cur], c->halo,
+                           c->cells.start, c->cells.list, c->cells.xs, c->cells.xq, c->step, f, part, c->err_d);
+    };
+    if (dpd_pairs(c)) go(k_eval<R, MODE, BATCH, PAIR_DPD>);
+    else go(k_eval<R, MODE, BATCH, PAIR_WCA>);
 }
 
 template <int MODE>
 static void launch_eval(db_ctx* c, double* f, double* part) {
     launch_halo(c);
     const bool batch = c->nrep > 0;
-    if (c->precision == DB_MIXED) {
-        if (batch) launch_eval_pair<float, MODE, true>(c, f, part);
-        else launch_eval_pair<float, MODE, false>(c, f, part);
-    } else {
-        if (batch) launch_eval_pair<double, MODE, true>(c, f, part);
-        else launch_eval_pair<double, MODE, false>(c, f, part);
-    }
+    if (c->precision == DB_MIXED)
+        batch ? launch_eval_pair<float, MODE, true>(c, f, part) : launch_eval_pair<float, MODE, false>(c, f, part);
+    else
+        batch ? launch_eval_pair<double, MODE, true>(c, f, part) : launch_eval_pair<double, MODE, false>(c, f, part);
 }
 
 void launch_forces(db_ctx* c, double* f) {

@@ -14,6 +14,14 @@ from gpu_common import both, forces_close
 
 pytestmark = pytest.mark.gpu
 
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    torch.cuda.init()
+
+
 BENDS = [0.0, 1e-9, 1e-6, 1e-3, 0.3, math.radians(44.9999), math.radians(45.0001), 1.2, 0.5 * math.pi, 2.2,
          math.radians(170)]
 TORSIONS = [0.0, 1e-3, 0.7, -0.7, 0.5 * math.pi, -2.0, 3.0, math.pi]
@@ -152,3 +160,32 @@ def test_blocks_cut_short_follow_the_oracle(tiles, graph, skin):
     d -= s.L * np.round(d / s.L)
     assert np.abs(d).max() < 1e-9
     assert same_topology(g, o)
+
+
+def _list_forces(system, ff, precision, seed):
+    """forces through the Verlet lists: the velocity change of one step from rest, over the step"""
+    import paper_1108_4214_amd as pk
+    g = pk.System(system.n, system.L, seed, precision).configure(system, ff, synth.RuleSet(every=0), generate=False)
+    g.step(1)
+    return g.state()[1] / ff.dt
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n,L", [(2, 3.1), (200, 3.2), (500, 4.3), (1500, 5.5), (700, 40.0), (3000, 300.0),
+                                 (3000, 3000.0), (140000, 40.0)])
+def test_list_build_matches_oracle(n, L, precision):
+    """Lists from two to hundreds of cells per edge: crowded cells (more candidates than the staged rows), nearly
+    empty ones (a run's last group reaches far into other rows), an edge whose sixteenth-bit units are too coarse,
+    one and four threads per bead.  Forces of soft pairs, so every term is good to some twenty roundings; clusters of
+    beads across the corner of the box make every wrapped row count."""
+    rng = np.random.default_rng(n)
+    x = rng.uniform(0.0, L, size=(n, 3))
+    k = n // 3
+    x[:k] = np.mod(rng.normal(0.0, max(0.8, 0.25 * k ** (1.0 / 3.0)), size=(k, 3)), L)   # a cloud about the corner
+    s = synth.System(L=L, x=synth.wrap(x, L), v=np.zeros((n, 3)), type=np.ones(n, dtype=np.int32),
+                     reactive=np.zeros(n, dtype=np.uint8), bonds=np.zeros((0, 4), dtype=np.int32))
+    ff = dataclasses.replace(synth.ff_dpd(gamma_dpd=0.0), dt=2.0 ** -10)
+    import oracle
+    o = oracle.Oracle.from_system(s, ff, synth.RuleSet(every=0), seed=1, generate=False)
+    ok, msg = forces_close(_list_forces(s, ff, precision, 1), o.forces(), 1e-11 if precision == 0 else 1e-5)
+    assert ok, msg
