@@ -169,10 +169,10 @@ __device__ __forceinline__ uint32_t quantised_cut(const Box& X, double reach) {
     return X.noff == 3 && 2.0 <= 0.03 * r ? (uint32_t)fmin((r + 2.0) * (r + 2.0) + 1.0, 4294967040.0) : 0u;
 }
 
-// f(p, rem, r2) with p the place in list order of the first of four consecutive
+// f(p, rem, r2, z) with p the place in list order of the first of four consecutive
 // entries, rem how many of them belong to the run (those after it are to be ignored:
 // they may be entries of another run), and r2[4] their squared distances in squared
-// units (the bead itself among them).  reach: no entry farther than that from the
+// units (the bead itself among them); z[4] the entries' second words.  reach: no entry farther than that from the
 // bead need be visited.
 // Four threads may share a bead (PARTS; a system that does not fill the GPU with one
 // thread per bead takes as long as one thread's chain of loads): each takes an edge
@@ -195,9 +195,9 @@ __device__ __forceinline__ void scan_cells_quantised(const Box& X, const int* __
     const int cx = cell_coord(xi.x, X.cell_scale, nc);
     const int cy = cell_coord(xi.y, X.cell_scale, nc);
     const int cz = cell_coord(xi.z, X.cell_scale, nc);
-    const uint2 own = quantise(X, (float)xi.x, (float)xi.y, (float)xi.z);
+    const uint2 own = quantise(X, (float)xi.x, (float)xi.y, (float)xi.z, 0);
     const db_short2 pxy = __builtin_bit_cast(db_short2, own.x);
-    const db_short2 pz0 = __builtin_bit_cast(db_short2, own.y);
+    const short pz = (short)own.y;
     cstart += X.cell_off;
     // place inside the cell and squared reach, in cell edges (the reach with room for
     // the rounding of both)
@@ -227,10 +227,10 @@ __device__ __forceinline__ void scan_cells_quantised(const Box& X, const int* __
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const db_short2 d = __builtin_bit_cast(db_short2, xy[q]) - pxy;
-            const db_short2 dz = __builtin_bit_cast(db_short2, z[q]) - pz0;
-            r2[q] = (uint32_t)__builtin_amdgcn_sdot2(dz, dz, __builtin_amdgcn_sdot2(d, d, 0, false), false);
+            const int dz = (short)((short)z[q] - pz);
+            r2[q] = (uint32_t)__builtin_amdgcn_sdot2(d, d, dz * dz, false);
         }
-        f(p, rem, r2);
+        f(p, rem, r2, z);
     };
     // the runs [s, e) one after another; the next four entries are requested before
     // the present four are looked at (two sets of registers take turns)

@@ -138,13 +138,16 @@ __device__ __forceinline__ int xs_slot(int w) { return w & DB_MAX_BEADS; }
 __device__ __forceinline__ int xs_type(int w) { return (int)(((uint32_t)w >> DB_SLOT_BITS) & 31u); }
 __device__ __forceinline__ bool xs_reactive(int w) { return ((uint32_t)w >> 31) != 0u; }
 
+__device__ __forceinline__ int creates_as(int meta) { return meta_reactive(meta) ? meta_type(meta) : 0; }
+
 // Coordinates in units of edge / 65536, rounded down: differences of these 16-bit
 // words wrap as the box does, so the nearest image comes with the subtraction.  Each
-// is low by less than 1.01 units, and a difference off by less than that.
+// is low by less than 1.01 units, and a difference off by less than that.  The second
+// word's upper half holds the type of a reactive bead, 0 for others.
 __device__ __forceinline__ uint32_t quantum(float x, float units) { return (uint32_t)(x * units) & 0xFFFFu; }
-__device__ __forceinline__ uint2 quantise(const Box& X, float x, float y, float z) {
+__device__ __forceinline__ uint2 quantise(const Box& X, float x, float y, float z, int kind) {
     const float units = (float)(65536.0 / X.L);
-    return make_uint2(quantum(x, units) | quantum(y, units) << 16, quantum(z, units));
+    return make_uint2(quantum(x, units) | quantum(y, units) << 16, quantum(z, units) | (uint32_t)kind << 16);
 }
 
 // The box of a bead: the system's own, or in a batch the replica's (BATCH is a

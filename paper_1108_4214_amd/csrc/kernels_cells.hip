@@ -291,7 +291,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_cellsort(const Params* __restrict_
     const float fx = (float)xj.x, fy = (float)xj.y, fz = (float)xj.z;
     list[s0 + r] = j;
     xs[s0 + r] = make_float4(fx, fy, fz, xs_word(j, meta_word(xj)));
-    xq[s0 + r] = quantise(box_of<BATCH>(*Pp, meta_word(xj)), fx, fy, fz);
+    xq[s0 + r] = quantise(box_of<BATCH>(*Pp, meta_word(xj)), fx, fy, fz, creates_as(meta_word(xj)));
 }
 
 void launch_build_cells(db_ctx* c) {

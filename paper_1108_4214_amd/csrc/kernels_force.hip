@@ -297,7 +297,7 @@ __device__ __forceinline__ int stage_quantised(const Box& X, const int* __restri
     char* const column = (char*)&stage[0][threadIdx.x];
     uint32_t at = 0;
     bool over = false;
-    scan_cells_quantised<PARTS>(X, cstart, xq, xi, reach, part, [&](int p, int rem, const uint32_t (&r2)[4]) {
+    scan_cells_quantised<PARTS>(X, cstart, xq, xi, reach, part, [&](int p, int rem, const uint32_t (&r2)[4], const uint32_t (&)[4]) {
         over |= at > LIMIT;
         at = min(at, LIMIT);
 #pragma unroll

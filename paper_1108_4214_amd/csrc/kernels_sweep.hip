@@ -156,25 +156,37 @@ __device__ __forceinline__ bool create_admits(const Params& P, int ti, const Tab
 // S.aoff[n]) by a stream compaction, so that the creation scan runs on full
 // wavefronts.
 
-// LANES threads per listed bead, each scanning a share of every cell run; the
-// group's nominee is the least (r^2, id) of its members' nominees, which is what
-// one thread scanning every run in any order would find.  The listed range is
-// split per XCD; the workgroups step over the tiles of the list, so that a list
-// longer than the grid's share is covered too.  The kernel picks LANES from the
-// list's length: a list of half a million beads or more (the bases of a melted
-// system) fills the GPU with one thread per bead (on the 4M-bead stress case 239
-// against 300 us with two, 377 with four), a short one (a few melted bases among
-// hybridized duplexes) needs sixteen to fill it at all.
-__device__ __forceinline__ int create_lanes_for(int nl) {
+// LANES threads per listed bead, each scanning a share of the cells; the group's
+// nominee is the least (r^2, id) of its members' nominees, which is what one thread
+// scanning every run in any order would find.  The listed range is split per XCD; the
+// workgroups step over the tiles of the list, so that a list longer than the grid's
+// share is covered too.
+// One thread per bead, or four, scan the quantised copy of the positions with the
+// reactive beads' types beside them, and keep the places of the candidates of a wanted
+// type in their LDS columns.  It is bound by instructions, as the list build is.  Per
+// sweep against the float scan (one to sixteen threads by the list's length): 126 ->
+// 75 us with every base of 1.7M melted beads listed, 76 -> 35 us in a batch of 24
+// duplex boxes, 16.8 -> 9.5 us with 40 beads (one thread's chain of loads: nine rows
+// before, three now).
+// The kernel picks LANES from the list's length: one thread per bead fills the GPU from
+// 2^16 listed beads (one against four: 75 and 113 us with 850k listed, 36 and 38 with
+// 100k, 33 and 20 with 30k).  With a creation distance beyond one cell edge the float
+// scan of 5 x 5 x 5 cells serves, and a short list takes up to sixteen threads (1M-bead
+// case of the 1-bead model, about 30k listed: 52 / 33 / 24 / 20 us with 2 / 4 / 8 / 16).
+template <bool BATCH>
+__device__ __forceinline__ int create_lanes_for(const Params& P, int nl) {
+    if (!(BATCH ? P.rep[0] : P.box).wide_create) return nl >= (1 << 16) ? 1 : 4;
     return nl >= (1 << 19) ? 1 : (nl >= (1 << 18) ? 2 : (nl >= (1 << 17) ? 4 : (nl >= (1 << 16) ? 8 : 16)));
 }
 
-// candidates a thread queues before examining them (more are examined at once)
-constexpr int CREATE_QUEUE = 8;
+// candidates a thread queues before examining them; four rows more take the scan's
+// writes of candidates that are not kept
+constexpr int CREATE_ROWS = 12;
 
 template <bool BATCH, int LANES>
 __device__ __forceinline__ void nominate_create_one(const Params& P, const int n, const Bank& B,
-                                                    const int* __restrict__ cstart, const float4* __restrict__ xs,
+                                                    const int* __restrict__ cstart, const int* __restrict__ clist,
+                                                    const float4* __restrict__ xs, const uint2* __restrict__ xq,
                                                     const SweepBuf& S, const int i, const int lane,
                                                     int (*queue)[DB_BLOCK]) {
     const double4 xi = B.x[i];
@@ -184,12 +196,41 @@ __device__ __forceinline__ void nominate_create_one(const Params& P, const int n
     const int gi = meta_gid(xi);
     int best = -1, best_rule = -1, best_bt = 0, best_g = 0;
     double best_r2 = 0.0;
+    const float cut2 = X.pf_create2;
+    // types and reactivity ride in the scan's words: most candidates are rejected
+    // before anything else of them is read
+    const uint32_t partner_types = create_partner_types(P, ti);
+    // The places of the candidates of a wanted type, kept in the thread's column and
+    // turned into slots after the scan; cnt < 0: not scanned, or more than the rows hold
+    const int tid = threadIdx.x;
+    int cnt = -1;
+    if constexpr (LANES == 1 || LANES == 4) {   // what the quantised scan splits into
+        const float reach = sqrtf(cut2) * 1.000001f;
+        const uint32_t cutq = X.wide_create ? 0u : quantised_cut(X, reach);
+        if (cutq) {
+            const uint32_t kinds = partner_types & ~1u;   // kind 0 is no partner
+            int at = 0;
+            bool over = false;
+            scan_cells_quantised<LANES>(X, cstart, xq, xi, reach, lane,
+                                        [&](int p, int rem, const uint32_t (&r2)[4], const uint32_t (&z)[4]) {
+                over |= at > CREATE_ROWS;
+                at = min(at, CREATE_ROWS);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const bool in_run = q == 0 || q < rem;
+                    queue[at][tid] = p + q;
+                    at += in_run & (r2[q] < cutq) & (((kinds >> (z[q] >> 16)) & 1u) != 0u);
+                }
+            });
+            // the float scan splits otherwise: the threads of a bead go over to it together
+            int fits = !over && at <= CREATE_ROWS;
+#pragma unroll
+            for (int o = 1; o < LANES; o <<= 1) fits &= __shfl_xor(fits, o, 64);
+            if (fits) cnt = at;
+        }
+    }
     const Tab Ti = load_tab_all(B, n, i);
     {
-        const float cut2 = X.pf_create2;
-        // types and reactivity ride in the scan's words: most candidates are
-        // rejected before anything else of them is read
-        const uint32_t partner_types = create_partner_types(P, ti);
         // the beads two bonds away, gathered once for the distance-3 test
         int two[DB_MAXB * DB_MAXB];
 #pragma unroll
@@ -259,19 +300,33 @@ __device__ __forceinline__ void nominate_create_one(const Params& P, const int n
                 best_bt = bti;
             }
         };
-        const int tid = threadIdx.x;
         int nq = 0;
         auto visit = [&](int j, int w) {
             if (!xs_reactive(w) || !((partner_types >> xs_type(w)) & 1u)) return;
-            if (nq == CREATE_QUEUE) {   // full: examine the queue
-                for (int k = 0; k < CREATE_QUEUE; ++k) examine(queue[k][tid]);
+            if (nq == CREATE_ROWS) {   // full: examine the queue
+                for (int k = 0; k < CREATE_ROWS; ++k) examine(queue[k][tid]);
                 nq = 0;
             }
             queue[nq][tid] = j;
             ++nq;
         };
-        if (X.wide_create) scan_cells_wide<LANES, 1>(X, cstart, xs, i, xi, cut2, visit, lane);
-        else scan_cells<LANES>(X, cstart, xs, i, xi, cut2, visit, lane);
+        if (cnt >= 0) {
+            for (int k0 = 0; k0 < cnt; k0 += 4) {
+                int j[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) j[q] = clist[queue[min(k0 + q, cnt - 1)][tid]];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if ((k0 + q < cnt) & (j[q] != i)) {
+                        queue[nq][tid] = j[q];
+                        ++nq;
+                    }
+                }
+            }
+        } else {
+            if (X.wide_create) scan_cells_wide<LANES, 1>(X, cstart, xs, i, xi, cut2, visit, lane);
+            else scan_cells<LANES>(X, cstart, xs, i, xi, cut2, visit, lane);
+        }
         for (int k = 0; k < nq; ++k) examine(queue[k][tid]);
     }
     // the group's least (r^2, id), exchanged within the aligned group of lanes
@@ -299,7 +354,8 @@ __device__ __forceinline__ void nominate_create_one(const Params& P, const int n
 
 template <bool BATCH, int LANES>
 __device__ __forceinline__ void nominate_create_all(const Params& P, const Bank& B, const int* __restrict__ cstart,
-                                                    const float4* __restrict__ xs, const SweepBuf& S, int nl,
+                                                    const int* __restrict__ clist, const float4* __restrict__ xs,
+                                                    const uint2* __restrict__ xq, const SweepBuf& S, int nl,
                                                     int (*queue)[DB_BLOCK]) {
     static_assert(64 % LANES == 0 && DB_BLOCK % 64 == 0, "groups lie within a wavefront");
     const int ntile = (int)(((long long)nl * LANES + DB_BLOCK - 1) / DB_BLOCK);
@@ -308,23 +364,25 @@ __device__ __forceinline__ void nominate_create_all(const Params& P, const Bank&
         const int t = (int)(pos / LANES);
         const int lane = (int)(pos % LANES);
         // the lanes of a group share t: they take this branch together
-        if (t < nl) nominate_create_one<BATCH, LANES>(P, P.n, B, cstart, xs, S, S.aoff[t], lane, queue);
+        if (t < nl) nominate_create_one<BATCH, LANES>(P, P.n, B, cstart, clist, xs, xq, S, S.aoff[t], lane, queue);
     }
 }
 
 template <bool BATCH>
 __global__ __launch_bounds__(DB_BLOCK) void k_nominate_create(const Params* __restrict__ Pp, Bank B,
                                                               const int* __restrict__ cstart,
-                                                              const float4* __restrict__ xs, SweepBuf S) {
+                                                              const int* __restrict__ clist,
+                                                              const float4* __restrict__ xs,
+                                                              const uint2* __restrict__ xq, SweepBuf S) {
     const Params& P = *Pp;
     const int nl = S.aoff[P.n];
-    __shared__ int queue[CREATE_QUEUE][DB_BLOCK];   // a column per thread
-    switch (create_lanes_for(nl)) {   // uniform over the grid
-        case 1: nominate_create_all<BATCH, 1>(P, B, cstart, xs, S, nl, queue); break;
-        case 2: nominate_create_all<BATCH, 2>(P, B, cstart, xs, S, nl, queue); break;
-        case 4: nominate_create_all<BATCH, 4>(P, B, cstart, xs, S, nl, queue); break;
-        case 8: nominate_create_all<BATCH, 8>(P, B, cstart, xs, S, nl, queue); break;
-        default: nominate_create_all<BATCH, 16>(P, B, cstart, xs, S, nl, queue); break;
+    __shared__ int queue[CREATE_ROWS + 4][DB_BLOCK];   // a column per thread
+    switch (create_lanes_for<BATCH>(P, nl)) {   // uniform over the grid
+        case 1: nominate_create_all<BATCH, 1>(P, B, cstart, clist, xs, xq, S, nl, queue); break;
+        case 2: nominate_create_all<BATCH, 2>(P, B, cstart, clist, xs, xq, S, nl, queue); break;
+        case 4: nominate_create_all<BATCH, 4>(P, B, cstart, clist, xs, xq, S, nl, queue); break;
+        case 8: nominate_create_all<BATCH, 8>(P, B, cstart, clist, xs, xq, S, nl, queue); break;
+        default: nominate_create_all<BATCH, 16>(P, B, cstart, clist, xs, xq, S, nl, queue); break;
     }
 }
 
@@ -841,7 +899,7 @@ static void sweep_kernels(db_ctx* c, const Bank& B, unsigned g, int64_t step) {
     hipLaunchKernelGGL(k_nominate_break<BATCH>, dim3(g), dim3(DB_BLOCK), 0, s, c->dp, B, c->sw);
     launch_compact(c->sw.act, c->n, c->sw.aoff, c->sw.aoff + c->n, c->cells.blocksum, s);
     hipLaunchKernelGGL(k_nominate_create<BATCH>, dim3(g), dim3(DB_BLOCK), 0, s, c->dp, B, c->cells.start,
-                       c->cells.xs, c->sw);
+                       c->cells.list, c->cells.xs, c->cells.xq, c->sw);
     hipLaunchKernelGGL(k_resolve<BATCH>, dim3(g), dim3(DB_BLOCK), 0, s, c->dp, B, c->sw, step);
     hipLaunchKernelGGL(k_apply<BATCH>, dim3(g), dim3(DB_BLOCK), 0, s, c->dp, B, c->sw, step, c->err_d);
 }

@@ -189,3 +189,27 @@ def test_list_build_matches_oracle(n, L, precision):
     o = oracle.Oracle.from_system(s, ff, synth.RuleSet(every=0), seed=1, generate=False)
     ok, msg = forces_close(_list_forces(s, ff, precision, 1), o.forces(), 1e-11 if precision == 0 else 1e-5)
     assert ok, msg
+
+
+@pytest.mark.parametrize("n,L", [(2, 3.1), (250, 4.7), (2500, 9.0), (900, 40.0), (3000, 3000.0), (140000, 38.0)])
+def test_creation_scan_matches_oracle(n, L):
+    """One sweep over beads of four types, part of them not reactive, from three cells per edge to hundreds: a cloud
+    about the corner of the box (more candidates than a thread's rows in the small boxes, none in the large), rules
+    with and without a wildcard, lists of one thread and of four per bead.  The bonds are the oracle's."""
+    rng = np.random.default_rng(n + 7)
+    x = rng.uniform(0.0, L, size=(n, 3))
+    k = n // 3
+    x[:k] = np.mod(rng.normal(0.0, max(0.9, 0.3 * k ** (1.0 / 3.0)), size=(k, 3)), L)
+    kind = rng.integers(1, 5, size=n).astype(np.int32)
+    s = synth.System(L=L, x=synth.wrap(x, L), v=np.zeros((n, 3)), type=kind,
+                     reactive=(rng.uniform(size=n) < 0.9).astype(np.uint8), bonds=np.zeros((0, 4), dtype=np.int32))
+    if n == 2:
+        s.x[:] = [[0.05, 1.0, 3.05], [3.05, 1.0, 0.05]]
+        s.type[:], s.reactive[:] = [1, 2], 1
+    rules = synth.RuleSet(every=1, rules=[("create", 1, 1, 2, 0.99, 1.0), ("create", 2, 0, 3, 0.7, 0.6)])
+    g, o = both(s, synth.ForceField(), rules, seed=3)
+    g.sweep_now()
+    o.sweep_now()
+    assert np.array_equal(g.bonds(), o.bonds())
+    if L < 100:
+        assert len(g.bonds()) > 0
