@@ -191,11 +191,13 @@ def test_list_build_matches_oracle(n, L, precision):
     assert ok, msg
 
 
-@pytest.mark.parametrize("n,L", [(2, 3.1), (250, 4.7), (2500, 9.0), (900, 40.0), (3000, 3000.0), (140000, 38.0)])
+@pytest.mark.parametrize("n,L", [(2, 3.1), (250, 4.7), (2500, 9.0), (900, 40.0), (3000, 3000.0), (4096, 30.0),
+                                 (4097, 30.0), (32768, 40.0), (32769, 40.0), (140000, 38.0)])
 def test_creation_scan_matches_oracle(n, L):
     """One sweep over beads of four types, part of them not reactive, from three cells per edge to hundreds: a cloud
     about the corner of the box (more candidates than a thread's rows in the small boxes, none in the large), rules
-    with and without a wildcard, lists of one thread and of four per bead.  The bonds are the oracle's."""
+    with and without a wildcard, lists of one thread and of four per bead, flags
+    that fill a scan's tiles to the last and begin one more.  The bonds are the oracle's."""
     rng = np.random.default_rng(n + 7)
     x = rng.uniform(0.0, L, size=(n, 3))
     k = n // 3
