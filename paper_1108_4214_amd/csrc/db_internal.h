@@ -235,7 +235,7 @@ struct Cells {
     int* start;       // [ncell + 1]
     int* list;        // [n] slots, cell by cell, ascending within a cell
     float4* xs;       // [n + DB_XS_PAD] in list order: float x, y, z and (bits) slot | type << 26 | reactive << 31
-    uint2* xq;        // [n + DB_XS_PAD] in list order: x | y << 16, z, in units of edge / 65536 (rounded down)
+    uint2* xq;        // [n + DB_XS_PAD] in list order: x | y << 16, z | kind << 16 (quantise)
     int* cellid;      // [n]
     int* rank;        // [n] place of the bead among the beads of its cell
     int* unsorted;    // [n] the list before the ordering inside each cell
