@@ -285,30 +285,31 @@ constexpr int scan_rows() { return PARTS == 1 ? 28 : 18; }
 // order: every candidate is written into the row of the next kept one, which a kept
 // one advances, so the scan has no branch per candidate.  counted is advanced by
 // the candidates with a squared distance below count_cut.  Returns their number; more
-// than ROWS - 4: not all were kept.
-template <int ROWS, int PARTS = 1>
+// than ROWS - 4: not all were kept (the first ROWS - 4 were).  SKIP leaves out the first
+// skip of them.
+template <int ROWS, int PARTS = 1, bool SKIP = false>
 __device__ __forceinline__ int stage_quantised(const Box& X, const int* __restrict__ cstart,
                                                const uint2* __restrict__ xq, const double4& xi, double reach,
                                                uint32_t cutq, int (*stage)[DB_BLOCK], int part = 0,
-                                               uint32_t count_cut = 0, int* counted = nullptr) {
+                                               uint32_t count_cut = 0, int* counted = nullptr, int skip = 0) {
     // the row of the next kept candidate, as a byte offset; past the rows for kept
     // ones the four after them are written over and over
-    constexpr uint32_t ROW = sizeof(int) * DB_BLOCK, LIMIT = (ROWS - 4) * ROW;
+    constexpr int ROW = sizeof(int) * DB_BLOCK, LIMIT = (ROWS - 4) * ROW;
     char* const column = (char*)&stage[0][threadIdx.x];
-    uint32_t at = 0;
+    int at = SKIP ? -skip * ROW : 0;
     bool over = false;
     scan_cells_quantised<PARTS>(X, cstart, xq, xi, reach, part, [&](int p, int rem, const uint32_t (&r2)[4], const uint32_t (&)[4]) {
         over |= at > LIMIT;
         at = min(at, LIMIT);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            *(int*)(column + at) = p + q;
+            *(int*)(column + (SKIP ? max(at, 0) : at)) = p + q;
             const bool in_run = q == 0 || q < rem;   // a group holds one entry of its run at least
-            at += (in_run & (r2[q] < cutq)) ? ROW : 0u;
+            at += (in_run & (r2[q] < cutq)) ? ROW : 0;
             if (counted) *counted += (in_run & (r2[q] < count_cut)) ? 1 : 0;
         }
     });
-    return over ? ROWS : (int)(at / ROW);
+    return over ? ROWS : at / ROW;
 }
 
 // the staged places turned into slots, in place and in order, without the bead itself
@@ -2110,8 +2111,9 @@ __global__ __launch_bounds__(DB_BLOCK) void k_step_tile(const Params* __restrict
 // the scan, as the list build is (instructions and L1 accesses).  500k duplex beads,
 // energies in FP64: 75 us and 5 us for the final sum, against 400 us for a serial loop
 // over the candidates' double positions and 247 us for a final sum by six threads;
-// 100k beads of DPD solution in FP32 104 + 5 (46 once reordered: it waits for
-// neighbours' positions and velocities from the other dies' memory) against 644 + 51;
+// 100k beads of DPD solution in FP32 74 + 5 (46 once reordered and evenly spread: it
+// waits for neighbours' data from the other dies' memory, and for crowded beads)
+// against 644 + 51;
 // 191k duplex beads, forces in FP32: 28 us against 42 for a list build and a force pass.
 template <typename R, int MODE, bool BATCH, int PAIR>
 __global__ __launch_bounds__(DB_BLOCK) void k_eval(const Params* __restrict__ Pp, Bank B, Halo H,
@@ -2176,11 +2178,11 @@ __global__ __launch_bounds__(DB_BLOCK) void k_eval(const Params* __restrict__ Pp
                     pair_sep<R, MODE>(P, dx, dy, dz, rc2, a);
                 }
             };
+            const double list_reach = sqrt(P.rnl2) + X.pf_slack;
             int raw = EV_STAGE + 1;
             bool crowded = true;   // more than a Verlet list's capacity of beads may be within its cutoff
             const uint32_t cutq = quantised_cut(X, reach);
             if (cutq) {
-                const double list_reach = sqrt(P.rnl2) + X.pf_slack;
                 int listed = 0;
                 if (MODE == MODE_FORCE)
                     raw = stage_quantised<EV_STAGE + 4, 1>(X, cstart, xq, xi, list_reach, cutq, lds.stage, 0,
@@ -2191,8 +2193,8 @@ __global__ __launch_bounds__(DB_BLOCK) void k_eval(const Params* __restrict__ Pp
             }
             ExclSet E;   // after the scan, for its registers
             gather_excl(P, B, n, i, E);
-            if (raw <= EV_STAGE) {
-                const int cnt = settle_staged(clist, i, raw, lds.stage, E);
+            for (int skip = 0; cutq;) {
+                const int cnt = settle_staged(clist, i, min(raw, EV_STAGE), lds.stage, E);
                 for (int k0 = 0; k0 < cnt; k0 += 4) {
                     int j[4];
                     double4 xj[4];
@@ -2207,7 +2209,16 @@ __global__ __launch_bounds__(DB_BLOCK) void k_eval(const Params* __restrict__ Pp
                     for (int q = 0; q < 4; ++q)
                         if (k0 + q < cnt) pair(xj[q], vj[q]);
                 }
-            } else {   // crowded, or a box the quantised scan does not serve
+                if (raw <= EV_STAGE) break;
+                // more than the rows hold: the next rows' worth.  (Random solvent at density 3
+                // has such a bead in every few thousand, and the pass lasts as long as they
+                // do: 104 us with the float scan for them, 74 so.  The list build, whose scan
+                // the second one costs registers, 72 -> 81 us at 1M beads, keeps that.)
+                skip += EV_STAGE;
+                raw = stage_quantised<EV_STAGE + 4, 1, true>(X, cstart, xq, xi, MODE == MODE_FORCE ? list_reach : reach,
+                                                             cutq, lds.stage, 0, 0, nullptr, skip);
+            }
+            if (!cutq) {   // a box the quantised scan does not serve
                 scan_cells(X, cstart, xs, i, xi, cut2, [&](int j, int) {
                     if (!E.has(j)) pair(B.x[j], vel_of(j));
                 });
