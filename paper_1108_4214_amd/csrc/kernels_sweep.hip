@@ -939,6 +939,22 @@ void launch_generate_all(db_ctx* c) {
 // return them, and no sort of the whole list remains (on the host it took most of a
 // readout: 205k beads with 630k entries, 13 of 20 ms).
 //
+// A dihedral that names bead i several times (the ends may be one bead) is in its table
+// as often; this says whether entry k stands for the dihedral: every so-manyth of the
+// bead's equal entries does.
+__device__ __forceinline__ bool owns_dihedral(const Bank& B, int n, int i, int k, const int4& e) {
+    if (e.x != i) return false;
+    const int times = 1 + (e.y == i) + (e.z == i) + (e.w == i);
+    if (times == 1) return true;
+    const int t = B.dt[k * n + i];
+    int before = 0;
+    for (int m = 0; m < k; ++m) {
+        const int4 q = B.dih[m * n + i];
+        before += q.x == e.x && q.y == e.y && q.z == e.z && q.w == e.w && B.dt[m * n + i] == t;
+    }
+    return before % times == 0;
+}
+
 // Counts of the three kinds per id, at cnt[kind * (n + 1) + id].
 __global__ __launch_bounds__(DB_BLOCK) void k_count_owned(int n, Bank B, const int* __restrict__ slot_of_gid,
                                                           int* __restrict__ cnt) {
@@ -951,7 +967,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_count_owned(int n, Bank B, const i
     const int na = B.na[i];
     for (int k = 0; k < na; ++k) c1 += B.ang[k * n + i].x == i;
     const int nd = B.nd[i];
-    for (int k = 0; k < nd; ++k) c2 += B.dih[k * n + i].x == i;
+    for (int k = 0; k < nd; ++k) c2 += owns_dihedral(B, n, i, k, B.dih[k * n + i]);
     cnt[g] = c0;
     cnt[n + 1 + g] = c1;
     cnt[2 * (n + 1) + g] = c2;
@@ -1019,7 +1035,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_write_owned(int n, Bank B, const i
     const int nd = B.nd[i];
     auto dihedral_row = [&](int k, int (&r)[4]) {   // (b, c, d, type), false: another end's
         const int4 e = B.dih[k * n + i];
-        if (e.x != i) return false;
+        if (!owns_dihedral(B, n, i, k, e)) return false;
         r[0] = meta_gid(B.x[e.y]);
         r[1] = meta_gid(B.x[e.z]);
         r[2] = meta_gid(B.x[e.w]);

@@ -238,3 +238,21 @@ def test_state_into_device_buffers(want):
     first = {"v": -np.ones((n, 3)), "one buffer": v}.get(want, x)
     assert np.array_equal(room[:n], first)
     assert np.array_equal(room[n:], v if want in ("both", "v") else -np.ones((n, 3)))
+
+
+def test_repeated_members_of_a_dihedral_come_back_once():
+    """Dihedrals that name a bead twice (it holds such an entry twice), one of them set twice: the lists read from the
+    device, and read again after they went back to it with an edit, are those set."""
+    import paper_1108_4214_amd as pk
+    rng = np.random.default_rng(5)
+    d = np.array([[1, 0, 1, 2, 0], [1, 0, 1, 2, 0], [2, 0, 1, 2, 0], [1, 0, 1, 2, 3], [1, 0, 1, 1, 3], [1, 1, 2, 1, 3],
+                  [3, 2, 2, 0, 3]], dtype=np.int32)
+    s = synth.System(L=12.0, x=rng.uniform(0.0, 12.0, size=(4, 3)), v=np.zeros((4, 3)), type=np.ones(4, dtype=np.int32),
+                     reactive=np.zeros(4, dtype=np.uint8), bonds=np.zeros((0, 4), dtype=np.int32), dihedrals=d)
+    g = pk.System(s.n, s.L, 3).configure(s, synth.ForceField(), synth.RuleSet(every=0))
+    want = d[np.lexsort((d[:, 0], d[:, 4], d[:, 3], d[:, 2], d[:, 1]))]
+    for _ in range(2):
+        g.sweep_now()
+        g.set_step(g.stats()["steps"] + 1)
+        assert np.array_equal(g.dihedrals(), want)
+        pk.db_set_reactive(g.ctx, np.zeros(4, dtype=np.uint8))
