@@ -1662,7 +1662,9 @@ int db_checkpoint_save(db_ctx* c, void* buf, size_t bytes) {
     h.list_valid = c->list_valid;
     h.tiles_valid = c->tiles_valid;
     h.regions_valid = c->regions_valid;
-    h.halo_force = c->halo_force;
+    // a library that codes the halo's entries otherwise honours this flag by rebuilding
+    // it; it would take the codes in the saved arena for its own
+    h.halo_force = 1;
     h.halo_sweep = c->halo_sweep;
     h.have_topology = c->have_topology;
     h.ledger = c->ledger;

@@ -145,3 +145,17 @@ def test_checkpoint_rejects_another_system():
     x1, v1 = other.state()
     assert np.array_equal(x0, x1) and np.array_equal(v0, v1)
     other.step(2)
+
+
+def test_checkpoint_asks_its_reader_to_rebuild_the_halo():
+    """The halo's codes in a checkpoint are this library's; one that codes them otherwise reads the file too and
+    rebuilds the halo where the header says so.  The flag is the fourth of the header's eight bytes after its
+    eight-byte magic, 4 ints, seed, edge, arena size, skin, 8 ints and 23 counters."""
+    import paper_1108_4214_amd as pk
+    s = synth.small_duplexes()
+    g = pk.System(s.n, s.L, 3).configure(s, synth.ff_t2(), synth.rules_t2())
+    g.step(12)   # lists and halo are current
+    buf = pk.db_checkpoint_save(g.ctx)
+    flags = buf[8 + 16 + 4 * 8 + 32 + 23 * 8:][:8]
+    assert np.all(flags <= 1) and flags[0] == 1   # the list is valid
+    assert flags[3] == 1
