@@ -194,6 +194,7 @@ __device__ __forceinline__ void dpd_pair(const Params& P, const Box& X, const do
     } else {
         ir = r_rsqrt<R>(r2);
         r = r2 * ir;
+        if (ENERGY) r = r2 > (R)0 ? r : (R)0;   // beads on one point have an energy, if no force
     }
     const R w = (R)1.0 - r * (R)P.inv_rc;
     R f = (R)P.dpd_a * w;

@@ -256,3 +256,18 @@ def test_repeated_members_of_a_dihedral_come_back_once():
         g.set_step(g.stats()["steps"] + 1)
         assert np.array_equal(g.dihedrals(), want)
         pk.db_set_reactive(g.ctx, np.zeros(4, dtype=np.uint8))
+
+
+@pytest.mark.parametrize("gamma", [0.0, 20.0])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_dpd_energy_of_beads_on_one_point(precision, gamma):
+    """The soft pair energy and its virial are finite at zero separation (a rc / 2 and 0), where the force has no
+    direction.  The second pair adds a rc / 2 (1 - 1/4)^2 and the virial a (1 - 1/4) / 4."""
+    import paper_1108_4214_amd as pk
+    s = synth.System(L=9.0, x=np.array([[1.0, 2.0, 3.0], [1.0, 2.0, 3.0], [6.0, 6.0, 6.0], [6.25, 6.0, 6.0]]),
+                     v=np.zeros((4, 3)), type=np.ones(4, dtype=np.int32), reactive=np.zeros(4, dtype=np.uint8),
+                     bonds=np.zeros((0, 4), dtype=np.int32))
+    g = pk.System(s.n, s.L, 3, precision).configure(s, synth.ff_dpd(gamma_dpd=gamma), synth.RuleSet(every=0))
+    e = g.energy()
+    tol = 1e-12 if precision == 0 else 1e-5   # as in the other evaluations
+    assert abs(e[1] - 12.5 * (1.0 + 0.5625)) <= 20.0 * tol and abs(e[5] - 25.0 * 0.75 * 0.25) <= 20.0 * tol, e
