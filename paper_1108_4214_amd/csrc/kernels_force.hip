@@ -652,8 +652,10 @@ __device__ __forceinline__ void angle_share(const Coef<R>& C, bool centre, int t
     const R iru = r_rsqrt<R>(ru2), irw = r_rsqrt<R>(rw2);
     const R q = iru * irw;
     const R cs = sg * (dot(s1, w) * q);   // cos(theta)
-    const V3<R> cr = cross(s1, w);
-    const R sn2 = dot(cr, cr) * (q * q);
+    V3<R> cr = cross(s1, w);
+    // scaled before it is squared: the square of q is beyond float at 1e-10 of separation
+    cr = V3<R>{cr.x * q, cr.y * q, cr.z * q};
+    const R sn2 = dot(cr, cr);
     const R K = C.aK[t], pth = C.aPm[t];   // pth = pi - theta0
     R ratio, del = (R)0;
     if (cs < (R)0 && sn2 <= (R)0.5) {

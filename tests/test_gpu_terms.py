@@ -271,3 +271,24 @@ def test_dpd_energy_of_beads_on_one_point(precision, gamma):
     e = g.energy()
     tol = 1e-12 if precision == 0 else 1e-5   # as in the other evaluations
     assert abs(e[1] - 12.5 * (1.0 + 0.5625)) <= 20.0 * tol and abs(e[5] - 25.0 * 0.75 * 0.25) <= 20.0 * tol, e
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_angles_of_beads_close_together(precision):
+    """Separations down to 1e-16 at the corner of the box, where positions resolve them: a wide and a slight bend, both
+    ends alike.  A force is good to some twenty roundings over the sine of the bend, the oracle's to as many of its own,
+    relative to the largest of the angle."""
+    for size in (1e-3, 1e-8, 1e-11, 1e-16):
+        for bend in (1e-3, 0.3, 1.2):
+            x = size * np.array([[3.0, 1.0, 2.0], [2.0, 1.0, 2.0],
+                                 [2.0 - math.cos(bend), 1.0 + math.sin(bend), 2.0]])
+            s = synth.System(L=9.0, x=x, v=np.zeros((3, 3)), type=np.ones(3, dtype=np.int32),
+                             reactive=np.zeros(3, dtype=np.uint8),   # bonded, so that no pair interacts
+                             bonds=np.array([[0, 1, 1, 1], [1, 2, 1, 1]], dtype=np.int32),
+                             angles=np.array([[1, 0, 1, 2]], dtype=np.int32))
+            ff = synth.ForceField(gamma=0.0, exclude_depth=2)
+            ff.bonds, ff.angles = {1: (0.0, 1.0)}, {1: (10.0, math.pi)}
+            g, o = both(s, ff, synth.RuleSet(every=0), precision=precision, generate=False)
+            f, want = g.forces(), o.forces()
+            tol = 40.0 * (2.0 ** -53 if precision == 0 else 2.0 ** -24) / math.sin(bend)
+            assert np.abs(f - want).max() <= tol * np.abs(want).max(), (size, bend, f, want)
