@@ -221,6 +221,7 @@ __device__ __forceinline__ void scan_cells_quantised(const Box& X, const int* __
         return c;
     };
     static_assert((uint64_t)DB_MAX_BEADS * sizeof(uint2) < (1ull << 32), "places as 32-bit byte offsets");
+    static_assert(4 <= DB_XS_PAD, "four entries from the list's end lie within the padded copy");
     auto group = [&](const Four& c, int p, int rem) {
         const uint32_t xy[4] = {c.a.x, c.a.z, c.b.x, c.b.z}, z[4] = {c.a.y, c.a.w, c.b.y, c.b.w};
         uint32_t r2[4];
@@ -269,7 +270,7 @@ __device__ __forceinline__ void scan_cells_quantised(const Box& X, const int* __
         for (;;) {
             int now, rem;
             advance(now, rem);
-            const Four d = fetch(p);   // past the last run too: a place in the list all the same
+            const Four d = fetch(p);   // past the last run too: from a run's end at most, so within the padding
             group(c, now, rem);
             if (!(p < end)) break;
             advance(now, rem);
@@ -311,7 +312,7 @@ __device__ __forceinline__ void scan_cells_quantised(const Box& X, const int* __
             e[k] = any ? (right ? t3 : t2) : s[k];
             if (PARTS > 1 && k == 2) {   // the thread's share of the middle row
                 const int chunk = ((e[k] - s[k] + 4 * PARTS - 1) / (4 * PARTS)) * 4;
-                s[k] += part * chunk;
+                s[k] = min(s[k] + part * chunk, e[k]);   // an empty share begins within the run all the same
                 e[k] = min(e[k], s[k] + chunk);
             }
         }
