@@ -2196,6 +2196,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_eval(const Params* __restrict__ Pp
             }
             ExclSet E;   // after the scan, for its registers
             gather_excl(P, B, n, i, E);
+            bool serial = !cutq;   // a box the quantised scan does not serve
             for (int skip = 0; cutq;) {
                 const int cnt = settle_staged(clist, i, min(raw, EV_STAGE), lds.stage, E);
                 for (int k0 = 0; k0 < cnt; k0 += 4) {
@@ -2218,10 +2219,19 @@ __global__ __launch_bounds__(DB_BLOCK) void k_eval(const Params* __restrict__ Pp
                 // do: 104 us with the float scan for them, 74 so.  The list build, whose scan
                 // the second one costs registers, 72 -> 81 us at 1M beads, keeps that.)
                 skip += EV_STAGE;
+                int within = 0;
                 raw = stage_quantised<EV_STAGE + 4, 1, true>(X, cstart, xq, xi, MODE == MODE_FORCE ? list_reach : reach,
-                                                             cutq, lds.stage, 0, 0, nullptr, skip);
+                                                             cutq, lds.stage, 0, cutq, &within, skip);
+                // A scan per 28 neighbours grows with their square: in a collapsed system,
+                // thousands within reach, the float scan takes them all in one (8,000 beads
+                // within 0.9, FP64 energies: 124 ms by repeated scans, 5 so)
+                if (within > DB_NLCAP) {
+                    a = Acc<R>();   // nothing but the pairs so far
+                    serial = true;
+                    break;
+                }
             }
-            if (!cutq) {   // a box the quantised scan does not serve
+            if (serial) {
                 scan_cells(X, cstart, xs, i, xi, cut2, [&](int j, int) {
                     if (!E.has(j)) pair(B.x[j], vel_of(j));
                 });

@@ -292,3 +292,34 @@ def test_angles_of_beads_close_together(precision):
             f, want = g.forces(), o.forces()
             tol = 40.0 * (2.0 ** -53 if precision == 0 else 2.0 ** -24) / math.sin(bend)
             assert np.abs(f - want).max() <= tol * np.abs(want).max(), (size, bend, f, want)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_energy_of_a_collapsed_system(precision):
+    """Thousands of beads within reach of each other: the oracle's energies (sums of 2e6 soft pairs, each good to some
+    twenty roundings), and a time that grows with the neighbours of a bead (3.8 times from 2,000 to 8,000 beads, which
+    do not fill the GPU) and not with their square (14 times, by a scan for every 28 of them)."""
+    import time
+    import paper_1108_4214_amd as pk
+    least = []
+    for n in (2000, 8000):
+        rng = np.random.default_rng(n)
+        d = rng.normal(size=(n, 3))
+        d *= 0.45 * rng.uniform(size=(n, 1)) ** (1.0 / 3.0) / np.linalg.norm(d, axis=1)[:, None]
+        s = synth.System(L=20.0, x=10.0 + d, v=np.zeros_like(d), type=np.ones(n, dtype=np.int32),
+                         reactive=np.zeros(n, dtype=np.uint8), bonds=np.zeros((0, 4), dtype=np.int32))
+        ff = synth.ff_dpd(gamma_dpd=0.0)
+        g = pk.System(n, s.L, 3, precision).configure(s, ff, synth.RuleSet(every=0))
+        e = g.energy()
+        if n == 2000:
+            import oracle
+            o = oracle.Oracle.from_system(s, ff, synth.RuleSet(every=0), seed=3).energy()
+            tol = 1e-12 if precision == 0 else 1e-5
+            assert np.all(np.abs(e - o) <= 10 * tol * np.maximum(1.0, np.abs(o))), (e, o)
+        t = []
+        for _ in range(5):
+            t0 = time.perf_counter()
+            g.energy()
+            t.append(time.perf_counter() - t0)
+        least.append(min(t))
+    assert least[1] < 8.0 * least[0], least
