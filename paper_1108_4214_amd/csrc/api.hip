@@ -9,8 +9,8 @@
 // Each step kernel records the largest speed, and the sum of dt * max speed bounds
 // the largest displacement.  Past half the skin (list cutoff minus pair cutoff) some
 // pair could be missed: a step kernel whose input is beyond that bound stores
-// nothing, so the block ends there by itself, the host sees where from the block's
-// report, and the next block starts from that step with a fresh list.  The interval
+// nothing, so the block ends there by itself, its report tells the host how many
+// steps were stored, and the next block starts from that step with a fresh list.  The interval
 // adapts to the speeds seen, so that this is rare.  With DPD the pair friction
 // decorrelates velocities within a few steps, so the motion is diffusive and the
 // speed bound far too cautious: there the step kernels record the largest
@@ -54,7 +54,7 @@ const double kSkinDefaultDPD = 0.02;
 // host memory the device writes its end-of-block report into (mapped, pinned)
 struct Pinned {
     int err;
-    int pad;
+    int stored;                    // steps of the block that were stored
     float vmax2[kMaxBlock];        // largest |v|^2 (DPD: squared displacement) after each step of the block
     unsigned long long stats[8];
     double energy[6];
@@ -63,8 +63,9 @@ struct Pinned {
 };
 
 // the block's maxima go to the host and their words are cleared for the next block
-__global__ void k_report(float* __restrict__ vmax2, int len, const int* __restrict__ err,
-                         const unsigned long long* __restrict__ stats, int with_stats, Pinned* __restrict__ out) {
+__global__ void k_report(float* __restrict__ vmax2, int len, const int* __restrict__ stored,
+                         const int* __restrict__ err, const unsigned long long* __restrict__ stats,
+                         int with_stats, Pinned* __restrict__ out) {
     int q = threadIdx.x;
     if (q < len) {
         float m = 0.0f;
@@ -74,7 +75,10 @@ __global__ void k_report(float* __restrict__ vmax2, int len, const int* __restri
         }
         out->vmax2[q] = m;
     }
-    if (q == 0) out->err = *err;
+    if (q == 0) {
+        out->err = *err;
+        out->stored = stored ? *stored : len;
+    }
     if (with_stats && q < 8) out->stats[q] = stats[q];
 }
 
@@ -1337,7 +1341,8 @@ int db_step(db_ctx* c, int64_t nsteps) {
                 if (rc) return rc;
             }
         }
-        hipLaunchKernelGGL(k_report, dim3(1), dim3(kMaxBlock), 0, s, c->vmax2, (int)len, c->err_d, c->sw.stats,
+        hipLaunchKernelGGL(k_report, dim3(1), dim3(kMaxBlock), 0, s, c->vmax2, (int)len,
+                           c->n > 0 ? (const int*)(c->gate_bound + 2) : nullptr, c->err_d, c->sw.stats,
                            sweep_due ? 1 : 0, X.pin_dev);
         HIPCHK(c, hipEventRecord(c->ev_report, s));
         // the next block's cell list (it needs only this block's positions) is built
@@ -1354,14 +1359,19 @@ int db_step(db_ctx* c, int64_t nsteps) {
         host_stale(c);
         rc = check_device_error(c);
         if (rc) return rc;
+        // the block ended at the first step whose input was beyond the limit; the kernels
+        // alone decide which that is (a sum of the host's own could differ in its last
+        // bit, and the positions would then be taken from the wrong buffer)
+        const int64_t done = pin->stored;
+        if (done < 1 || done > len) {
+            X.dev_error = DB_EDEVICE;
+            return fail(c, DB_EDEVICE, "a block of %lld steps reports %lld", (long long)len, (long long)done);
+        }
         // dlast: the bound on how far any bead is from where the list was built, after
-        // the steps so far, by the gate's own arithmetic; the block ended at the first
-        // step whose input was beyond the limit
+        // the steps that were stored
         double vmax = 0.0, dlast = d0;
-        int64_t done = 0;
-        for (; done < len; ++done) {
-            if (done > 0 && !(dlast <= skin)) break;
-            const double v = std::sqrt((double)pin->vmax2[done]);
+        for (int64_t q = 0; q < done; ++q) {
+            const double v = std::sqrt((double)pin->vmax2[q]);
             vmax = std::max(vmax, v);
             dlast = track ? std::max(dlast, v) : dlast + dt * v;
         }

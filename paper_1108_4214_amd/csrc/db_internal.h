@@ -207,6 +207,7 @@ struct Tiles {
 struct Gate {
     unsigned int* vmax2;   // the block's maxima, DB_VMAX_SPREAD words per step
     double* bound;         // [2] the bound at the input of step q, at q & 1
+    int* stored;           // the block's steps so far that were stored, for its report
     int q;                 // the step's place in the block
     double d0, limit;      // the bound at the block's input, and its limit
 };
@@ -272,7 +273,7 @@ struct db_ctx {
     double4* xref;       // positions at the last full Verlet-list build (slot order)
     double* vnext;       // double buffer of velocities (DPD: the step reads neighbour velocities)
     double* fext;        // [3n] external force by global bead id
-    double* gate_bound;  // [2] displacement bounds of the current block (Gate)
+    double* gate_bound;  // [2] displacement bounds of the current block, then its steps stored (Gate)
     db::SweepBuf sw;
     db::Cells cells;
     db::NList nlist;

@@ -1156,11 +1156,10 @@ __device__ __forceinline__ void step_amplitudes(const Params& P, const BlockBase
 }
 
 // Whether the block's list holds for this step: the bound on any bead's displacement
-// at its input, which the host forms alike from the block's report.  The bound
-// grows by dt times the largest speed of each step, or (TRACK: DPD) is the largest
-// displacement measured after the steps so far.  Every wave forms it (the step
-// before has ended, so its words are final); the first one records it for the next
-// step.
+// at its input.  The bound grows by dt times the largest speed of each step, or
+// (TRACK: DPD) is the largest displacement measured after the steps so far.  Every
+// wave forms it (the step before has ended, so its words are final); the first one
+// records it for the next step, and that this step was stored for the block's report.
 template <bool TRACK>
 __device__ __forceinline__ bool gate_open(const Params& P, const Gate& G) {
     double b = G.d0;
@@ -1173,8 +1172,12 @@ __device__ __forceinline__ bool gate_open(const Params& P, const Gate& G) {
         const double v = sqrt((double)m);
         b = TRACK ? fmax(before, v) : before + P.dt * v;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) G.bound[G.q & 1] = b;
-    return b <= G.limit;
+    const bool open = b <= G.limit;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        G.bound[G.q & 1] = b;
+        if (open || G.q == 0) *G.stored = open ? G.q + 1 : 0;
+    }
+    return open;
 }
 
 // pref: sqrt(24 gamma T / dt) of a single system (from the host), dsig: the DPD
@@ -2475,7 +2478,7 @@ void launch_step(db_ctx* c, int64_t step, int q, double d0, double limit) {
     const double pref = c->base_captured ? 0.0 : langevin_prefactor(c->hp, step);
     const double dsig = c->base_captured ? 0.0 : dpd_sigma(c->hp, step);
     Bank& B = c->bank[c->cur];
-    const Gate G{(unsigned*)c->vmax2, c->gate_bound, q, d0, limit};
+    const Gate G{(unsigned*)c->vmax2, c->gate_bound, (int*)(c->gate_bound + 2), q, d0, limit};
     if (tiles_enabled(c) && c->tiles_valid && c->regions_valid) {
         if (c->precision == DB_MIXED)
             hipLaunchKernelGGL(k_step_tile<float>, dim3(c->ntile), dim3(DB_BLOCK), 0, c->stream, c->dp, B, c->nlist,

@@ -323,3 +323,84 @@ def test_energy_of_a_collapsed_system(precision):
             t.append(time.perf_counter() - t0)
         least.append(min(t))
     assert least[1] < 8.0 * least[0], least
+
+
+def _apart(g, o, s):
+    d = g.state()[0] - o.state()[0]
+    return np.abs(d - s.L * np.round(d / s.L)).max()
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+@pytest.mark.parametrize("skin", [0.05, 0.09, 0.15])
+def test_dpd_blocks_cut_short_follow_the_oracle(skin, graph):
+    """Blocks that end early where the step exchanges the velocity buffers too, with launches and graphs.  Soft forces
+    (a = 25, a friction of 5) leave the rounding of 20 steps as it is."""
+    import paper_1108_4214_amd as pk
+    s = synth.dpd_solution(4, 6, 1500, 3.0, 11, 21, T=2.0)
+    g, o = both(s, synth.ff_dpd(T=2.0, gamma_dpd=5.0), synth.rules_t2(p=0.7, every=7), seed=9)
+    pk.db_tune(g.ctx, skin, 2)
+    pk.db_graph(g.ctx, graph)
+    for k in (9, 1, 10):
+        g.step(k)
+        o.step(k)
+    assert g.stats()["rollbacks"] > 0 and g.stats()["steps"] == 20
+    assert _apart(g, o, s) < 1e-9
+    v, w = g.state()[1], o.state()[1]
+    assert np.abs(v - w).max() < 1e-7
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+def test_batch_and_mixed_blocks_cut_short(graph):
+    """A batch whose fastest replica ends the blocks of all, and a mixed run: float forces are good to 1e-5 of some
+    hundred, so 24 steps of 0.005 put positions off by 24^2 / 2 x 0.005^2 x 1e-3 at most."""
+    import paper_1108_4214_amd as pk
+    rules = synth.rules_t2(p=0.7, every=7, r_kill=1.35)
+    reps = []
+    for r, T in enumerate((0.2, 2.0, 0.5)):
+        s = synth.single_strands(20 + 3 * r, 6, L=11.0, seed_w=3 + r, seed_d=4 + r, T=T)
+        reps.append((s, *both(s, synth.ff_t2(T0=T, T1=T), rules, seed=9 + r)))
+    s, ff = reps[1][0], synth.ff_t2(T0=2.0, T1=2.0)
+    mixed = pk.System(s.n, s.L, 10, 1).configure(s, ff, rules)
+    b = pk.Batch([g for _, g, _ in reps])
+    for h in (b, mixed):
+        pk.db_tune(h.ctx, 0.08, 2)
+        pk.db_graph(h.ctx, graph)
+        for _ in range(3):
+            h.step(8)
+        assert h.stats()["rollbacks"] > 0 and h.stats()["steps"] == 24
+    for r, (s, _, o) in enumerate(reps):
+        o.step(24)
+        d = b.replica_state(r)[0] - o.state()[0]
+        assert np.abs(d - s.L * np.round(d / s.L)).max() < 1e-9
+        if r == 1:
+            assert _apart(mixed, o, s) < 1e-5
+
+
+@pytest.mark.parametrize("tiles,graph", [(0, 0), (0, 1), (1, 0)])
+def test_block_with_a_kept_list_cut_short(tiles, graph):
+    """A list kept across a sweep, its displacement bound above 0 at the block's begin.  One bead of a resting lattice is
+    pulled, so its speed is the step number in units of F dt: 174 units of F dt^2 since the list of step 8, 400 more
+    expected of the block from step 20 (1.25 times that are asked for), 570 made until its last step.  Half the skin is
+    710 units: kept, and cut."""
+    import paper_1108_4214_amd as pk
+    k = np.arange(64)
+    s = synth.System(L=12.0, x=1.5 + 3.0 * np.stack([k % 4, k // 4 % 4, k // 16], 1), v=np.zeros((64, 3)),
+                     type=np.ones(64, dtype=np.int32), reactive=np.ones(64, dtype=np.uint8),
+                     bonds=np.zeros((0, 4), dtype=np.int32))
+    ff = synth.ForceField(gamma=0.0, dt=0.005)
+    pulled, f = np.array([5], dtype=np.int32), np.array([[10.0, 0.0, 0.0]])
+    g, o = both(s, ff, synth.RuleSet(every=20), seed=9)
+    pk.db_external_force(g.ctx, pulled, f)
+    o.set_external_force(pulled, f)
+    pk.db_tune(g.ctx, 2.0 * 710.0 * 10.0 * ff.dt ** 2, 4)
+    pk.db_tile_shape(g.ctx, tiles)
+    pk.db_graph(g.ctx, graph)
+    g.step(8)
+    g.step(12)
+    assert g.stats()["rollbacks"] == 0 and g.stats()["list_patches"] == 0
+    g.step(20)
+    st = g.stats()
+    assert st["list_patches"] == 1 and st["rollbacks"] == 1 and st["steps"] == 40
+    o.step(40)
+    assert _apart(g, o, s) < 1e-9
+    assert np.abs(g.state()[1] - o.state()[1]).max() < 1e-9
