@@ -311,7 +311,8 @@ int db_tile_stats(db_ctx* ctx, int64_t out[4]);
  * so sampling keeps the timed run close to an untimed one.  EINVAL if every < 0. */
 int db_profile(db_ctx* ctx, int every);
 /* mean GPU time per launch (microseconds) of the fused step kernel over the
- * launches timed since the last call, and their number; resets the tally */
+ * launches timed since the last call that made a step, and their number; resets
+ * the tally */
 int db_step_kernel_time(db_ctx* ctx, double* mean_us, int64_t* launches);
 
 /* enable (1) / disable (0) the topology-energy ledger of db_stats: every sweep is

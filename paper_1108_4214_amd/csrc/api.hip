@@ -1183,20 +1183,24 @@ static int launch_timed_step(db_ctx* c, int64_t step, int q, double d0, double l
         launch_step(c, step, q, d0, limit);
         HIPCHK(c, hipEventRecord(c->ev_pool[c->ev_used + 1], c->stream));
         c->ev_used += 2;
+        c->ev_step.push_back(q);
     } else {
         launch_step(c, step, q, d0, limit);
     }
     return DB_OK;
 }
 
-static int harvest_events(db_ctx* c) {
+// the times of the block's launches that stored a step (the first done of them)
+static int harvest_events(db_ctx* c, int done) {
     for (int k = 0; k + 1 < c->ev_used; k += 2) {
+        if (c->ev_step[k / 2] >= done) continue;
         float ms = 0;
         HIPCHK(c, hipEventElapsedTime(&ms, c->ev_pool[k], c->ev_pool[k + 1]));
         c->prof_ms += ms;
         c->prof_launches++;
     }
     c->ev_used = 0;
+    c->ev_step.clear();
     return DB_OK;
 }
 
@@ -1352,7 +1356,7 @@ int db_step(db_ctx* c, int64_t nsteps) {
         HIPCHK(c, hipEventSynchronize(c->ev_report));
         HIPCHK(c, hipGetLastError());
         if (c->profile) {
-            rc = harvest_events(c);
+            rc = harvest_events(c, pin->stored);
             if (rc) return rc;
         }
         if (sweep_due) record_sweep_stats(c);

@@ -335,6 +335,7 @@ struct db_ctx {
     int64_t profile_count;
     std::vector<hipEvent_t> ev_pool;
     int ev_used;
+    std::vector<int> ev_step;   // the step within its block that each pair of events times
     double prof_ms;
     int64_t prof_launches;
 };

@@ -404,3 +404,16 @@ def test_block_with_a_kept_list_cut_short(tiles, graph):
     o.step(40)
     assert _apart(g, o, s) < 1e-9
     assert np.abs(g.state()[1] - o.state()[1]).max() < 1e-9
+
+
+def test_profile_counts_the_steps_made():
+    """Launches after a block's early end store nothing: with every launch timed, their number is that of the steps."""
+    import paper_1108_4214_amd as pk
+    s = synth.single_strands(24, 6, L=11.0, seed_w=3, seed_d=4, T=2.0)
+    g = pk.System(s.n, s.L, 9).configure(s, synth.ff_t2(T0=2.0, T1=2.0), synth.rules_t2(every=7))
+    pk.db_tune(g.ctx, 0.08, 2)
+    pk.db_profile(g.ctx, 1)
+    g.step(24)
+    assert g.stats()["rollbacks"] > 0
+    us, launches = pk.db_step_kernel_time(g.ctx)
+    assert launches == 24 and us > 0.0
