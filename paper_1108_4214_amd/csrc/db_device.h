@@ -213,9 +213,13 @@ __device__ __forceinline__ int cell_coord(double x, double scale, int nc) {
     return t >= 0.0 ? (t < (double)nc ? (int)t : nc - 1) : 0;
 }
 
-// neighbour offset k < 3 of box X by selects (an indexed read would place a box
-// held in registers in scratch memory)
-__device__ __forceinline__ int box_off(const Box& X, int k) { return k == 0 ? X.off[0] : (k == 1 ? X.off[1] : X.off[2]); }
+// neighbour offset k < 3 of box X by selects among the values (an indexed read would
+// place a box held in registers in scratch memory, and so would reads inside the
+// selects, which the compiler makes one read at a selected place)
+__device__ __forceinline__ int box_off(const Box& X, int k) {
+    const int a = X.off[0], b = X.off[1], c = X.off[2];
+    return k == 0 ? a : (k == 1 ? b : c);
+}
 
 __device__ __forceinline__ int wrap_cell(int c, int nc) { return c < 0 ? c + nc : (c >= nc ? c - nc : c); }
 

@@ -2123,8 +2123,10 @@ __global__ __launch_bounds__(DB_BLOCK) void k_step_tile(const Params* __restrict
 // waits for neighbours' data from the other dies' memory, and for crowded beads)
 // against 644 + 51;
 // 191k duplex beads, forces in FP32: 28 us against 42 for a list build and a force pass.
+// FP32 is held to three waves per SIMD, which only the energies of a batch in DPD
+// solvent would miss (24 boxes of 12k beads: 222 us a call without, 193 so).
 template <typename R, int MODE, bool BATCH, int PAIR>
-__global__ __launch_bounds__(DB_BLOCK) void k_eval(const Params* __restrict__ Pp, Bank B, Halo H,
+__global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 4 ? 3 : 1) void k_eval(const Params* __restrict__ Pp, Bank B, Halo H,
                                                    const int* __restrict__ cstart, const int* __restrict__ clist,
                                                    const float4* __restrict__ xs, const uint2* __restrict__ xq,
                                                    int64_t step,
