@@ -393,6 +393,7 @@ static double skin_of(const db_ctx* c) {
 static int upload_params(db_ctx* c) {
     if (!c->params_dirty) return DB_OK;
     compute_grid(c);
+    choose_list_form(c);
     c->hp.n = c->n;
     c->hp.fext = c->fext;
     c->hp.nrep = c->nrep;
@@ -713,6 +714,7 @@ int db_create(db_ctx** out, int32_t n, double L, uint64_t seed, int precision, v
     c->ev_report = nullptr;
     c->profile_every = 1;
     c->profile_count = 0;
+    c->list_form = LIST_QUANTISED;
     c->list_valid = false;
     c->list_disp = 0.0;
     c->disp_rate = 0.0;

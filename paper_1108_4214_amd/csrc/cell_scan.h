@@ -139,6 +139,85 @@ __device__ __forceinline__ void scan_cells(const Box& X, const int* __restrict__
     }
 }
 
+// The candidates of scan_cells (grids of three or more cells per edge only), each
+// passed as f(w, hit) with w the entry's word (xs_slot(w) is its slot) and hit =
+// (slot != i and float r2 < cut2), in scan_cells' order.  f runs for every
+// candidate, so a visitor without branches (one that writes every candidate and
+// advances its count by hit) keeps the lanes of a wave together; the x-range of a
+// row and its wrapped part are separate loops, so the common range needs no
+// per-candidate choice of image.  The bead's own entry is told apart by its whole
+// word (the slot bits differ for every other bead), and r2 is formed with fused
+// multiply-adds, whose rounding is within the relative margin of cut2.
+template <class F>
+__device__ __forceinline__ void scan_cells_all(const Box& X, const int* __restrict__ cstart,
+                                               const float4* __restrict__ xs, int i, const double4& xi, float cut2,
+                                               F&& f) {
+    const int nc = X.nc;
+    const int cx = cell_coord(xi.x, X.cell_scale, nc);
+    const int cy = cell_coord(xi.y, X.cell_scale, nc);
+    const int cz = cell_coord(xi.z, X.cell_scale, nc);
+    const float Lf = (float)X.L;
+    const float px = (float)xi.x, py = (float)xi.y, pz = (float)xi.z;
+    const int wi = __float_as_int(xs_word(i, meta_word(xi)));
+    cstart += X.cell_off;
+    auto shift = [&](int c) { return c < 0 ? -Lf : (c >= nc ? Lf : 0.0f); };
+    int a0, a1, b0 = 0, b1 = 0;
+    float qx1 = px;
+    if (cx >= 1 && cx <= nc - 2) {
+        a0 = cx - 1;
+        a1 = cx + 2;
+    } else if (cx == 0) {
+        a0 = 0;
+        a1 = 2;
+        b0 = nc - 1;
+        b1 = nc;
+        qx1 = px + Lf;
+    } else {
+        a0 = nc - 2;
+        a1 = nc;
+        b0 = 0;
+        b1 = 1;
+        qx1 = px - Lf;
+    }
+    const bool wrapx = b1 > b0;
+    auto row_of = [&](int r) { return (wrap_cell(cz + r / 3 - 1, nc) * nc + wrap_cell(cy + r % 3 - 1, nc)) * nc; };
+    // one run [s, e) of consecutive entries seen from (qx, qy, qz); a group of
+    // loads may run past e (into the next cells' entries, or into the padding after
+    // the last entry), and those candidates are masked
+    auto run = [&](int s, int e, float qx, float qy, float qz) {
+        for (int p = s; p < e; p += DB_SCAN_W) {
+            float4 c[DB_SCAN_W];
+            const float4* src = xs + p;
+#pragma unroll
+            for (int q = 0; q < DB_SCAN_W; ++q) c[q] = src[q];
+            const int rem = e - p;
+#pragma unroll
+            for (int q = 0; q < DB_SCAN_W; ++q) {
+                const int w = __float_as_int(c[q].w);
+                const float dx = c[q].x - qx, dy = c[q].y - qy, dz = c[q].z - qz;
+                const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
+                f(w, (q < rem) & (w != wi) & (r2 < cut2));
+            }
+        }
+    };
+    int row = row_of(0);
+    int s0 = cstart[row + a0], s1 = cstart[row + a1];
+    int t0 = wrapx ? cstart[row + b0] : 0, t1 = wrapx ? cstart[row + b1] : 0;
+    for (int r = 0; r < 9; ++r) {
+        const float qz = pz - shift(cz + r / 3 - 1), qy = py - shift(cy + r % 3 - 1);
+        const int c0 = s0, c1 = s1, d0 = t0, d1 = t1;
+        if (r + 1 < 9) {   // the next row's bounds are requested before this row is scanned
+            row = row_of(r + 1);
+            s0 = cstart[row + a0];
+            s1 = cstart[row + a1];
+            t0 = wrapx ? cstart[row + b0] : 0;
+            t1 = wrapx ? cstart[row + b1] : 0;
+        }
+        run(c0, c1, px, qy, qz);
+        run(d0, d1, qx1, qy, qz);
+    }
+}
+
 // ---- the quantised scan ----------------------------------------------------------
 // The same cells through the quantised copy, for the kernels that scan for every
 // bead.  Scattered loads cost the vector memory path a pass per few lanes whatever
@@ -164,7 +243,7 @@ typedef short db_short2 __attribute__((ext_vector_type(2)));
 // the scan does not serve: grids of fewer than three cells per edge, and boxes where
 // two units are more than 3 % of the reach (edges beyond about 1,000 reaches), which
 // would keep too many entries.
-__device__ __forceinline__ uint32_t quantised_cut(const Box& X, double reach) {
+__host__ __device__ inline uint32_t quantised_cut(const Box& X, double reach) {
     const double r = reach * (65536.0 / X.L);
     return X.noff == 3 && 2.0 <= 0.03 * r ? (uint32_t)fmin((r + 2.0) * (r + 2.0) + 1.0, 4294967040.0) : 0u;
 }

@@ -197,6 +197,10 @@ struct Tiles {
     uint32_t* nitems; // [ntile] angle items | dihedral items << 16; 0xFFFFFFFF: no items (per-bead terms)
 };
 
+// How Verlet lists are built: by the quantised scan, by the float scan staged in LDS,
+// or by the float scan with the exclusion test inside (choose_list_form)
+enum ListForm { LIST_QUANTISED = 0, LIST_FLOAT_STAGED, LIST_FLOAT };
+
 // The validity gate of a block's step launches.  A step may use the block's Verlet
 // list while the bound on any bead's displacement since the list's full build, at
 // the step's input, is within half the skin.  The launches of a block are issued
@@ -290,6 +294,7 @@ struct db_ctx {
     bool halo_sweep;     // a sweep ran since the last halo build: rebuild it if the sweep changed bonds
     // Verlet list kept across sweeps: valid for the current slots and topology, and
     // list_disp bounds how far any bead has moved since its full build
+    int list_form;       // ListForm
     bool list_valid;
     double list_disp;
     double disp_rate;    // growth of that bound per step seen lately
@@ -355,6 +360,7 @@ void launch_compact(const int* flags, int count, int* list, int* total, int* blo
 // kernels_force.hip
 void launch_halo(db_ctx* c);                         // bonded halo, if slots or tables changed
 void launch_build_nlist(db_ctx* c);                  // halo, then the Verlet list from the current cell list
+void choose_list_form(db_ctx* c);                    // sets list_form for the present grid
 void launch_regions(db_ctx* c);                      // tile regions and 16-bit entries of the current lists
 // Verlet lists of the beads whose exclusions the last sweep changed, with cutoff
 // cut (the list cutoff plus twice the displacement since the full build)

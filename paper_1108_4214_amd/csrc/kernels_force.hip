@@ -415,6 +415,61 @@ void k_build_nlist(const Params* __restrict__ Pp, Bank B, const int* __restrict_
     if (part == 0) NL.cnt[i] = (uint8_t)cnt;
 }
 
+// The same by the float scan, one thread per bead, for the boxes and lists that the
+// quantised scan does not serve well (ListForm).  staged: every candidate is written
+// into the LDS row of the next kept entry without a branch (one not kept is
+// overwritten by the next one kept; past the rows the extra row takes them all), and
+// the exclusions are applied afterwards; a bead with more kept candidates than rows,
+// and without staged every bead, is scanned with the test inside.
+template <bool BATCH>
+__global__ __launch_bounds__(DB_BLOCK)
+void k_build_nlist_float(const Params* __restrict__ Pp, Bank B, const int* __restrict__ cstart,
+                         const float4* __restrict__ xs, NList NL, int* __restrict__ err,
+                         double4* __restrict__ xref, int staged) {
+    const Params& P = *Pp;
+    const int n = P.n;
+    constexpr int NL_STAGE = 24;
+    __shared__ int stage[NL_STAGE + 1][DB_BLOCK];
+    const int tid = threadIdx.x;
+    const int i = xcd_tile(blockIdx.x, gridDim.x) * DB_BLOCK + tid;
+    if (i >= n) return;
+    const double4 xi = B.x[i];
+    if (xref) xref[i] = xi;
+    ExclSet E;
+    gather_excl(P, B, n, i, E);
+    const Box& X = box_of<BATCH>(P, meta_word(xi));
+    int cnt = 0, raw = NL_STAGE + 1;
+    if (staged && X.noff == 3) {
+        raw = 0;
+        scan_cells_all(X, cstart, xs, i, xi, X.pf_list2, [&](int w, bool hit) {
+            stage[min(raw, NL_STAGE)][tid] = w;   // the word; its slot is taken below
+            raw += hit ? 1 : 0;
+        });
+    }
+    if (raw <= NL_STAGE) {
+        for (int k = 0; k < raw; ++k) {
+            const int j = xs_slot(stage[k][tid]);
+            if (E.has(j)) continue;
+            stage[cnt][tid] = j;
+            ++cnt;
+        }
+    } else {
+        scan_cells(X, cstart, xs, i, xi, X.pf_list2, [&](int j, int) {
+            if (E.has(j)) return;
+            if (cnt < NL_STAGE) stage[cnt][tid] = j;
+            else if (cnt < DB_NLCAP) NL.nl[cnt * n + i] = j;
+            ++cnt;
+        });
+    }
+    const int ns = min(cnt, NL_STAGE);
+    for (int k = 0; k < ns; ++k) NL.nl[k * n + i] = stage[k][tid];
+    if (cnt > DB_NLCAP) {
+        atomicOr(err, ERR_NLIST);
+        cnt = DB_NLCAP;
+    }
+    NL.cnt[i] = (uint8_t)cnt;
+}
+
 // The list of one bead whose exclusions a sweep changed, redone with cutoff cut
 // (beyond the list cutoff by the displacement margin; the 5 x 5 x 5 stencil
 // reaches it) by LANES threads that share its rows (row r to thread r mod LANES).
@@ -2367,6 +2422,34 @@ static unsigned grid_for_parts(const db_ctx* c, int parts) {
     return (unsigned)(((int64_t)c->n * parts + DB_BLOCK - 1) / DB_BLOCK);
 }
 
+// Which scan builds the lists: by whether the quantised one serves a bead's box and
+// whether its LDS rows hold the lists expected at the box's density; a batch goes by
+// what holds for most beads.  Past the rows the quantised build scans again by one
+// thread, so longer lists take the float scan at once.  The lines, by list builds with
+// growing skins, quantised against float: one thread per bead, 300k DPD beads at 21.7
+// entries expected 78 and 100 us, at 24.5 163 and 107 (319 and 201 at 47), 500k of a
+// melt at 22.7 87 and 118, at 24.5 133 and 126; four threads, 130k DPD beads at 24.5
+// 74 and 82, at 34 175 and 109 (fewer beads gain nothing: 12k 153 and 152 at 47).  In the boxes that are not
+// served the staged float scan is the faster while its rows hold (300k at 13.5
+// expected 46 and 70 us).
+static bool four_per_bead(const db_ctx* c) { return c->n < (1 << 17); }
+
+void choose_list_form(db_ctx* c) {
+    const double line = c->n < (1 << 16) ? INFINITY : (four_per_bead(c) ? 30.0 : 23.0);
+    int64_t quantised = 0, staged = 0;
+    auto count = [&](const Box& X, int64_t beads) {
+        const double reach = sqrt(c->hp.rnl2) + X.pf_slack;
+        const double expected = 4.18879020478639 * reach * reach * reach * (double)beads / (X.L * X.L * X.L);
+        if (quantised_cut(X, reach) && expected <= line) quantised += beads;
+        else if (X.noff == 3 && expected <= 23.0) staged += beads;
+    };
+    if (c->nrep == 0) count(c->hp.box, c->n);
+    for (int r = 0; r < c->nrep; ++r) count(c->reps[r], c->rep_n[r]);
+    const int64_t other = c->n - quantised - staged;
+    c->list_form = quantised >= std::max(staged, other) ? LIST_QUANTISED
+                                                        : (staged >= other ? LIST_FLOAT_STAGED : LIST_FLOAT);
+}
+
 template <bool BATCH, int PARTS>
 static void launch_nlist(db_ctx* c, double4* xref) {
     hipLaunchKernelGGL((k_build_nlist<BATCH, PARTS>), dim3(grid_for_parts(c, PARTS)), dim3(DB_BLOCK), 0, c->stream,
@@ -2378,7 +2461,18 @@ void launch_build_nlist(db_ctx* c) {
     if (c->n == 0) return;
     launch_halo(c);
     double4* xref = c->hp.have_pair && c->hp.pair_style == PAIR_DPD ? c->xref : nullptr;
-    const bool four = c->n < (1 << 17);
+    if (c->list_form != LIST_QUANTISED) {
+        const int staged = c->list_form == LIST_FLOAT_STAGED;
+        if (c->nrep > 0)
+            hipLaunchKernelGGL(k_build_nlist_float<true>, dim3(grid_for(c->n)), dim3(DB_BLOCK), 0, c->stream, c->dp,
+                               c->bank[c->cur], c->cells.start, c->cells.xs, c->nlist, c->err_d, xref, staged);
+        else
+            hipLaunchKernelGGL(k_build_nlist_float<false>, dim3(grid_for(c->n)), dim3(DB_BLOCK), 0, c->stream, c->dp,
+                               c->bank[c->cur], c->cells.start, c->cells.xs, c->nlist, c->err_d, xref, staged);
+        launch_regions(c);
+        return;
+    }
+    const bool four = four_per_bead(c);
     if (c->nrep > 0) four ? launch_nlist<true, 4>(c, xref) : launch_nlist<true, 1>(c, xref);
     else four ? launch_nlist<false, 4>(c, xref) : launch_nlist<false, 1>(c, xref);
     launch_regions(c);

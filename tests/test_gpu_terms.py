@@ -417,3 +417,36 @@ def test_profile_counts_the_steps_made():
     assert g.stats()["rollbacks"] > 0
     us, launches = pk.db_step_kernel_time(g.ctx)
     assert launches == 24 and us > 0.0
+
+
+@pytest.mark.parametrize("form", ["dense one thread", "dense four threads", "dense few beads", "far box", "small boxes", "mixed batch"])
+def test_list_forms_match_oracle(form):
+    """Lists by the float scan: longer than the quantised scan's rows hold (a skin of 0.5 at density 3, about 44 entries,
+    with one and with four threads' share of beads), in an edge beyond its reach, in boxes of two cells per edge, and a
+    batch where some boxes are served and some not.  Forces of soft pairs as in the other list builds."""
+    import paper_1108_4214_amd as pk
+    import oracle
+    ff = dataclasses.replace(synth.ff_dpd(gamma_dpd=0.0), dt=2.0 ** -10)
+    sizes = {"dense one thread": [(132000, 35.3)], "dense four threads": [(66000, 28.0)], "dense few beads": [(6000, 12.6)], "far box": [(4000, 2500.0)],
+             "small boxes": [(60, 2.9), (81, 3.0)], "mixed batch": [(3000, 10.0), (500, 2000.0), (70, 2.9)]}[form]
+    for order in (1, -1):
+        reps, want = [], []
+        for n, L in sizes[::order]:
+            rng = np.random.default_rng(n)
+            x = rng.uniform(0.0, L, size=(n, 3))
+            if L > 1000.0:
+                x[:n // 2] = np.mod(rng.normal(0.0, 4.0, size=(n // 2, 3)), L)
+            s = synth.System(L=L, x=synth.wrap(x, L), v=np.zeros((n, 3)), type=np.ones(n, dtype=np.int32),
+                             reactive=np.zeros(n, dtype=np.uint8), bonds=np.zeros((0, 4), dtype=np.int32))
+            reps.append(pk.System(n, L, 1, 0).configure(s, ff, synth.RuleSet(every=0), generate=False))
+            o = oracle.Oracle.from_system(s, ff, synth.RuleSet(every=0), seed=1, generate=False)
+            want.append(o.forces())
+        g = pk.Batch(reps) if len(reps) > 1 else reps[0]
+        pk.db_tune(g.ctx, 0.5 if form.startswith("dense") else 0.02, 8)
+        g.step(1)
+        got = [g.replica_state(r)[1] for r in range(len(reps))] if len(reps) > 1 else [g.state()[1]]
+        for v, f in zip(got, want):
+            ok, msg = forces_close(v / ff.dt, f, 1e-11)
+            assert ok, msg
+        if len(sizes) == 1:
+            break
