@@ -1243,10 +1243,14 @@ __device__ __forceinline__ bool gate_open(const Params& P, const Gate& G) {
 // of |v|^2 (WCA) or, with DPD, of the squared displacement of the new position
 // from xref, the position at the last full Verlet-list build.
 // The step kernels are held to the registers of six (FP32 WCA), five (FP32 DPD)
-// and three (FP64) waves per SIMD, what their LDS allows or just below, which the
-// compiler otherwise gives up for a few registers.
-template <typename R, bool BATCH, int PAIR>
-__global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 8 ? 3 : (PAIR == PAIR_WCA ? 6 : 5))
+// and three (FP64) waves per SIMD, what their LDS allows or just below.  The DPD ones
+// spill for it, 20 registers in FP32 batches and 2 to 14 in FP64, and are the faster
+// all the same: 24 boxes of 12k beads at four and five waves 104 and 95 us in FP32, at
+// two and three 2,146 and 2,028 us for 6 steps in FP64; 300k beads in FP64 966 and 944.
+template <typename R, int PAIR>
+constexpr int step_waves() { return sizeof(R) == 8 ? 3 : (PAIR == PAIR_WCA ? 6 : 5); }
+template <typename R, bool BATCH, int PAIR, int WAVES = step_waves<R, PAIR>()>
+__global__ __launch_bounds__(DB_BLOCK, WAVES)
 void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __restrict__ xout, double* vout,
             int64_t step, double pref, double dsig, Gate G, int* __restrict__ err, const double4* __restrict__ xref,
             const BlockBase* __restrict__ base) {
@@ -2538,25 +2542,30 @@ static bool velocity_double_buffer(const db_ctx* c) {
     return c->hp.have_pair && c->hp.pair_style == PAIR_DPD && c->hp.dpd_gamma != 0.0;
 }
 
-template <typename R, bool BATCH, int PAIR>
+template <typename R, bool BATCH, int PAIR, int WAVES = step_waves<R, PAIR>()>
 static void launch_step_kernel(db_ctx* c, const Bank& B, double4* xout, double* vout, int64_t step, double pref,
                                double dsig, const Gate& G) {
-    hipLaunchKernelGGL((k_step<R, BATCH, PAIR>), dim3(grid_for(c->n)), dim3(DB_BLOCK), 0, c->stream, c->dp, B,
+    hipLaunchKernelGGL((k_step<R, BATCH, PAIR, WAVES>), dim3(grid_for(c->n)), dim3(DB_BLOCK), 0, c->stream, c->dp, B,
                        c->nlist, c->halo, xout, vout, step, pref, dsig, G, c->err_d, c->xref,
                        (const BlockBase*)c->base_captured);
 }
 
-template <int PAIR>
+template <typename R, int PAIR>
 static void launch_step_pair(db_ctx* c, const Bank& B, double4* xout, double* vout, int64_t step, double pref,
                              double dsig, const Gate& G) {
     const bool batch = c->nrep > 0;
-    if (c->precision == DB_MIXED) {
-        if (batch) launch_step_kernel<float, true, PAIR>(c, B, xout, vout, step, pref, dsig, G);
-        else launch_step_kernel<float, false, PAIR>(c, B, xout, vout, step, pref, dsig, G);
-    } else {
-        if (batch) launch_step_kernel<double, true, PAIR>(c, B, xout, vout, step, pref, dsig, G);
-        else launch_step_kernel<double, false, PAIR>(c, B, xout, vout, step, pref, dsig, G);
-    }
+    // DPD batches: the waves per SIMD at which the kernel spills nothing serve where the
+    // grid fits the chip with them (400 boxes of 80 beads in FP64, 6 steps 437 us against
+    // 463), and in FP32 for small boxes: waves that straddle two of them read the box per
+    // lane, in whose loops the spilled registers weigh more than a fifth wave (250k beads,
+    // four against five waves: boxes of 80 beads 74 and 80 us, of 1,200 77 and 83, of
+    // 1,600 79 and 80, of 3,200 and more the same)
+    constexpr int FREE = PAIR != PAIR_DPD ? step_waves<R, PAIR>() : (sizeof(R) == 8 ? 2 : 4);
+    const bool small = sizeof(R) == 4 && (int64_t)c->n < (int64_t)c->nrep * 1500;
+    if (batch && (small || grid_for(c->n) <= 256u * FREE))
+        launch_step_kernel<R, true, PAIR, FREE>(c, B, xout, vout, step, pref, dsig, G);
+    else if (batch) launch_step_kernel<R, true, PAIR>(c, B, xout, vout, step, pref, dsig, G);
+    else launch_step_kernel<R, false, PAIR>(c, B, xout, vout, step, pref, dsig, G);
 }
 
 static bool dpd_pairs(const db_ctx* c) { return c->hp.have_pair && c->hp.pair_style == PAIR_DPD; }
@@ -2588,8 +2597,11 @@ void launch_step(db_ctx* c, int64_t step, int q, double d0, double limit) {
                                (const BlockBase*)c->base_captured);
     } else {
         double* vout = velocity_double_buffer(c) ? c->vnext : B.v;
-        if (dpd_pairs(c)) launch_step_pair<PAIR_DPD>(c, B, c->xnext, vout, step, pref, dsig, G);
-        else launch_step_pair<PAIR_WCA>(c, B, c->xnext, vout, step, pref, dsig, G);
+        auto go = [&](auto launch) { launch(c, B, c->xnext, vout, step, pref, dsig, G); };
+        if (c->precision == DB_MIXED)
+            dpd_pairs(c) ? go(launch_step_pair<float, PAIR_DPD>) : go(launch_step_pair<float, PAIR_WCA>);
+        else
+            dpd_pairs(c) ? go(launch_step_pair<double, PAIR_DPD>) : go(launch_step_pair<double, PAIR_WCA>);
     }
     swap_step_buffers(c);
 }

@@ -450,3 +450,23 @@ def test_list_forms_match_oracle(form):
             assert ok, msg
         if len(sizes) == 1:
             break
+
+
+@pytest.mark.parametrize("beads", [60, 1499, 1501])
+def test_dpd_batches_of_small_and_large_boxes(beads):
+    """Steps of DPD batches in boxes on both sides of the size that chooses the step kernel's registers, mixed, against
+    the oracle: float forces are good to 1e-5 of some hundred, over five steps of 0.01 with a friction of 5."""
+    import paper_1108_4214_amd as pk
+    ff = synth.ff_dpd(gamma_dpd=5.0)
+    reps = []
+    for r in range(3):
+        s = synth.random_gas(beads, (beads / 3.0) ** (1.0 / 3.0), seed=r)
+        reps.append((s, *both(s, ff, synth.RuleSet(every=0), seed=9 + r, precision=1, generate=False)))
+    b = pk.Batch([g for _, g, _ in reps])
+    b.step(5)
+    for r, (s, _, o) in enumerate(reps):
+        o.step(5)
+        x, v = b.replica_state(r)
+        d = x - o.state()[0]
+        assert np.abs(d - s.L * np.round(d / s.L)).max() < 5e-6
+        assert np.abs(v - o.state()[1]).max() < 1e-4
