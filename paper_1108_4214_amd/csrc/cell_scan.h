@@ -140,18 +140,18 @@ __device__ __forceinline__ void scan_cells(const Box& X, const int* __restrict__
 }
 
 // The candidates of scan_cells (grids of three or more cells per edge only), each
-// passed as f(w, hit) with w the entry's word (xs_slot(w) is its slot) and hit =
-// (slot != i and float r2 < cut2), in scan_cells' order.  f runs for every
-// candidate, so a visitor without branches (one that writes every candidate and
-// advances its count by hit) keeps the lanes of a wave together; the x-range of a
-// row and its wrapped part are separate loops, so the common range needs no
-// per-candidate choice of image.  The bead's own entry is told apart by its whole
-// word (the slot bits differ for every other bead), and r2 is formed with fused
-// multiply-adds, whose rounding is within the relative margin of cut2.
+// passed as f(w, other, r2) with w the entry's word (xs_slot(w) is its slot), other =
+// it is a candidate and not the bead itself, and r2 its squared distance in float, in
+// scan_cells' order.  f runs for every candidate, so a visitor without branches (one
+// that writes every candidate and advances its count by a test) keeps the lanes of a
+// wave together; the x-range of a row and its wrapped part are separate loops, so the
+// common range needs no per-candidate choice of image.  The bead's own entry is told
+// apart by its whole word (the slot bits differ for every other bead), and r2 is
+// formed with fused multiply-adds, whose rounding is within the relative margin of
+// the prefilter cutoffs.
 template <class F>
 __device__ __forceinline__ void scan_cells_all(const Box& X, const int* __restrict__ cstart,
-                                               const float4* __restrict__ xs, int i, const double4& xi, float cut2,
-                                               F&& f) {
+                                               const float4* __restrict__ xs, int i, const double4& xi, F&& f) {
     const int nc = X.nc;
     const int cx = cell_coord(xi.x, X.cell_scale, nc);
     const int cy = cell_coord(xi.y, X.cell_scale, nc);
@@ -196,7 +196,7 @@ __device__ __forceinline__ void scan_cells_all(const Box& X, const int* __restri
                 const int w = __float_as_int(c[q].w);
                 const float dx = c[q].x - qx, dy = c[q].y - qy, dz = c[q].z - qz;
                 const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
-                f(w, (q < rem) & (w != wi) & (r2 < cut2));
+                f(w, (q < rem) & (w != wi), r2);
             }
         }
     };

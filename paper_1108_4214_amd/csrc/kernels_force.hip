@@ -313,17 +313,21 @@ __device__ __forceinline__ int stage_quantised(const Box& X, const int* __restri
     return over ? ROWS : at / ROW;
 }
 
-// the staged places turned into slots, in place and in order, without the bead itself
-// and its exclusions; returns their number
-template <class Excl>
+// the staged places (slots already where SLOTS and slots) turned into slots, in place
+// and in order, without the bead itself and its exclusions; returns their number
+template <bool SLOTS = false, class Excl>
 __device__ __forceinline__ int settle_staged(const int* __restrict__ clist, int i, int raw, int (*stage)[DB_BLOCK],
-                                             const Excl& E) {
+                                             const Excl& E, bool slots = false) {
     const int tid = threadIdx.x;
     int cnt = 0;
     for (int k0 = 0; k0 < raw; k0 += 4) {
         int j[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) j[q] = clist[stage[min(k0 + q, raw - 1)][tid]];
+        for (int q = 0; q < 4; ++q) j[q] = stage[min(k0 + q, raw - 1)][tid];
+        if (!(SLOTS && slots)) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) j[q] = clist[j[q]];
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             if ((k0 + q < raw) & (j[q] != i) && !E.has(j[q])) {
@@ -441,9 +445,9 @@ void k_build_nlist_float(const Params* __restrict__ Pp, Bank B, const int* __res
     int cnt = 0, raw = NL_STAGE + 1;
     if (staged && X.noff == 3) {
         raw = 0;
-        scan_cells_all(X, cstart, xs, i, xi, X.pf_list2, [&](int w, bool hit) {
+        scan_cells_all(X, cstart, xs, i, xi, [&](int w, bool other, float r2) {
             stage[min(raw, NL_STAGE)][tid] = w;   // the word; its slot is taken below
-            raw += hit ? 1 : 0;
+            raw += (other & (r2 < X.pf_list2)) ? 1 : 0;
         });
     }
     if (raw <= NL_STAGE) {
@@ -2184,6 +2188,10 @@ __global__ __launch_bounds__(DB_BLOCK) void k_step_tile(const Params* __restrict
 // 191k duplex beads, forces in FP32: 28 us against 42 for a list build and a force pass.
 // FP32 is held to three waves per SIMD, which only the energies of a batch in DPD
 // solvent would miss (24 boxes of 12k beads: 222 us a call without, 193 so).
+// Boxes that the quantised scan does not serve take the float scan, for forces staged
+// where they have three cells per edge or more (400k sparse beads in an edge of 2,000,
+// forces in FP64 90 us unstaged and with the list counted in a pass of its own, 69 so;
+// energies, as fast unstaged as a list build and a pass, keep its registers).
 template <typename R, int MODE, bool BATCH, int PAIR>
 __global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 4 ? 3 : 1) void k_eval(const Params* __restrict__ Pp, Bank B, Halo H,
                                                    const int* __restrict__ cstart, const int* __restrict__ clist,
@@ -2223,6 +2231,7 @@ __global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 4 ? 3 : 1) void k_eval(const
         with_box<BATCH>(P, meta_word(xi), [&](const Box& X) __attribute__((always_inline)) {
             const double reach = P.rc + X.pf_slack;
             const float cut2 = (float)(reach * reach * 1.0001);
+            const float scan2 = MODE == MODE_FORCE ? X.pf_list2 : cut2;   // of the float scans: forces count the list too
             const R rc2 = (R)P.rc2;
             const bool friction = MODE == MODE_ENERGY && PAIR == PAIR_DPD && P.dpd_gamma != 0.0;
             double dsig = 0.0;
@@ -2249,7 +2258,7 @@ __global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 4 ? 3 : 1) void k_eval(const
             };
             const double list_reach = sqrt(P.rnl2) + X.pf_slack;
             int raw = EV_STAGE + 1;
-            bool crowded = true;   // more than a Verlet list's capacity of beads may be within its cutoff
+            bool crowded = false;   // more than a Verlet list's capacity of beads may be within its cutoff
             const uint32_t cutq = quantised_cut(X, reach);
             if (cutq) {
                 int listed = 0;
@@ -2259,12 +2268,18 @@ __global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 4 ? 3 : 1) void k_eval(const
                 else
                     raw = stage_quantised<EV_STAGE + 4, 1>(X, cstart, xq, xi, reach, cutq, lds.stage, 0);
                 crowded = listed > DB_NLCAP;
+            } else if (MODE == MODE_FORCE && X.noff == 3) {   // slots, by the float scan
+                raw = 0;
+                scan_cells_all(X, cstart, xs, i, xi, [&](int w, bool other, float r2) {
+                    lds.stage[min(raw, EV_STAGE)][tid] = xs_slot(w);
+                    raw += (other & (r2 < scan2)) ? 1 : 0;
+                });
             }
             ExclSet E;   // after the scan, for its registers
             gather_excl(P, B, n, i, E);
-            bool serial = !cutq;   // a box the quantised scan does not serve
-            for (int skip = 0; cutq;) {
-                const int cnt = settle_staged(clist, i, min(raw, EV_STAGE), lds.stage, E);
+            bool serial = !cutq && raw > EV_STAGE;
+            for (int skip = 0; !serial;) {
+                const int cnt = settle_staged<MODE == MODE_FORCE>(clist, i, min(raw, EV_STAGE), lds.stage, E, !cutq);
                 for (int k0 = 0; k0 < cnt; k0 += 4) {
                     int j[4];
                     double4 xj[4];
@@ -2285,29 +2300,29 @@ __global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 4 ? 3 : 1) void k_eval(const
                 // do: 104 us with the float scan for them, 74 so.  The list build, whose scan
                 // the second one costs registers, 72 -> 81 us at 1M beads, keeps that.)
                 skip += EV_STAGE;
-                int within = 0;
-                raw = stage_quantised<EV_STAGE + 4, 1, true>(X, cstart, xq, xi, MODE == MODE_FORCE ? list_reach : reach,
-                                                             cutq, lds.stage, 0, cutq, &within, skip);
                 // A scan per 28 neighbours grows with their square: in a collapsed system,
                 // thousands within reach, the float scan takes them all in one (8,000 beads
-                // within 0.9, FP64 energies: 124 ms by repeated scans, 5 so)
-                if (within > DB_NLCAP) {
+                // within 0.9, FP64 energies: 124 ms by repeated scans, 6 so)
+                if (skip > DB_NLCAP) {
                     a = Acc<R>();   // nothing but the pairs so far
                     serial = true;
                     break;
                 }
+                raw = stage_quantised<EV_STAGE + 4, 1, true>(X, cstart, xq, xi, MODE == MODE_FORCE ? list_reach : reach,
+                                                             cutq, lds.stage, 0, 0, nullptr, skip);
             }
+            int c = 0;   // entries of the bead's Verlet list, counted where they may be too many
             if (serial) {
-                scan_cells(X, cstart, xs, i, xi, cut2, [&](int j, int) {
-                    if (!E.has(j)) pair(B.x[j], vel_of(j));
+                scan_cells(X, cstart, xs, i, xi, scan2, [&](int j, int) {
+                    if (E.has(j)) return;
+                    pair(B.x[j], vel_of(j));
+                    ++c;
                 });
             }
-            // a bead whose Verlet list would overflow is an error here too
-            if (MODE == MODE_FORCE && crowded) {
-                int c = 0;
+            if (MODE == MODE_FORCE && crowded && !serial)
                 scan_cells(X, cstart, xs, i, xi, X.pf_list2, [&](int j, int) { c += E.has(j) ? 0 : 1; });
-                if (c > DB_NLCAP) atomicOr(err, ERR_NLIST);
-            }
+            // a bead whose Verlet list would overflow is an error here too
+            if (MODE == MODE_FORCE && c > DB_NLCAP) atomicOr(err, ERR_NLIST);
         });
     }
     __syncthreads();   // the coefficients, and the LDS columns change their layout

@@ -470,3 +470,30 @@ def test_dpd_batches_of_small_and_large_boxes(beads):
         d = x - o.state()[0]
         assert np.abs(d - s.L * np.round(d / s.L)).max() < 5e-6
         assert np.abs(v - o.state()[1]).max() < 1e-4
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("pair", ["wca", "dpd"])
+@pytest.mark.parametrize("size", [0.0, 2.5, 4.6])
+def test_evaluation_in_a_far_box_matches_oracle(size, pair, precision):
+    """Edges beyond the quantised scan's reach: a sparse box, a cluster whose beads fit the staged rows and one whose
+    central beads do not, half of it across the corner of the box.  Soft pairs as in the other evaluations; WCA beads on
+    a lattice with 2 % noise, whose forces go with the 14th power of distances good to a rounding of the edge in
+    float input and to 1e-13 in double."""
+    n, L = 700, 2000.0
+    rng = np.random.default_rng(7)
+    if pair == "wca":
+        k = np.arange(n)
+        x = np.stack([k % 9, k // 9 % 9, k // 81], 1) * (1.08 if size else 200.0) + rng.normal(0.0, 0.02, size=(n, 3)) - 3.0
+        ff = synth.ForceField(gamma=0.0)
+    else:
+        x = rng.normal(0.0, size, size=(n, 3)) if size else rng.uniform(0.0, L, size=(n, 3))
+        ff = synth.ff_dpd(gamma_dpd=20.0)
+    s = synth.System(L=L, x=synth.wrap(np.mod(x, L), L), v=rng.normal(size=(n, 3)), type=np.ones(n, dtype=np.int32),
+                     reactive=np.zeros(n, dtype=np.uint8), bonds=np.zeros((0, 4), dtype=np.int32))
+    g, o = both(s, ff, synth.RuleSet(every=0), precision=precision, generate=False)
+    tol = 1e-10 if precision == 0 else 1e-5
+    ok, msg = forces_close(g.forces(), o.forces(), tol)
+    assert ok, msg
+    eg, eo = g.energy(), o.energy()
+    assert np.all(np.abs(eg - eo) <= 10 * tol * np.maximum(1.0, np.abs(eo))), (eg, eo)
