@@ -171,11 +171,19 @@ __device__ __forceinline__ bool create_admits(const Params& P, int ti, const Tab
 // The kernel picks LANES from the list's length: one thread per bead fills the GPU from
 // 2^16 listed beads (one against four: 75 and 113 us with 850k listed, 36 and 38 with
 // 100k, 33 and 20 with 30k).  With a creation distance beyond one cell edge the float
-// scan of 5 x 5 x 5 cells serves, and a short list takes up to sixteen threads (1M-bead
-// case of the 1-bead model, about 30k listed: 52 / 33 / 24 / 20 us with 2 / 4 / 8 / 16).
+// scan of 5 x 5 x 5 cells serves, and where the quantised copy does not, that of 3 x 3 x
+// 3; a short list then takes up to sixteen threads (1M-bead case of the 1-bead model,
+// about 30k listed: 52 / 33 / 24 / 20 us with 2 / 4 / 8 / 16; 200k beads clustered in an
+// edge of 3,000, 100k listed: a sweep in 41 ms with one, 27 with eight).  A batch goes
+// by its first box.
+__device__ __forceinline__ uint32_t create_cut(const Box& X, double& reach) {
+    reach = sqrtf(X.pf_create2) * 1.000001f;
+    return X.wide_create ? 0u : quantised_cut(X, reach);
+}
 template <bool BATCH>
 __device__ __forceinline__ int create_lanes_for(const Params& P, int nl) {
-    if (!(BATCH ? P.rep[0] : P.box).wide_create) return nl >= (1 << 16) ? 1 : 4;
+    double reach;
+    if (create_cut(BATCH ? P.rep[0] : P.box, reach)) return nl >= (1 << 16) ? 1 : 4;
     return nl >= (1 << 19) ? 1 : (nl >= (1 << 18) ? 2 : (nl >= (1 << 17) ? 4 : (nl >= (1 << 16) ? 8 : 16)));
 }
 
@@ -205,8 +213,8 @@ __device__ __forceinline__ void nominate_create_one(const Params& P, const int n
     const int tid = threadIdx.x;
     int cnt = -1;
     if constexpr (LANES == 1 || LANES == 4) {   // what the quantised scan splits into
-        const float reach = sqrtf(cut2) * 1.000001f;
-        const uint32_t cutq = X.wide_create ? 0u : quantised_cut(X, reach);
+        double reach;
+        const uint32_t cutq = create_cut(X, reach);
         if (cutq) {
             const uint32_t kinds = partner_types & ~1u;   // kind 0 is no partner
             int at = 0;

@@ -497,3 +497,27 @@ def test_evaluation_in_a_far_box_matches_oracle(size, pair, precision):
     assert ok, msg
     eg, eo = g.energy(), o.energy()
     assert np.all(np.abs(eg - eo) <= 10 * tol * np.maximum(1.0, np.abs(eo))), (eg, eo)
+
+
+@pytest.mark.parametrize("order", [1, -1])
+def test_creation_scan_of_a_mixed_batch(order):
+    """A sweep over a batch whose first box chooses the threads per bead, one that the quantised scan serves and one that
+    it does not, either first: the bonds of the standalone handles."""
+    import paper_1108_4214_amd as pk
+    rules = synth.RuleSet(every=1, rules=[("create", 1, 1, 2, 0.99, 1.0), ("create", 2, 0, 3, 0.7, 0.6)])
+    reps = []
+    for n, L in [(2500, 9.0), (3000, 2500.0), (40, 3.4)][::order]:
+        rng = np.random.default_rng(n)
+        x = np.mod(rng.normal(0.0, 3.0, size=(n, 3)), L) if L > 1000.0 else rng.uniform(0.0, L, size=(n, 3))
+        s = synth.System(L=L, x=synth.wrap(x, L), v=np.zeros((n, 3)), type=rng.integers(1, 5, size=n).astype(np.int32),
+                         reactive=np.ones(n, dtype=np.uint8), bonds=np.zeros((0, 4), dtype=np.int32))
+        reps.append(pk.System(n, L, n).configure(s, synth.ForceField(), rules))
+    b = pk.Batch(reps)
+    b.sweep_now()
+    rows, off = b.bonds(), 0
+    for g in reps:
+        g.sweep_now()
+        mine = rows[(rows[:, 0] >= off) & (rows[:, 0] < off + g.n)].copy()
+        mine[:, :2] -= off
+        assert len(mine) > 0 and np.array_equal(mine, g.bonds())
+        off += g.n
