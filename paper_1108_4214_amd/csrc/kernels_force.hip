@@ -67,7 +67,7 @@ __device__ __forceinline__ R r_sqrt(R v);
 template <>
 __device__ __forceinline__ double r_sqrt<double>(double v) { return sqrt(v); }
 template <>
-__device__ __forceinline__ float r_sqrt<float>(float v) { return __builtin_amdgcn_sqrtf(v); }
+__device__ __forceinline__ float r_sqrt<float>(float v) { return sqrtf(v); }   // correctly rounded
 // Reciprocal and reciprocal square root.  In float the native single-instruction
 // approximations (about 1 ulp), far inside the float path's error budget.  In
 // double the native approximation (relative error e0 below 2^-23) and one
