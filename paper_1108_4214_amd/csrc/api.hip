@@ -46,9 +46,12 @@ namespace {
 
 const int kMaxBlock = DB_MAX_BLOCK;
 const double kSkinDefault = 0.55;
-// DPD at density 3 with the pair friction of the paper moves some bead far enough
-// to need a new list after about every step whatever the skin, so the thinnest
-// skin (shortest lists, cells of edge r_c) costs least per step
+// DPD at density 3 with the pair friction of the paper moves some bead by 0.06 a step.
+// A list that outlasts a step needs a skin of 0.2 and then holds 22 entries instead of
+// 13, which costs the step more than the saved build: 300k beads of solution 125 us a
+// step at 0.02 (a list per step), 140 at 0.13 (a list per step), 132 at 0.22 (every
+// second step), 139 at 0.32 (2 lists in 5 steps); 400k of the 1-bead model in FP64 368,
+// 427, 538 and 511
 const double kSkinDefaultDPD = 0.02;
 
 // host memory the device writes its end-of-block report into (mapped, pinned)

@@ -23,7 +23,7 @@
 #define DB_RCAP 768          // region entries a tile of the step kernel stages in LDS
 #define DB_CAPA 448          // angle work items of a tile
 #define DB_CAPD 224          // dihedral work items of a tile
-#define DB_XS_PAD 8          // entries after the float position copy that a run of the cell scan may read
+#define DB_XS_PAD 8          // entries after the float and the quantised position copy that a scan may read
 #define DB_SLOT_BITS 26      // the float position copy packs slot | type << 26 | reactive << 31
 #define DB_MAX_BEADS ((1 << DB_SLOT_BITS) - 1)
 

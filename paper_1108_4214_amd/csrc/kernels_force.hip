@@ -700,7 +700,7 @@ __device__ __forceinline__ void bond_force(const Params& P, const Coef<R>& C, in
 // root or arctangent; a wave that holds a wider bend takes those too.
 // Step kernel, before and after these two functions: FP64 20.6 -> 15.5 us (80k-bead
 // duplex box), 175 -> 149 us (400k beads, 1-bead model in DPD solvent); FP32 69.9 ->
-// 66.8 us with 28.4M -> 20.8M VALU instructions per launch (1M-bead duplex box: its
+// 66.8 us with 28.4M -> 21.1M VALU instructions per launch (1M-bead duplex box: its
 // gathers now weigh as much, 26M L1 accesses).
 template <typename R, int MODE>
 __device__ __forceinline__ void angle_share(const Coef<R>& C, bool centre, int t, const V3<R>& s1, const V3<R>& w,
@@ -847,8 +847,9 @@ __device__ __forceinline__ void dihedral_ends(const Coef<R>& C, int t, R b1x, R 
 // The FP32 kernel with DPD pairs keeps these: at the paper's friction a DPD step
 // multiplies small velocity differences, so that another rounding of the forces
 // shows in every velocity after some twenty steps, and mixed runs with DPD keep the
-// rounding, and with it the trajectories, that they have always had.  (There the
-// bonded terms of the few chain beads are a small part of the step.)
+// rounding, and with it the trajectories, that they have always had.  It costs 1 % of
+// the step kernel with chains in solvent (300k beads 50.8 and 50.5 us) and 3 % in the
+// 1-bead model (400k beads 99.1 and 96.2 us).
 template <typename R, int MODE, int PAIR>
 constexpr bool unfused() { return MODE == MODE_FORCE && sizeof(R) == 4 && PAIR == PAIR_DPD; }
 
@@ -2182,7 +2183,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_step_tile(const Params* __restrict
 // the scan, as the list build is (instructions and L1 accesses).  500k duplex beads,
 // energies in FP64: 75 us and 5 us for the final sum, against 400 us for a serial loop
 // over the candidates' double positions and 247 us for a final sum by six threads;
-// 100k beads of DPD solution in FP32 74 + 5 (46 once reordered and evenly spread: it
+// 100k beads of DPD solution in FP32 76 + 5 (46 once reordered and evenly spread: it
 // waits for neighbours' data from the other dies' memory, and for crowded beads)
 // against 644 + 51;
 // 191k duplex beads, forces in FP32: 28 us against 42 for a list build and a force pass.
@@ -2297,7 +2298,7 @@ __global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 4 ? 3 : 1) void k_eval(const
                 if (raw <= EV_STAGE) break;
                 // more than the rows hold: the next rows' worth.  (Random solvent at density 3
                 // has such a bead in every few thousand, and the pass lasts as long as they
-                // do: 104 us with the float scan for them, 74 so.  The list build, whose scan
+                // do: 104 us with the float scan for them, 76 so.  The list build, whose scan
                 // the second one costs registers, 72 -> 81 us at 1M beads, keeps that.)
                 skip += EV_STAGE;
                 // A scan per 28 neighbours grows with their square: in a collapsed system,
@@ -2387,8 +2388,8 @@ __global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 4 ? 3 : 1) void k_eval(const
 }
 
 // The workgroups' sums in a fixed order: every thread adds up every 1024th partial
-// of each of the six (so that all are in flight together: a serial chain over a
-// million beads' partials took 247 us), then a tree over the threads.
+// of each of the six (so that all are in flight together: a serial chain over the
+// partials of 500k beads took 247 us), then a tree over the threads.
 #define DB_FINAL_BLOCK 1024
 __global__ __launch_bounds__(DB_FINAL_BLOCK) void k_energy_final(const double* __restrict__ epart, int nblocks,
                                                                  double* __restrict__ out) {
