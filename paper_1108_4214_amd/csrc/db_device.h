@@ -143,8 +143,11 @@ __device__ __forceinline__ int creates_as(int meta) { return meta_reactive(meta)
 // Coordinates in units of edge / 65536, rounded down: differences of these 16-bit
 // words wrap as the box does, so the nearest image comes with the subtraction.  Each
 // is low by less than 1.01 units, and a difference off by less than that.  The second
-// word's upper half holds the type of a reactive bead, 0 for others.
-__device__ __forceinline__ uint32_t quantum(float x, float units) { return (uint32_t)(x * units) & 0xFFFFu; }
+// word's upper half holds the type of a reactive bead, 0 for others.  Every input, NaN
+// and infinities included, converts in range (as cell_coord below).
+__device__ __forceinline__ uint32_t quantum(float x, float units) {
+    return (uint32_t)fminf(fmaxf(x * units, 0.0f), 65536.0f) & 0xFFFFu;
+}
 __device__ __forceinline__ uint2 quantise(const Box& X, float x, float y, float z, int kind) {
     const float units = (float)(65536.0 / X.L);
     return make_uint2(quantum(x, units) | quantum(y, units) << 16, quantum(z, units) | (uint32_t)kind << 16);

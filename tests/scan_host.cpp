@@ -90,7 +90,23 @@ static void check(const Box& X, const std::vector<int>& start, const std::vector
     }
 }
 
+// words of a position that a step has just left not finite or outside its box: read before the host stops, they may
+// be anything but must not come from a conversion out of range (the build traps on one)
+static void odd_positions() {
+    Box X{};
+    for (double L : {2.0, 125.99, 65536.0}) {
+        X.L = L;
+        for (float v : {NAN, INFINITY, -INFINITY, -1e30f, 1e30f, -0.25f, (float)L, (float)(2.0 * L)}) quantise(X, v, v, v, 3);
+        const uint2 top = quantise(X, (float)L, 0.0f, (float)(0.5 * L), 0);
+        if (top.x || (top.y & 0xFFFFu) != 32768u) {
+            printf("the edge of a box of %g is not its origin: %x %x\n", L, top.x, top.y);
+            exit(1);
+        }
+    }
+}
+
 int main() {
+    odd_positions();
     std::mt19937_64 gen(5);
     auto uniform = [&](double a) { return a * (double)(gen() >> 11) * 0x1p-53; };
     for (int nc : {3, 4, 5, 9})

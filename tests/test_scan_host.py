@@ -12,7 +12,8 @@ def test_quantised_scan_reads_its_arrays_and_visits_every_neighbour_once(tmp_pat
     (tmp_path / "hip").mkdir()
     (tmp_path / "hip" / "hip_runtime.h").write_text("#pragma once\n")   # the program brings what it needs of it
     exe = str(tmp_path / "scan")
-    subprocess.run(["/opt/rocm/llvm/bin/clang++", "-std=c++17", "-O1", "-w", "-ffp-contract=off", "-I", str(tmp_path),
-                    "-I", CSRC, os.path.join(HERE, "scan_host.cpp"), "-o", exe], check=True)
+    subprocess.run(["/opt/rocm/llvm/bin/clang++", "-std=c++17", "-O1", "-w", "-ffp-contract=off",
+                    "-fsanitize=float-cast-overflow", "-fsanitize-trap=all", "-I", str(tmp_path), "-I", CSRC,
+                    os.path.join(HERE, "scan_host.cpp"), "-o", exe], check=True)
     run = subprocess.run([exe], capture_output=True, text=True, timeout=100)
-    assert run.returncode == 0, run.stdout
+    assert run.returncode == 0, (run.returncode, run.stdout)
