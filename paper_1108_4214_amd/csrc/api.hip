@@ -1291,6 +1291,10 @@ static bool list_reuse_allowed(const db_ctx* c) {
     return true;
 }
 
+// steps of a block from the number that the bound admits (a system near rest admits
+// more than an integer holds)
+static int interval_of(double want) { return (int)std::max(1.0, std::min((double)kMaxBlock, std::floor(want))); }
+
 int db_step(db_ctx* c, int64_t nsteps) {
     if (!c || nsteps < 0) return DB_EINVAL;
     int rc = ready(c);
@@ -1398,15 +1402,13 @@ int db_step(db_ctx* c, int64_t nsteps) {
             // extrapolate the largest displacement linearly in time from the block's
             // end (exact for ballistic motion, cautious for diffusive motion, so the
             // interval keeps growing while the test passes)
-            int want = dlast > 0 ? (int)std::floor(0.8 * skin * (double)done / dlast) + 1 : kMaxBlock;
-            c->rebuild_interval = std::max(1, std::min(kMaxBlock, want));
+            c->rebuild_interval = dlast > 0 ? interval_of(1.0 + 0.8 * skin * (double)done / dlast) : kMaxBlock;
         } else if (std::isfinite(skin) && vmax > 0) {
             // as many steps as the bound admits at the speeds just seen: the last
             // step's input is want - 1 steps from the list.  A step too many is one
             // launch that stores nothing; a step too few may split the steps between
             // two sweeps into two blocks, each with its own list
-            int want = (int)std::floor(1.0 + skin / (1.02 * dt * vmax));
-            c->rebuild_interval = std::max(1, std::min(kMaxBlock, want));
+            c->rebuild_interval = interval_of(1.0 + skin / (1.02 * dt * vmax));
         } else if (!std::isfinite(skin)) {
             c->rebuild_interval = kMaxBlock;
         }

@@ -521,3 +521,19 @@ def test_creation_scan_of_a_mixed_batch(order):
         mine[:, :2] -= off
         assert len(mine) > 0 and np.array_equal(mine, g.bonds())
         off += g.n
+
+
+@pytest.mark.parametrize("pair", ["wca", "dpd"])
+def test_a_system_near_rest_keeps_its_lists(pair):
+    """Speeds of 1e-12 admit more steps per list than an integer holds: blocks are as long as they may be (64 steps
+    after a first of 8), not single steps."""
+    import paper_1108_4214_amd as pk
+    k = np.arange(125)
+    rng = np.random.default_rng(3)
+    s = synth.System(L=12.5, x=1.0 + 2.5 * np.stack([k % 5, k // 5 % 5, k // 25], 1), v=1e-12 * rng.normal(size=(125, 3)),
+                     type=np.ones(125, dtype=np.int32), reactive=np.zeros(125, dtype=np.uint8),
+                     bonds=np.zeros((0, 4), dtype=np.int32))
+    ff = synth.ForceField(gamma=0.0) if pair == "wca" else synth.ff_dpd(gamma_dpd=0.0)
+    g = pk.System(s.n, s.L, 3).configure(s, ff, synth.RuleSet(every=0))
+    g.step(8 + 3 * 64)
+    assert g.stats()["rebuilds"] <= 4 and g.stats()["steps"] == 200
