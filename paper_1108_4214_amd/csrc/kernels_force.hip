@@ -1220,17 +1220,27 @@ __device__ __forceinline__ void step_amplitudes(const Params& P, const BlockBase
 // (TRACK: DPD) is the largest displacement measured after the steps so far.  Every
 // wave forms it (the step before has ended, so its words are final); the first one
 // records it for the next step, and that this step was stored for the block's report.
+// Its words are requested with others of the kernel's begin, between gate_words and
+// gate_open.
+struct GateWords {
+    float m;         // the lane's maximum of the step before
+    double before;   // its bound
+};
+__device__ __forceinline__ GateWords gate_words(const Gate& G) {
+    static_assert(DB_VMAX_SPREAD == 64, "one word per lane");
+    if (G.q == 0) return GateWords{0.0f, G.d0};
+    return GateWords{__uint_as_float(G.vmax2[(size_t)(G.q - 1) * DB_VMAX_SPREAD + (threadIdx.x & 63)]),
+                     G.bound[(G.q - 1) & 1]};
+}
 template <bool TRACK>
-__device__ __forceinline__ bool gate_open(const Params& P, const Gate& G) {
-    double b = G.d0;
+__device__ __forceinline__ bool gate_open(const Params& P, const Gate& G, const GateWords& w) {
+    double b = w.before;
     if (G.q > 0) {
-        float m = __uint_as_float(G.vmax2[(size_t)(G.q - 1) * DB_VMAX_SPREAD + (threadIdx.x & 63)]);
-        static_assert(DB_VMAX_SPREAD == 64, "one word per lane");
-        const double before = G.bound[(G.q - 1) & 1];
+        float m = w.m;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
         const double v = sqrt((double)m);
-        b = TRACK ? fmax(before, v) : before + P.dt * v;
+        b = TRACK ? fmax(w.before, v) : w.before + P.dt * v;
     }
     const bool open = b <= G.limit;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1262,15 +1272,18 @@ void k_step(const Params* __restrict__ Pp, Bank B, NList NL, Halo H, double4* __
     const Params& P = *Pp;
     const int n = P.n;
     if (base) step_amplitudes(P, base, step, pref, dsig, G);
-    // Past the list's validity: the same for every thread of the launch.  Waiting for
-    // the answer here costs nothing that shows (10 steps of 40 beads 202 and 204 us, 20
-    // of 80k in FP64 518 and 503, with the force pass ahead of the wait and so), and a
-    // block cut short does not run up to 63 force passes for nothing.
-    if (!gate_open<PAIR == PAIR_DPD>(P, G)) return;
     __shared__ Coef<R> C;
     __shared__ R hs[3][DB_MAXU][DB_BLOCK];
+    const GateWords gw = gate_words(G);
     load_coef<R>(P, C);
+    const bool open = gate_open<PAIR == PAIR_DPD>(P, G, gw);
     __syncthreads();
+    // Past the list's validity, the same for every thread of the launch: nothing of the
+    // step is kept, and a block cut short does not run up to 63 force passes for nothing.
+    // The gate's words travel with the coefficients', so that the answer costs no latency
+    // of its own (20 steps of 80k beads in FP64 522 us with the force pass ahead of it, 528
+    // waiting for it first, 520 so; of 3k beads 382, 382 and 378).
+    if (!open) return;
     int tile = xcd_tile(blockIdx.x, gridDim.x);
     int i = tile * DB_BLOCK + threadIdx.x;
     bool active = i < n;
@@ -2007,7 +2020,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_step_tile(const Params* __restrict
         double dsig = 0.0;
         step_amplitudes(P, base, step, pref, dsig, G);
     }
-    if (!gate_open<false>(P, G)) return;   // the same for every thread of the launch
+    if (!gate_open<false>(P, G, gate_words(G))) return;   // the same for every thread of the launch
     const Box& X = P.box;
     __shared__ Coef<R> C;
     __shared__ double rx[DB_RCAP], ry[DB_RCAP], rz[DB_RCAP];
