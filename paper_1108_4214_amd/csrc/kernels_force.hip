@@ -2318,7 +2318,6 @@ __global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 4 ? 3 : 1) void k_eval(const
                 // thousands within reach, the float scan takes them all in one (8,000 beads
                 // within 0.9, FP64 energies: 124 ms by repeated scans, 6 so)
                 if (skip > DB_NLCAP) {
-                    a = Acc<R>();   // nothing but the pairs so far
                     serial = true;
                     break;
                 }
@@ -2327,6 +2326,7 @@ __global__ __launch_bounds__(DB_BLOCK, sizeof(R) == 4 ? 3 : 1) void k_eval(const
             }
             int c = 0;   // entries of the bead's Verlet list, counted where they may be too many
             if (serial) {
+                a = Acc<R>();   // nothing but the pairs so far
                 scan_cells(X, cstart, xs, i, xi, scan2, [&](int j, int) {
                     if (E.has(j)) return;
                     pair(B.x[j], vel_of(j));
